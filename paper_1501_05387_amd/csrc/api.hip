@@ -563,10 +563,8 @@ static void with_pred(Ctx &c, Graph &g, int32_t *pred_out, hipStream_t s, Run ru
     if (!pred_out) return;
     int32_t *pd = pred_out;
     const bool dev = is_device_ptr(pred_out);
-    if (!dev) {
-        c.arena.reserve(al256(4ull * g.n));
-        pd = c.arena.take<int32_t>(g.n);
-    }
+    c.arena.reserve((dev ? 0 : al256(4ull * g.n)) + pred_scratch_bytes(g));   // the solve's scratch is no longer needed
+    if (!dev) pd = c.arena.take<int32_t>(g.n);
     run(pd);
     if (!dev) deliver(c, pred_out, pd, 4ull * g.n, s);
 }

@@ -384,6 +384,8 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s);
 void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena &ar);
 void run_sssp(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStream_t s);
 // Predecessors from finished distances (device pointers): the first neighbour one step closer.
+// The caller has reserved pred_scratch_bytes in the context's arena.
+size_t pred_scratch_bytes(const Graph &g);
 void run_bfs_pred(Ctx &c, Graph &g, int32_t src, const int32_t *depth, int32_t *pred, hipStream_t s);
 void run_sssp_pred(Ctx &c, Graph &g, int32_t src, const uint32_t *dist, int32_t *pred, hipStream_t s);
 // Bucket width factor x mean edge weight, clamped to [1, 1e9].

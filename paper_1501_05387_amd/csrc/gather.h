@@ -139,7 +139,7 @@ __global__ __launch_bounds__(GFR_BLOCK) void gather_fixup(FrontierQ q, const uin
 
 // Visit every edge (v_i -> u) of the queue once, load-balanced over edges:
 // op(u, v_i) runs on one lane per edge.  Used where the per-edge work has no
-// reduction (connected-component hooking).
+// reduction (the 2-hop pushes).
 template <int CH, class Op>
 __global__ __launch_bounds__(GFR_BLOCK) void for_each_edge(FrontierQ q, const uint32_t *nf_p,
                                                            const uint32_t *mf_p, const int32_t *C,

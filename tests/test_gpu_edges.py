@@ -50,3 +50,46 @@ def test_predecessor_row_lengths(ctx, where):
     _, p = ctx.sssp(g, src, pred=True)
     assert np.array_equal(_host(p), oracle.sssp_pred(row, col, w, src)[1])
     g.free()
+
+
+def _union(*graphs):
+    """Disjoint union of CSR graphs, vertices numbered one graph after another."""
+    rows, cols, v0, e0 = [np.zeros(1, np.int64)], [], 0, 0
+    for row, col in graphs:
+        rows.append(row[1:].astype(np.int64) + e0)
+        cols.append(col.astype(np.int64) + v0)
+        v0 += row.size - 1
+        e0 += col.size
+    return np.concatenate(rows).astype(np.int32), np.concatenate(cols).astype(np.int32)
+
+
+def _renumbered(row, col, perm):
+    u = np.repeat(np.arange(row.size - 1), np.diff(row))
+    keep = u < col
+    return graphgen.from_edges(row.size - 1, perm[u[keep]], perm[col[keep]])
+
+
+CC_GRAPHS = {
+    "one vertex": lambda: (np.zeros(2, np.int32), np.zeros(0, np.int32)),
+    "no edges": lambda: (np.zeros(301, np.int32), np.zeros(0, np.int32)),
+    "pair": lambda: graphgen.from_edges(2, np.array([0]), np.array([1])),
+    # no component holds most of the sample: every list is swept, hubs among them
+    "two hubs apart": lambda: _union(graphgen.rmat(11, seed=5), graphgen.rmat(11, seed=6),
+                                     (np.zeros(70, np.int32), np.zeros(0, np.int32)), graphgen.grid(40)),
+    # chains that the first two neighbours leave long, in ascending, descending and mixed order
+    "path up": lambda: graphgen.from_edges(70001, np.arange(70000), np.arange(1, 70001)),
+    "path mixed": lambda: graphgen.from_edges(*(lambda p: (50021, p[:-1], p[1:]))(
+        np.random.default_rng(3).permutation(50021))),
+    "lattice mixed": lambda: _renumbered(*graphgen.grid(200), np.random.default_rng(4).permutation(40000)),
+    "many small": lambda: graphgen.from_edges(30011, np.arange(0, 30009, 3), np.arange(2, 30011, 3)),
+}
+
+
+@pytest.mark.parametrize("name", list(CC_GRAPHS))
+def test_components_of_skipped_and_swept_lists(ctx, name):
+    row, col = CC_GRAPHS[name]()
+    g = ctx.graph_load_csr(row, col)
+    lab, k = ctx.cc(g)
+    want, kw = oracle.cc(row, col)
+    assert k == kw and np.array_equal(_host(lab), want)
+    g.free()

@@ -26,15 +26,17 @@
 //
 // On mesh-like graphs (small, even degrees, long diameters) the frontier is
 // kept as mark bytes only, with one launch per level (bfs_bitmap_level): each
-// thread scans 16 mark bytes of the current level, consumes them, and expands
-// every marked vertex's list (through a per-work-group LDS list); an unvisited
-// neighbour (depth still -1) gets its depth and a mark byte for the next level,
-// with plain idempotent stores
-// (Sec. 4.5).  There is no queue and no compaction: on such graphs a level's
-// cost is the chain of memory round trips of its launches, and this halves the
-// number of launches and drops the compaction's scan and look-back.  Each
-// work-group records whether it marked anything; the next launch's first
-// work-group reads those flags and ends the traversal when all are zero.
+// thread owns a run of vertices, consumes their marks of the current level,
+// stores the depths of those not yet visited and lists them in LDS; the
+// work-group expands the list and marks unvisited neighbours for the next
+// level, with plain idempotent stores (Sec. 4.5).  There is no queue and no
+// compaction: on such graphs a level's cost is the chain of memory round trips
+// of its launches, and this halves the number of launches and drops the
+// compaction's scan and look-back.  Each work-group records whether it held a
+// vertex; a later launch's first work-group reads those flags and ends the
+// traversal when all are zero.
+#include <algorithm>
+
 #include "compact.h"
 #include "device.h"
 #include "engine.h"
@@ -362,20 +364,118 @@ __global__ void bfs_init(BfsArgs a, int32_t src, uint32_t chunk, uint32_t force,
     for (uint32_t c = threadIdx.x; (uint64_t)c * chunk < (uint64_t)deg; c += blockDim.x) a.q.part[c] = 0;
 }
 
+// ------------------------------------------------------------ mark-byte levels
+// What bounds a level is its chain of dependent memory round trips (marks, row
+// offsets, columns, depths), each about a microsecond, and the launch; so a
+// level should walk that chain once.  A work-group takes one span of
+// BM_BLOCK * VPT vertices: VPT is chosen so that all spans of the graph are
+// resident at once (up to 2^24 vertices), and a span's marked vertices, listed
+// in LDS as 16-bit offsets, usually fit one turn of the threads.  Spans keep
+// the expansion in vertex order, which a mesh rewards: neighbouring frontier
+// vertices share the lines of their rows and depths.  (A list of the frontier
+// in discovery order was slower, 85 us against 20 for levels of 600 K
+// vertices, for that reason.)
+//
+// On the 4096^2 lattice (139 levels of 120 K vertices on average) a level took
+// 19.5 us in two turns of 4 KB spans that probed and stored depth[] by edge.  It
+// takes 4 to 9 us while the frontier is thin and 43 us at its widest (600 K
+// vertices: about 200 MB of distinct lines, 4.6 TB/s), 13 us on average.
+//
+// The first levels, up to BM_SOLO vertices each, are run by one work-group in
+// one launch with the frontier in LDS (38 levels in 167 us there).
+constexpr int BM_BLOCK = 512;
+constexpr int BM_SOLO_BLOCK = 1024;
+constexpr uint32_t BM_SOLO = BM_SOLO_BLOCK;      // widest level that one work-group runs
+constexpr uint32_t BM_SOLO_LIST = 4096;          // discoveries it can list; more are marked at once
+constexpr int32_t BM_SOLO_LEVELS = 1 << 14;      // most levels in one launch
+
 struct BmArgs {
     const int32_t *R;
     const int32_t *C;
     int32_t n;
     int32_t *depth;
-    uint8_t *mk[2];      // mark bytes of the frontier, by level parity (n rounded up to 16 bytes)
-    uint32_t *flags;     // [2][gridDim]: did the work-group mark a vertex, by level parity
+    uint8_t *mk[2];      // mark bytes of the frontier, by level parity (n rounded up to 64 bytes)
+    uint32_t *vis;       // visited bitmap (null: depth[] alone says what is visited)
+    uint32_t *flags;     // [2][gridDim]: did the work-group hold a vertex of the level, by level parity
     BfsCtl *ctl;
 };
 
+// Levels 0, 1, ... while they hold at most BM_SOLO vertices (one work-group).
+// A discovery is claimed with an atomicOr on its visited bit, so the list
+// holds every vertex once.  Leaves ctl->level at the first level not expanded,
+// whose vertices it marks, unvisited as the level kernel expects them;
+// DIR_DONE if there is none.
+__global__ __launch_bounds__(BM_SOLO_BLOCK) void bfs_bitmap_head(BmArgs a, int32_t src)
+{
+    __shared__ int32_t s_cur[BM_SOLO], s_new[BM_SOLO_LIST];
+    __shared__ uint32_t s_cnt;
+    uint32_t cnt = 1;
+    if (threadIdx.x == 0) {
+        a.depth[src] = 0;
+        atomicOr(a.vis + (src >> 5), 1u << (src & 31));
+        s_cur[0] = src;
+        s_cnt = 0;
+    }
+    __syncthreads();
+    int32_t L = 0;
+    for (;;) {
+        if (threadIdx.x < cnt) {
+            const int32_t v = s_cur[threadIdx.x];
+            const int32_t e1 = a.R[v + 1];
+            for (int32_t e = a.R[v]; e < e1; e += 8) {
+                int32_t u[8];
+                uint32_t old[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) u[k] = a.C[min(e + k, e1 - 1)];
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (e + k < e1) old[k] = atomicOr(a.vis + (u[k] >> 5), 1u << (u[k] & 31));
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    if (e + k < e1 && !(old[k] >> (u[k] & 31) & 1u)) {
+                        a.depth[u[k]] = L + 1;
+                        const uint32_t i = atomicAdd(&s_cnt, 1u);
+                        if (i < BM_SOLO_LIST) {
+                            s_new[i] = u[k];
+                        } else {   // too wide for the head: handed over at once
+                            atomicAnd(a.vis + (u[k] >> 5), ~(1u << (u[k] & 31)));
+                            a.mk[(L & 1) ^ 1][u[k]] = 1;
+                        }
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        cnt = s_cnt;
+        ++L;
+        if (cnt == 0 || cnt > BM_SOLO || L == BM_SOLO_LEVELS) break;
+        __syncthreads();
+        if (threadIdx.x == 0) s_cnt = 0;
+        if (threadIdx.x < cnt) s_cur[threadIdx.x] = s_new[threadIdx.x];
+        __syncthreads();
+    }
+    for (uint32_t i = threadIdx.x; i < min(cnt, BM_SOLO_LIST); i += BM_SOLO_BLOCK) {
+        const int32_t u = s_new[i];
+        atomicAnd(a.vis + (u >> 5), ~(1u << (u & 31)));
+        a.mk[L & 1][u] = 1;
+    }
+    if (threadIdx.x == 0) {
+        BfsCtl *ctl = a.ctl;
+        ctl->dir = cnt > 0 ? DIR_PUSH : DIR_DONE;
+        ctl->level = L;
+        ctl->err = 0;
+        ctl->push_levels = (uint32_t)L;
+        ctl->pull_levels = 0;
+        ctl->push_entries = ctl->push_edges = ctl->push_new = 0ull;
+        ctl->pull_unvisited = ctl->pull_inspected = ctl->pull_new = 0ull;
+        ctl->nf = (uint32_t)L;   // the head's levels
+    }
+}
+
+// without the head: the source alone is marked
 __global__ void bfs_bitmap_init(BmArgs a, int32_t src)
 {
     BfsCtl *ctl = a.ctl;
-    a.depth[src] = 0;
     a.mk[0][src] = 1;
     ctl->dir = DIR_PUSH;
     ctl->level = 0;
@@ -383,76 +483,108 @@ __global__ void bfs_bitmap_init(BmArgs a, int32_t src)
     ctl->push_levels = ctl->pull_levels = 0;
     ctl->push_entries = ctl->push_edges = ctl->push_new = 0ull;
     ctl->pull_unvisited = ctl->pull_inspected = ctl->pull_new = 0ull;
+    ctl->nf = 0;
 }
 
-// level L of a mark-byte traversal (one launch per level; L is the launch index)
-__global__ __launch_bounds__(GFR_BLOCK) void bfs_bitmap_level(BmArgs a, int32_t L)
+// One level per launch: launch i runs level ctl->nf + i.  VIS: probe and keep
+// the visited bitmap.  A thread owns VPT consecutive vertices: it alone
+// consumes their marks, drops those already visited, sets their visited bits
+// and stores their depths.  An edge therefore only probes one bit (the bitmap
+// of 2^24 vertices is 2 MB and stays in L2; depth[] is 64 MB) and stores one
+// mark.  A probe that misses the bit of a vertex of the same level, which its
+// owner is just setting, leaves a mark that the owner drops in the next launch.
+template <int VPT, bool VIS>
+__global__ __launch_bounds__(BM_BLOCK) void bfs_bitmap_level(BmArgs a, int32_t launch)
 {
+    static_assert((VPT == 16 || VPT == 32) && BM_BLOCK * VPT <= 65536, "16-bit offsets in a span");
+    constexpr int VEC = VPT / 16;
+    constexpr int SPAN = BM_BLOCK * VPT;
+    __shared__ uint16_t s_v[SPAN];
+    __shared__ uint32_t s_cnt;
     BfsCtl *ctl = a.ctl;
-    if (ctl->dir == DIR_DONE) return;
     const uint32_t G = gridDim.x;
+    if (ctl->dir == DIR_DONE) return;
+    const int32_t L = (int32_t)ctl->nf + launch;
     uint8_t *cur = a.mk[L & 1];
     uint8_t *nxt = a.mk[(L & 1) ^ 1];
-    if (L > 0 && blockIdx.x == 0) {
-        // the previous level marked nothing: this level's frontier is empty
+    int found = 0;
+    const size_t nown = ((size_t)a.n + VPT - 1) / VPT;   // owners (the mark bytes are padded to whole ones)
+    for (size_t span = blockIdx.x; span * BM_BLOCK < nown; span += G) {
+        if (threadIdx.x == 0) s_cnt = 0;
+        __syncthreads();
+        const size_t own = span * BM_BLOCK + threadIdx.x;
+        uint4 w[VEC];
+#pragma unroll
+        for (int j = 0; j < VEC; ++j)
+            w[j] = own < nown ? *(const uint4 *)(cur + own * VPT + 16 * j) : make_uint4(0u, 0u, 0u, 0u);
+        uint32_t m = 0;
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) {
+            if ((w[j].x | w[j].y | w[j].z | w[j].w) == 0u) continue;
+            *(uint4 *)(cur + own * VPT + 16 * j) = make_uint4(0u, 0u, 0u, 0u);   // consumed
+            const uint32_t ws[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                m |= ((ws[k] & 0x01010101u) * 0x00204081u >> 21 & 0xFu) << (16 * j + 4 * k);
+        }
+        const int32_t v0 = (int32_t)(span * SPAN);
+        if (m) {
+            if (VIS) {
+                if (VPT == 32) {
+                    const uint32_t old = a.vis[own];
+                    m &= ~old;
+                    if (m) a.vis[own] = old | m;
+                } else {
+                    uint16_t *vw = (uint16_t *)a.vis + own;
+                    const uint32_t old = *vw;
+                    m &= ~old;
+                    if (m) *vw = (uint16_t)(old | m);
+                }
+            }
+            uint32_t i = m ? atomicAdd(&s_cnt, (uint32_t)__popc(m)) : 0u;
+            while (m) {
+                const int b = __ffs(m) - 1;
+                m &= m - 1;
+                s_v[i++] = (uint16_t)(threadIdx.x * VPT + b);
+            }
+        }
+        __syncthreads();
+        const uint32_t cnt = s_cnt;   // at most SPAN
+        for (uint32_t i = threadIdx.x; i < cnt; i += BM_BLOCK) {
+            const int32_t v = v0 + s_v[i];   // only vertices < n are ever marked
+            int32_t e = a.R[v];
+            const int32_t e1 = a.R[v + 1];
+            if (!VIS && a.depth[v] >= 0) continue;
+            a.depth[v] = L;
+            found = 1;
+            for (; e < e1; e += 8) {
+                int32_t u[8];
+                uint32_t d[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) u[k] = a.C[min(e + k, e1 - 1)];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) d[k] = VIS ? a.vis[u[k] >> 5] >> (u[k] & 31) & 1u : (uint32_t)(a.depth[u[k]] >= 0);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    if (e + k < e1 && !d[k]) nxt[u[k]] = 1;
+                }
+            }
+        }
+        __syncthreads();   // the list is reused by the next span
+    }
+    if (launch > 0 && blockIdx.x == 0) {
+        // the previous level held no vertex: it was the end
         const uint32_t *fprev = a.flags + (size_t)((L & 1) ^ 1) * G;
         uint32_t any = 0;
-        for (uint32_t i = threadIdx.x; i < G; i += GFR_BLOCK) any |= fprev[i];
+        for (uint32_t i = threadIdx.x; i < G; i += BM_BLOCK) any |= fprev[i];
         if (!__syncthreads_or((int)any)) {
             if (threadIdx.x == 0) {
-                ctl->level = L;
-                ctl->push_levels = (uint32_t)L;
+                ctl->level = L - 1;
+                ctl->push_levels = (uint32_t)(L - 1);
                 ctl->dir = DIR_DONE;
             }
             return;
         }
-    }
-    // Rounds of 256 chunks of 16 mark bytes per work-group: the marked
-    // vertices of a round are appended to an LDS list, then the whole group
-    // expands the list, one vertex per thread, with the column and depth loads
-    // of eight edges issued before any test.
-    constexpr int BM_LIST = GFR_BLOCK * 16;
-    __shared__ int32_t s_v[BM_LIST];
-    __shared__ uint32_t s_cnt;
-    int found = 0;
-    const size_t nchunks = ((size_t)a.n + 15) / 16;
-    for (size_t c0 = (size_t)blockIdx.x * GFR_BLOCK; c0 < nchunks; c0 += (size_t)G * GFR_BLOCK) {
-        if (threadIdx.x == 0) s_cnt = 0;
-        __syncthreads();
-        const size_t ci = c0 + threadIdx.x;
-        if (ci < nchunks) {
-            uint4 *p = (uint4 *)(cur + ci * 16);
-            const uint4 w = *p;
-            if ((w.x | w.y | w.z | w.w) != 0u) {
-                *p = make_uint4(0u, 0u, 0u, 0u);   // consumed: clean when it next receives marks
-                const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                for (int j = 0; j < 16; ++j)
-                    if ((ws[j >> 2] >> (8 * (j & 3))) & 0xFFu) s_v[atomicAdd(&s_cnt, 1u)] = (int32_t)(ci * 16 + j);
-            }
-        }
-        __syncthreads();
-        const uint32_t cnt = s_cnt;   // at most 16 per thread: fits BM_LIST
-        for (uint32_t i = threadIdx.x; i < cnt; i += GFR_BLOCK) {
-            const int32_t v = s_v[i];   // only vertices < n are ever marked
-            const int32_t e1 = a.R[v + 1];
-            for (int32_t e = a.R[v]; e < e1; e += 8) {
-                int32_t u[8], d[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) u[k] = a.C[min(e + k, e1 - 1)];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) d[k] = a.depth[u[k]];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    if (e + k < e1 && d[k] < 0) {
-                        a.depth[u[k]] = L + 1;
-                        nxt[u[k]] = 1;
-                        found = 1;
-                    }
-                }
-            }
-        }
-        __syncthreads();   // the list is reused by the next round
     }
     found = __syncthreads_or(found);
     if (threadIdx.x == 0) a.flags[(size_t)(L & 1) * G + blockIdx.x] = (uint32_t)found;
@@ -461,9 +593,15 @@ __global__ __launch_bounds__(GFR_BLOCK) void bfs_bitmap_level(BmArgs a, int32_t 
 static void run_bfs_bitmap(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena &ar)
 {
     const int32_t n = g.n;
-    const size_t nb = ((size_t)n + 15) / 16 * 16;
-    const int G = grid_blocks(c, 8);
-    ar.reserve(2 * al256(nb) + al256(8ull * G) + al256(sizeof(BfsCtl)));
+    const size_t nb = ((size_t)n + 63) / 64 * 64;
+    // 32 vertices per thread where 16 would leave more spans than are resident (four groups per CU)
+    const bool wide = (size_t)n > (size_t)grid_blocks(c, 4) * BM_BLOCK * 16;
+    const size_t span = (size_t)BM_BLOCK * (wide ? 32 : 16);
+    const int G = (int)std::min(((size_t)n + span - 1) / span, (size_t)grid_blocks(c, 16));
+    const size_t least = 2 * al256(nb) + al256(8ull * G) + al256(sizeof(BfsCtl));
+    // a fixed scratch too small for the visited bitmap does without it
+    const bool vis = !ar.fixed || least + al256(nb / 8) <= ar.fixed_bytes;
+    ar.reserve(least + (vis ? al256(nb / 8) : 0));
     BmArgs a;
     a.R = g.R.as<int32_t>();
     a.C = g.C.as<int32_t>();
@@ -471,23 +609,31 @@ static void run_bfs_bitmap(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStr
     a.depth = depth;
     a.mk[0] = ar.take<uint8_t>(nb);
     a.mk[1] = ar.take<uint8_t>(nb);
+    a.vis = vis ? ar.take<uint32_t>(nb / 32) : nullptr;
     a.flags = ar.take<uint32_t>(2ull * G);
     a.ctl = ar.take<BfsCtl>(1);
     fill_u32(depth, 0xFFFFFFFFu, (size_t)n, s);
-    fill_u32(a.mk[0], 0u, nb / 4, s);
-    fill_u32(a.mk[1], 0u, nb / 4, s);
-    fill_u32(a.flags, 0u, 2ull * G, s);
-    hipLaunchKernelGGL(bfs_bitmap_init, dim3(1), dim3(1), 0, s, a, src);
+    fill_u32(a.mk[0], 0u, (2 * al256(nb) + (vis ? al256(nb / 8) : 0)) / 4, s);   // marks and bitmap (adjacent)
+    // one thread per vertex: only where no vertex has a long row
+    const bool head = vis && g.cls == GRAPH_MESH;
+    if (head)
+        hipLaunchKernelGGL(bfs_bitmap_head, dim3(1), dim3(BM_SOLO_BLOCK), 0, s, a, src);
+    else
+        hipLaunchKernelGGL(bfs_bitmap_init, dim3(1), dim3(1), 0, s, a, src);
     GFR_LAUNCH_CHECK();
-    int32_t level = 0;
+    int32_t i = 0;
     auto launch = [&]() {
         c.ktimer.run("bfs_bitmap_level", s, [&]() {
-            hipLaunchKernelGGL(bfs_bitmap_level, dim3(G), dim3(GFR_BLOCK), 0, s, a, level);
+            const dim3 grid(G), block(BM_BLOCK);
+            if (!vis) hipLaunchKernelGGL((bfs_bitmap_level<32, false>), grid, block, 0, s, a, i);
+            else if (wide) hipLaunchKernelGGL((bfs_bitmap_level<32, true>), grid, block, 0, s, a, i);
+            else hipLaunchKernelGGL((bfs_bitmap_level<16, true>), grid, block, 0, s, a, i);
         });
-        ++level;
+        ++i;
     };
-    const int32_t launched = run_until_done(c, &a.ctl->dir, DIR_DONE, g.levels_hint() + 2, (int64_t)n + 4, s,
-                                            launch);
+    const int32_t launched = run_until_done(c, &a.ctl->dir, DIR_DONE,
+                                            g.bitmap_launch_hint.load(std::memory_order_relaxed) + 2,
+                                            (int64_t)n + 4, s, launch);
     BfsCtl h;
     GFR_HIP(hipMemcpyAsync(c.pinned, a.ctl, sizeof(BfsCtl), hipMemcpyDeviceToHost, s));
     GFR_HIP(hipStreamSynchronize(s));
@@ -497,7 +643,7 @@ static void run_bfs_bitmap(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStr
     c.stats.v["pull_levels"] += 0.0;
     c.stats.v["launches"] += launched;
     c.stats.v["solves"] += 1.0;
-    g.bfs_levels_hint.store(h.level, std::memory_order_relaxed);
+    g.bitmap_launch_hint.store(h.level + 1 - (int32_t)h.nf, std::memory_order_relaxed);
 }
 
 void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s) { run_bfs(c, g, src, depth, s, c.arena); }

@@ -127,6 +127,7 @@ struct Graph {
     // one source's); written by every solve on the graph, also from the
     // serving threads, hence atomic (relaxed: a stale hint only sizes a batch)
     std::atomic<int32_t> bfs_levels_hint{8};
+    std::atomic<int32_t> bitmap_launch_hint{8};
     std::atomic<int32_t> sssp_iter_hint{16};
     std::atomic<int32_t> msbfs_levels_hint{8};
     std::atomic<int32_t> bsssp_iter_hint{16};

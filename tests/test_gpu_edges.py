@@ -93,3 +93,57 @@ def test_components_of_skipped_and_swept_lists(ctx, name):
     want, kw = oracle.cc(row, col)
     assert k == kw and np.array_equal(_host(lab), want)
     g.free()
+
+
+def _tree(arity, depth):
+    n = sum(arity ** d for d in range(depth + 1))
+    child = np.arange(1, n)
+    return graphgen.from_edges(n, (child - 1) // arity, child)
+
+
+def _at_the_end(n, row, col):
+    """The graph as the last vertices of n."""
+    lead = n - (row.size - 1)
+    return np.concatenate([np.zeros(lead, np.int32), row]), col + np.int32(lead)
+
+
+MESHES = {   # name: (graph, source)
+    "span -1": (lambda: graphgen.from_edges(8191, np.arange(8190), np.arange(1, 8191)), 4000),
+    "span": (lambda: graphgen.from_edges(8192, np.arange(8191), np.arange(1, 8192)), 8191),
+    "span +1": (lambda: graphgen.from_edges(8193, np.arange(8192), np.arange(1, 8193)), 0),
+    # more levels than one launch of the head runs
+    "long path": (lambda: graphgen.from_edges(17003, np.arange(17002), np.arange(1, 17003)), 0),
+    # 729 vertices discover 6,561: past the head's width and past its list
+    "tree": (lambda: _tree(9, 5), 0),
+    "ragged lattice": (lambda: graphgen.grid(217), 1234),
+    "source without edges": (lambda: _union((np.zeros(41, np.int32), np.zeros(0, np.int32)), graphgen.grid(30)), 7),
+    # owners of 32 vertices each
+    "wide": (lambda: _at_the_end(8400001, *graphgen.grid(211)), 8400001 - 5),
+}
+
+
+@pytest.mark.parametrize("name", list(MESHES))
+def test_mark_byte_levels(ctx, name):
+    make, src = MESHES[name]
+    row, col = make()
+    g = ctx.graph_load_csr(row, col)
+    want = oracle.bfs(row, col, src)
+    for _ in range(2):
+        assert np.array_equal(_host(ctx.bfs(g, src)), want)
+        assert ctx.stat("levels") == want.max() + 1
+    out = ctx.bfs(g, src)
+    assert np.array_equal(_host(ctx.bfs_noalloc(g, src, out)), want)
+    g.free()
+
+
+def test_mark_byte_levels_in_scratch_too_small_for_the_bitmap(ctx):
+    n = 33000001   # two mark arrays fit 64 MiB, the visited bitmap does not
+    row, col = _at_the_end(n, *graphgen.grid(150))
+    g = ctx.graph_load_csr(row, col)
+    src = n - 1
+    out = ctx.bfs(g, src)
+    want = oracle.bfs(row, col, src)
+    assert np.array_equal(_host(out), want)
+    out.fill_(7)
+    assert np.array_equal(_host(ctx.bfs_noalloc(g, src, out)), want)
+    g.free()

@@ -99,9 +99,10 @@ const char *gfr_last_error(const gfr_ctx *ctx);
  *                     SSSP): an iteration whose near queue carries more than m / alpha edges
  *                     relaxes by a pull sweep over every list (one pre-checked atomicMin per
  *                     vertex instead of per edge); 0 (default) = always push
- *   "sssp.frontier"   0 auto (= 1), 1 queue iterations (advance + compaction), 2 mark-byte
- *                     iterations: the near and far sets are bytes per vertex, one launch
- *                     per iteration
+ *   "sssp.frontier"   0 auto (2 on mesh-class graphs with at most 6 entries per vertex unless
+ *                     a pull direction is set, else 1),
+ *                     1 queue iterations (advance + compaction), 2 mark-byte iterations: the
+ *                     near and far sets are bytes per vertex, one launch per iteration
  *   "sssp.delta"      bucket width of the near/far priority queue (Sec. 4.5);
  *                     0 = "sssp.delta_factor" (default 2) times the mean edge weight
  *   "advance.chunk"   edges per work-group chunk of the load-balanced advance (Sec. 4.4),

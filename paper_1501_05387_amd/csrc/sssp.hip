@@ -17,6 +17,8 @@
 //                entries inside the new bucket become the near queue, the rest
 //                stay far (Sec. 4.5).  The last work-group runs the control.
 // The host enqueues iterations speculatively (see bfs.hip).
+#include <algorithm>
+
 #include "compact.h"
 #include "device.h"
 #include "engine.h"
@@ -462,19 +464,32 @@ static void sssp_check_unfit(Ctx &c, Graph &g, const uint32_t *dist, uint32_t *f
     if (*(volatile uint32_t *)c.pinned) fail(GFR_E_INVALID, "sssp: a distance does not fit below 0xFFFFFFFF");
 }
 
-// ------------------------------------------------------------ mark-byte levels
-// Option sssp.frontier 2: the frontier stays as mark bytes and an iteration
-// is one launch, as for the mark-byte BFS levels: a launch
-// scans the current near marks (consuming them), lists the marked vertices
-// in LDS and relaxes each one's edges, marking improved vertices near
-// (distance inside the bucket) or far.  A launch that follows one which
-// marked nothing near splits instead (Sec. 4.5): the bucket moves past the
-// smallest far distance, far-marked vertices inside it are relaxed, those
-// beyond it keep their marks, those below it (relaxed since) drop theirs.
-// No launch waits for another work-group: every work-group of launch L reads
-// the per-group words of launch L-1 and derives the same mode and bucket.
+// ------------------------------------------------------------ mark-byte iterations
+// On mesh-like graphs the near set stays as mark bytes and an iteration is one
+// launch, as for the mark-byte BFS levels: every work-group takes one span of
+// vertices, whose owners (one thread per run of VPT vertices) consume the near
+// marks and list the vertices in LDS; the work-group relaxes their edges,
+// marking improved vertices near (distance inside the bucket) or far.  A
+// launch that follows one which marked nothing near splits instead (Sec. 4.5):
+// the bucket moves past the smallest far distance, far-marked vertices inside
+// it are relaxed, those beyond it keep their marks, those below it (relaxed
+// since) drop theirs.  No launch waits for another work-group: every
+// work-group of launch L reads the per-group words of launch L - 1 and derives
+// the same mode and bucket.
+//
+// What bounds an iteration is its chain of dependent memory round trips: with
+// 20 to 40 K near vertices there is little else.  The words of the previous
+// launch, the state and the span's own marks are loaded together, the counters
+// are kept per work-group (an atomic per work-group on one address costs 11 ns
+// each, one after another), and no compaction follows.  On the 1999^2 lattice
+// an iteration takes 6 to 8 us while the near set is thin (10.4 on average);
+// the queue form takes 21 (compaction 14.2, relax 6.9) for as many iterations.
 
 enum : uint32_t { SM_RELAX = 0, SM_SPLIT = 1, SM_DONE = 2 };
+
+constexpr int SM_BLOCK = 512;
+constexpr int SM_WAVES = SM_BLOCK / 64;
+constexpr int32_t SM_ROUNDS = 8;
 
 struct SmState {
     uint32_t mode, hi;            // this launch's mode and bucket bound [.., hi)
@@ -488,15 +503,21 @@ struct SmCtl {
     unsigned long long near_entries, relaxed, improvements, far_entries;
 };
 
+// counters of one work-group, summed after the solve
+struct SmCount {
+    unsigned long long v[4];      // near entries, relaxed, improvements, far marks
+};
+
 struct SmArgs {
     const int32_t *R;
     const int32_t *C;
     const uint32_t *W;
     int32_t n;
     uint32_t *dist;
-    uint8_t *mk[2];               // near marks by launch parity (n rounded up to 16 bytes)
+    uint8_t *mk[2];               // near marks by launch parity (n rounded up to 32 bytes)
     uint8_t *far;                 // far marks
     unsigned long long *flags;    // [2][G]: (smallest far distance marked or kept) << 32 | bits, by parity
+    SmCount *count;               // [G]
     SmState *st;                  // [2] by parity, written by work-group 0
     SmCtl *ctl;
     uint32_t delta;
@@ -508,7 +529,10 @@ __global__ void sssp_marks_init(SmArgs a, int32_t src, uint32_t G)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     // the launch "before" launch 0 marked the source near in work-group 0
-    if (i < G) a.flags[G + i] = i == 0 ? (0xFFFFFFFFull << 32) | SMF_NEAR : (0xFFFFFFFFull << 32);
+    if (i < G) {
+        a.flags[G + i] = i == 0 ? (0xFFFFFFFFull << 32) | SMF_NEAR : (0xFFFFFFFFull << 32);
+        a.count[i] = SmCount{{0ull, 0ull, 0ull, 0ull}};
+    }
     if (i == 0) {
         a.dist[src] = 0u;
         a.mk[0][src] = 1;
@@ -517,21 +541,61 @@ __global__ void sssp_marks_init(SmArgs a, int32_t src, uint32_t G)
         ctl->done = 0;
         ctl->unfit = 0;
         ctl->iter = ctl->splits = 0;
-        ctl->near_entries = ctl->relaxed = ctl->improvements = ctl->far_entries = 0ull;
     }
 }
 
-__global__ __launch_bounds__(GFR_BLOCK) void sssp_mark_level(SmArgs a, int32_t L)
+// the owner's marks of VPT vertices as a bit mask
+template <int VPT>
+__device__ __forceinline__ uint32_t owner_mask(const uint4 (&w)[VPT / 16])
 {
+    uint32_t m = 0;
+#pragma unroll
+    for (int j = 0; j < VPT / 16; ++j) {
+        const uint32_t ws[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) m |= ((ws[k] & 0x01010101u) * 0x00204081u >> 21 & 0xFu) << (16 * j + 4 * k);
+    }
+    return m;
+}
+
+// LOCAL: an improved vertex of the work-group's own span is not marked but
+// appended to the list and relaxed in the same launch, up to `rounds` times
+// round the list; a round is the same chain of memory round trips without the
+// launch.  The distances that the span has reached are kept in LDS: an edge's
+// own read of dist[] may come from a line loaded before the span's last
+// improvement, and relaxing with a value that only looks smaller could go round
+// in circles.  A vertex is in the list at most once (a bit in LDS), so SPAN
+// entries are enough.
+template <int VPT, bool LOCAL>
+__global__ __launch_bounds__(SM_BLOCK) void sssp_mark_level(SmArgs a, int32_t L, int32_t rounds)
+{
+    static_assert((VPT == 16 || VPT == 32) && SM_BLOCK * VPT <= 65536, "16-bit offsets in a span");
+    constexpr int VEC = VPT / 16;
+    constexpr int SPAN = SM_BLOCK * VPT;
     const uint32_t G = gridDim.x;
     const int lane = lane_id(), wave = threadIdx.x / 64;
-    __shared__ uint32_t s_bits[GFR_WAVES], s_min[GFR_WAVES];
+    __shared__ uint32_t s_bits[SM_WAVES], s_min[SM_WAVES];
     __shared__ SmState s_st;
+    __shared__ uint16_t s_v[SPAN];                      // circular list of vertices to relax
+    __shared__ uint32_t s_best[LOCAL ? SPAN : 1];       // smallest distance known here
+    __shared__ uint32_t s_in[LOCAL ? SPAN / 32 : 1];    // listed
+    __shared__ uint32_t s_tail;
+    uint8_t *near = a.mk[L & 1];
+    uint8_t *nxt = a.mk[(L & 1) ^ 1];
+    const size_t nown = ((size_t)a.n + VPT - 1) / VPT;   // (the mark bytes are padded to whole owners)
+    uint4 w[VEC];
+    auto load_marks = [&](const uint8_t *p, size_t own) {
+#pragma unroll
+        for (int j = 0; j < VEC; ++j)
+            w[j] = own < nown ? *(const uint4 *)(p + own * VPT + 16 * j) : make_uint4(0u, 0u, 0u, 0u);
+    };
+    load_marks(near, (size_t)blockIdx.x * SM_BLOCK + threadIdx.x);
+    const SmState p = a.st[(L & 1) ^ 1];
     // this launch's mode and bucket from the previous launch's words
     {
         const unsigned long long *pf = a.flags + (size_t)((L & 1) ^ 1) * G;
         uint32_t bits = 0, mn = 0xFFFFFFFFu;
-        for (uint32_t i = threadIdx.x; i < G; i += GFR_BLOCK) {
+        for (uint32_t i = threadIdx.x; i < G; i += SM_BLOCK) {
             const unsigned long long f = pf[i];
             bits |= (uint32_t)f;
             mn = min(mn, (uint32_t)(f >> 32));
@@ -544,11 +608,10 @@ __global__ __launch_bounds__(GFR_BLOCK) void sssp_mark_level(SmArgs a, int32_t L
         }
         __syncthreads();
         if (threadIdx.x == 0) {
-            for (int w = 1; w < GFR_WAVES; ++w) {
-                bits |= s_bits[w];
-                mn = min(mn, s_min[w]);
+            for (int i = 1; i < SM_WAVES; ++i) {
+                bits |= s_bits[i];
+                mn = min(mn, s_min[i]);
             }
-            const SmState p = a.st[(L & 1) ^ 1];
             // far marks left after the previous launch: a split examined
             // every older one, so only its kept and new ones remain
             const uint32_t far_any = (p.mode == SM_SPLIT ? 0u : p.far_any) | ((bits & SMF_FAR) ? 1u : 0u);
@@ -570,7 +633,7 @@ __global__ __launch_bounds__(GFR_BLOCK) void sssp_mark_level(SmArgs a, int32_t L
             if (blockIdx.x == 0) {
                 a.st[L & 1] = st;
                 if (st.mode == SM_DONE) {
-                    a.ctl->iter = (uint32_t)L;
+                    if (p.mode != SM_DONE) a.ctl->iter = (uint32_t)L;
                     a.ctl->done = 1u;
                 } else if (st.mode == SM_SPLIT) {
                     a.ctl->splits += 1u;
@@ -585,111 +648,163 @@ __global__ __launch_bounds__(GFR_BLOCK) void sssp_mark_level(SmArgs a, int32_t L
         if (threadIdx.x == 0) *myflag = 0xFFFFFFFFull << 32;
         return;
     }
-    const uint32_t hi = st.hi;
-    const uint32_t lo = a.st[(L & 1) ^ 1].hi;   // previous bucket bound (splits drop marks below it)
-    uint8_t *cur = st.mode == SM_RELAX ? a.mk[L & 1] : a.far;
-    uint8_t *nxt = a.mk[(L & 1) ^ 1];
-    constexpr int SM_LIST = GFR_BLOCK * 16;
-    __shared__ int32_t s_v[SM_LIST];
-    __shared__ uint32_t s_cnt;
+    const bool split = st.mode == SM_SPLIT;
+    const uint32_t hi = st.hi, lo = p.hi;   // lo: previous bucket bound (splits drop marks below it)
     uint32_t bits = 0, fmin = 0xFFFFFFFFu;
     uint32_t nent = 0, nrel = 0, nimp = 0, nfar = 0;
     bool ovf = false;
-    const size_t nchunks = ((size_t)a.n + 15) / 16;
-    for (size_t c0 = (size_t)blockIdx.x * GFR_BLOCK; c0 < nchunks; c0 += (size_t)G * GFR_BLOCK) {
-        if (threadIdx.x == 0) s_cnt = 0;
+    for (size_t span = blockIdx.x; span * SM_BLOCK < nown; span += G) {
+        const size_t own = span * SM_BLOCK + threadIdx.x;
+        if (split || span != blockIdx.x) load_marks(split ? a.far : near, own);
+        const uint32_t mine = owner_mask<VPT>(w);
+        if (!__syncthreads_or((int)mine)) continue;
+        if (LOCAL) {
+            for (uint32_t i = threadIdx.x; i < SPAN; i += SM_BLOCK) s_best[i] = 0xFFFFFFFFu;
+            if (threadIdx.x < SPAN / 32) s_in[threadIdx.x] = 0;
+        }
+        if (threadIdx.x == 0) s_tail = 0;
         __syncthreads();
-        const size_t ci = c0 + threadIdx.x;
-        if (ci < nchunks) {
-            uint4 *p = (uint4 *)(cur + ci * 16);
-            const uint4 w = *p;
-            if ((w.x | w.y | w.z | w.w) != 0u) {
-                const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-                if (st.mode == SM_RELAX) {
-                    *p = make_uint4(0u, 0u, 0u, 0u);   // consumed
+        const uint32_t v0 = (uint32_t)(span * SPAN);
+        uint32_t m = mine;
+        if (m) {
+            if (!split) {
 #pragma unroll
-                    for (int j = 0; j < 16; ++j)
-                        if ((ws[j >> 2] >> (8 * (j & 3))) & 0xFFu) s_v[atomicAdd(&s_cnt, 1u)] = (int32_t)(ci * 16 + j);
-                } else {
-                    // split: inside the bucket -> relax now; beyond -> keep;
-                    // below the previous bound -> relaxed since, dropped.
-                    // Marks leave by byte stores: relaxations of this launch
-                    // set far marks in the same array (a kept mark is never
-                    // rewritten, and a cleared vertex, whose distance is below
-                    // the bucket bound, can only gain a near mark)
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        if ((ws[j >> 2] >> (8 * (j & 3))) & 0xFFu) {
-                            const int32_t v = (int32_t)(ci * 16 + j);
-                            const uint32_t d = a.dist[v];
-                            if (d >= hi) {
-                                bits |= SMF_FAR;
-                                fmin = min(fmin, d);
-                            } else {
-                                cur[v] = 0;
-                                if (d >= lo) s_v[atomicAdd(&s_cnt, 1u)] = v;
-                            }
-                        }
+                for (int j = 0; j < VEC; ++j)
+                    *(uint4 *)(near + own * VPT + 16 * j) = make_uint4(0u, 0u, 0u, 0u);   // consumed
+            }
+            uint32_t rest = split || LOCAL ? m : 0u;
+            while (rest) {
+                const int b = __ffs(rest) - 1;
+                rest &= rest - 1;
+                const uint32_t d = a.dist[own * VPT + b];
+                if (split) {
+                    // inside the bucket -> relax now; beyond -> keep; below the
+                    // previous bound -> relaxed since, dropped.  Marks leave by
+                    // byte stores: relaxations of this launch set far marks in
+                    // the same array (a kept mark is never rewritten, and a
+                    // cleared vertex, whose distance is below the bucket bound,
+                    // can only gain a near mark)
+                    if (d >= hi) {
+                        bits |= SMF_FAR;
+                        fmin = min(fmin, d);
+                        m &= ~(1u << b);
+                        continue;
                     }
+                    a.far[own * VPT + b] = 0;
+                    if (d < lo) {
+                        m &= ~(1u << b);
+                        continue;
+                    }
+                }
+                if (LOCAL) s_best[threadIdx.x * VPT + b] = d;
+            }
+            if (m) {
+                uint32_t i = atomicAdd(&s_tail, (uint32_t)__popc(m));
+                if (LOCAL) atomicOr(&s_in[threadIdx.x * VPT / 32], m << (threadIdx.x * VPT % 32));
+                while (m) {
+                    s_v[i++] = (uint16_t)(threadIdx.x * VPT + __ffs(m) - 1);
+                    m &= m - 1;
                 }
             }
         }
-        __syncthreads();
-        const uint32_t cnt = s_cnt;   // at most 16 per thread: fits SM_LIST
-        nent += threadIdx.x < cnt ? (cnt - threadIdx.x + GFR_BLOCK - 1) / GFR_BLOCK : 0u;
-        for (uint32_t i = threadIdx.x; i < cnt; i += GFR_BLOCK) {
-            const int32_t v = s_v[i];   // only vertices < n are ever marked
-            const uint32_t du = a.dist[v];
-            const int32_t e1 = a.R[v + 1];
-            for (int32_t e = a.R[v]; e < e1; e += 8) {
-                int32_t u[8];
-                uint32_t w[8], d[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int32_t ek = min(e + k, e1 - 1);
-                    u[k] = a.C[ek];
-                    w[k] = a.W[ek];
+        uint32_t head = 0, lim = SPAN;
+        for (int32_t round = 0; LOCAL || round == 0; ++round) {
+            __syncthreads();
+            const uint32_t put = s_tail, tail = min(put, lim);
+            __syncthreads();
+            if (tail == head) break;
+            if (put > lim) {   // uniform: places that were not given out
+                if (threadIdx.x == 0) s_tail = tail;
+                __syncthreads();
+            }
+            lim = head + SPAN;   // entries from head on are still being read in this round
+            if (round == rounds) {   // the rest goes to the next launch
+                for (uint32_t i = head + threadIdx.x; i < tail; i += SM_BLOCK) nxt[v0 + s_v[i % SPAN]] = 1;
+                bits |= SMF_NEAR;
+                break;
+            }
+            for (uint32_t i = head + threadIdx.x; i < tail; i += SM_BLOCK) {
+                const uint32_t off = s_v[i % SPAN];
+                const int32_t v = (int32_t)(v0 + off);   // only vertices < n are ever marked
+                ++nent;
+                uint32_t du;
+                if (LOCAL) {
+                    // unlisted before the distance is read: an improvement that finds the bit set is read here
+                    atomicAnd(&s_in[off >> 5], ~(1u << (off & 31)));
+                    asm volatile("" ::: "memory");
+                    du = atomicMin(&s_best[off], 0xFFFFFFFFu);
+                } else {
+                    du = a.dist[v];
                 }
+                const int32_t e1 = a.R[v + 1];
+                for (int32_t e = a.R[v]; e < e1; e += 8) {
+                    int32_t u[8];
+                    uint32_t wt[8], d[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) d[k] = a.dist[u[k]];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    if (e + k >= e1) continue;
-                    ++nrel;
-                    const unsigned long long nd64 = (unsigned long long)du + w[k];
-                    if (nd64 >= 0xFFFFFFFFull) {
-                        ovf = true;
-                        continue;
+                    for (int k = 0; k < 8; ++k) {
+                        const int32_t ek = min(e + k, e1 - 1);
+                        u[k] = a.C[ek];
+                        wt[k] = a.W[ek];
                     }
-                    const uint32_t nd = (uint32_t)nd64;
-                    if (nd < d[k]) {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) d[k] = a.dist[u[k]];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        if (e + k >= e1) continue;
+                        ++nrel;
+                        const unsigned long long nd64 = (unsigned long long)du + wt[k];
+                        if (nd64 >= 0xFFFFFFFFull) {
+                            ovf = true;
+                            continue;
+                        }
+                        const uint32_t nd = (uint32_t)nd64;
+                        if (nd >= d[k]) continue;
+                        const uint32_t uo = (uint32_t)u[k] - v0;
+                        const bool here = LOCAL && uo < SPAN;
+                        if (here && atomicMin(&s_best[uo], nd) <= nd) continue;   // known here already
                         // non-returning: the mark follows the pre-check (a
                         // superset of the true improvements)
                         atomicMin(a.dist + u[k], nd);
                         ++nimp;
-                        if (nd < hi) {
-                            nxt[u[k]] = 1;
-                            bits |= SMF_NEAR;
-                        } else {
+                        if (nd >= hi) {
                             a.far[u[k]] = 1;
                             bits |= SMF_FAR;
                             fmin = min(fmin, nd);
                             ++nfar;
+                        } else if (here) {
+                            const uint32_t bit = 1u << (uo & 31);
+                            if (!(atomicOr(&s_in[uo >> 5], bit) & bit)) {
+                                const uint32_t i = atomicAdd(&s_tail, 1u);
+                                if (i < lim) {
+                                    s_v[i % SPAN] = (uint16_t)uo;
+                                } else {   // no place: for the next launch (its bit keeps it from being listed again)
+                                    nxt[u[k]] = 1;
+                                    bits |= SMF_NEAR;
+                                }
+                            }
+                        } else {
+                            nxt[u[k]] = 1;
+                            bits |= SMF_NEAR;
                         }
                     }
                 }
             }
+            head = tail;
         }
-        __syncthreads();   // the list is reused by the next round
+        __syncthreads();   // LDS is reused by the next span
     }
     // per-group word for the next launch, counters, unfit sums
+    if (!__syncthreads_or((int)(nent | bits))) {   // nothing held or kept
+        if (threadIdx.x == 0) *myflag = 0xFFFFFFFFull << 32;
+        return;
+    }
     bits = wave_or_u32(bits);
     fmin = wave_min_u32(fmin);
     nent = wave_sum_u32(nent);
     nrel = wave_sum_u32(nrel);
     nimp = wave_sum_u32(nimp);
     nfar = wave_sum_u32(nfar);
-    __shared__ uint32_t s_c[4][GFR_WAVES];
+    __shared__ uint32_t s_c[4][SM_WAVES];
     if (lane == 0) {
         s_bits[wave] = bits;
         s_min[wave] = fmin;
@@ -700,27 +815,50 @@ __global__ __launch_bounds__(GFR_BLOCK) void sssp_mark_level(SmArgs a, int32_t L
     }
     ovf = __syncthreads_or((int)ovf) != 0;
     if (threadIdx.x == 0) {
-        uint32_t t[4] = {0u, 0u, 0u, 0u};
-        for (int w = 0; w < GFR_WAVES; ++w) {
-            bits |= s_bits[w];
-            fmin = min(fmin, s_min[w]);
-            for (int k = 0; k < 4; ++k) t[k] += s_c[k][w];
+        for (int i = 1; i < SM_WAVES; ++i) {
+            bits |= s_bits[i];
+            fmin = min(fmin, s_min[i]);
         }
         *myflag = ((unsigned long long)fmin << 32) | bits;
         if (ovf) a.ctl->unfit = 1u;
-        if (t[0]) atomicAdd(&a.ctl->near_entries, (unsigned long long)t[0]);
-        if (t[1]) atomicAdd(&a.ctl->relaxed, (unsigned long long)t[1]);
-        if (t[2]) atomicAdd(&a.ctl->improvements, (unsigned long long)t[2]);
-        if (t[3]) atomicAdd(&a.ctl->far_entries, (unsigned long long)t[3]);
     }
+    if (threadIdx.x < 4) {
+        uint32_t t = 0;
+        for (int i = 0; i < SM_WAVES; ++i) t += s_c[threadIdx.x][i];
+        if (t) a.count[blockIdx.x].v[threadIdx.x] += t;   // this work-group's own
+    }
+}
+
+// the counters of all work-groups, one wave per counter
+__global__ void sssp_marks_sum(SmArgs a, uint32_t G)
+{
+    const int lane = lane_id(), k = threadIdx.x / 64;
+    unsigned long long s = 0;
+    for (uint32_t i = lane; i < G; i += 64) s += a.count[i].v[k];
+    s = wave_sum_u64(s);
+    if (lane == 0) (&a.ctl->near_entries)[k] = s;
 }
 
 static void run_sssp_marks(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStream_t s, uint32_t delta)
 {
     const int32_t n = g.n;
-    const size_t nb = ((size_t)n + 15) / 16 * 16;
-    const int G = grid_blocks(c, 4);
-    c.arena.reserve(3 * al256(nb) + al256(16ull * G) + al256(2 * sizeof(SmState)) + al256(sizeof(SmCtl)) + al256(4));
+    const size_t nb = ((size_t)n + 31) / 32 * 32;
+    // Rounds inside a launch where all spans are resident with the 49 KB of
+    // LDS they take (three groups per CU).  Lattices of 100^2, 300^2, 1000^2
+    // and 1999^2 at the packaged bucket width: 0.55, 0.97, 1.41 and 2.08 ms with
+    // rounds, 0.85, 1.27, 1.59 and 2.39 without; 4096^2, where groups wait for
+    // LDS, 7.2 against 6.6.  One, three, eight and 32 rounds on 1999^2: 2.91,
+    // 2.12, 2.08 and 3.06 ms (too many carry distances far that are improved later).
+    // Beyond that, 32 vertices per thread where 16 would leave more spans than
+    // are resident (four groups per CU).
+    const size_t cu_span = (size_t)c.num_cu * SM_BLOCK * 16;
+    const bool local = (size_t)n <= 3 * cu_span, wide = (size_t)n > 4 * cu_span;
+    const size_t span = (size_t)SM_BLOCK * (wide ? 32 : 16);
+    const int G = (int)std::min(((size_t)n + span - 1) / span, (size_t)grid_blocks(c, 4));
+    // a graph of one span has nothing to wait for: its bucket is finished in one launch
+    const int32_t rounds = G == 1 ? INT32_MAX : SM_ROUNDS;
+    c.arena.reserve(3 * al256(nb) + al256(16ull * G) + al256(sizeof(SmCount) * (size_t)G) + al256(2 * sizeof(SmState)) +
+                    al256(sizeof(SmCtl)) + al256(4));
     SmArgs a;
     memset(&a, 0, sizeof a);
     a.R = g.R.as<int32_t>();
@@ -732,25 +870,28 @@ static void run_sssp_marks(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStr
     a.mk[1] = c.arena.take<uint8_t>(nb);
     a.far = c.arena.take<uint8_t>(nb);
     a.flags = c.arena.take<unsigned long long>(2ull * G);
+    a.count = c.arena.take<SmCount>(G);
     a.st = c.arena.take<SmState>(2);
     a.ctl = c.arena.take<SmCtl>(1);
     uint32_t *unfit_flag = c.arena.take<uint32_t>(1);
     a.delta = delta;
     fill_u32(dist, 0xFFFFFFFFu, (size_t)n, s);
-    fill_u32(a.mk[0], 0u, nb / 4, s);
-    fill_u32(a.mk[1], 0u, nb / 4, s);
-    fill_u32(a.far, 0u, nb / 4, s);
+    fill_u32(a.mk[0], 0u, 3 * al256(nb) / 4, s);   // near and far marks (adjacent)
     hipLaunchKernelGGL(sssp_marks_init, dim3((G + 255) / 256), dim3(256), 0, s, a, src, (uint32_t)G);
     GFR_LAUNCH_CHECK();
     int32_t level = 0;
     auto launch = [&]() {
         c.ktimer.run("sssp_mark_level", s, [&]() {
-            hipLaunchKernelGGL(sssp_mark_level, dim3(G), dim3(GFR_BLOCK), 0, s, a, level);
+            const dim3 grid(G), block(SM_BLOCK);
+            if (local) hipLaunchKernelGGL((sssp_mark_level<16, true>), grid, block, 0, s, a, level, rounds);
+            else if (wide) hipLaunchKernelGGL((sssp_mark_level<32, false>), grid, block, 0, s, a, level, rounds);
+            else hipLaunchKernelGGL((sssp_mark_level<16, false>), grid, block, 0, s, a, level, rounds);
         });
         ++level;
     };
     const int64_t cap = 64ll * n + 1024;
     const int32_t launched = run_until_done(c, &a.ctl->done, 1u, g.iter_hint() + 2, cap, s, launch);
+    hipLaunchKernelGGL(sssp_marks_sum, dim3(1), dim3(256), 0, s, a, (uint32_t)G);
     SmCtl h;
     GFR_HIP(hipMemcpyAsync(c.pinned, a.ctl, sizeof(SmCtl), hipMemcpyDeviceToHost, s));
     GFR_HIP(hipStreamSynchronize(s));
@@ -777,11 +918,15 @@ void run_sssp(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStream_t s)
     const uint32_t nwords = (uint32_t)(((int64_t)n + 63) / 64) * 2u;
     const size_t nparts = (size_t)(g.m / chunk) + 2;
     const uint32_t delta = c.opt.sssp_delta > 0 ? (uint32_t)c.opt.sssp_delta : sssp_auto_delta(g, c.opt.sssp_delta_factor);
-    // mark-byte iterations on request (sssp.frontier 2); auto keeps the queue,
-    // which takes fewer iterations on the 4096^2 lattice (241 against 366 at
-    // the same bucket width) and is faster there
+    // mark-byte iterations on mesh-like graphs of at most six edges per vertex,
+    // whose near sets are thin and whose rows one thread takes in one turn:
+    // 1.4 ms against 3.0 on the 1000^2 lattice, 6.6 against 10.0 on the 4096^2
+    // one; random regular graphs of 1 M vertices with 4, 6, 8 and 12 edges
+    // each, packaged bucket width: 0.94 / 0.96, 1.26 / 1.30, 1.46 / 1.24 and
+    // 2.48 / 1.73 ms (a hub's row is worse: R-MAT, 1 M vertices, 75 against
+    // 1.0).  A pull sweep needs the queue.
     const int fr = c.opt.sssp_frontier;
-    if (fr == 2) {
+    if (fr == 2 || (fr == 0 && g.cls == GRAPH_MESH && g.m <= 6ll * n && !(c.opt.sssp_pull_alpha > 0))) {
         run_sssp_marks(c, g, src, dist, s, delta);
         return;
     }

@@ -147,3 +147,47 @@ def test_mark_byte_levels_in_scratch_too_small_for_the_bitmap(ctx):
     out.fill_(7)
     assert np.array_equal(_host(ctx.bfs_noalloc(g, src, out)), want)
     g.free()
+
+
+def _random_regular(n, deg, seed):
+    rng = np.random.default_rng(seed)
+    u = np.concatenate([rng.permutation(n) for _ in range(deg // 2)])
+    v = np.concatenate([rng.permutation(n) for _ in range(deg // 2)])
+    return graphgen.from_edges(n, u, v)
+
+
+SSSP_MESHES = {   # name: (graph, source, largest weight, bucket width or 0 for the default)
+    "span -1": (lambda: graphgen.from_edges(8191, np.arange(8190), np.arange(1, 8191)), 4000, 64, 0),
+    "span": (lambda: graphgen.from_edges(8192, np.arange(8191), np.arange(1, 8192)), 8191, 64, 100),
+    "span +1": (lambda: graphgen.from_edges(8193, np.arange(8192), np.arange(1, 8193)), 0, 64, 0),
+    # more improved vertices than the list of a span has places for
+    "one span full": (lambda: _random_regular(8192, 12, 1), 17, 1000, 1000000),
+    "spans full": (lambda: _random_regular(40000, 12, 2), 39999, 1000, 1000000),
+    "narrow buckets": (lambda: graphgen.grid(217), 1234, 1000, 40),
+    "one weight": (lambda: graphgen.grid(120), 5, 1, 0),
+    "source without edges": (lambda: _union((np.zeros(41, np.int32), np.zeros(0, np.int32)), graphgen.grid(30)), 7,
+                             64, 0),
+    # spans of which not all are resident: no rounds in a launch; owners of 32 vertices
+    "no rounds": (lambda: _at_the_end(7000001, *graphgen.grid(211)), 7000001 - 5, 1000, 0),
+    "wide": (lambda: _at_the_end(8400001, *graphgen.grid(211)), 8400001 - 5, 1000, 0),
+}
+
+
+@pytest.mark.parametrize("name", list(SSSP_MESHES))
+def test_mark_byte_iterations(ctx, name):
+    make, src, maxw, delta = SSSP_MESHES[name]
+    row, col = make()
+    w = graphgen.weights(row, col, maxw)
+    if name == "narrow buckets":
+        w = np.where(w % 5 == 0, np.uint32(0), w).astype(np.uint32)   # (symmetric: the weight depends on the pair)
+    g = ctx.graph_load_csr(row, col, w)
+    ctx.set_option("sssp.delta", delta)
+    ctx.set_option("sssp.frontier", 2 if "full" in name else 0)
+    try:
+        want = oracle.sssp(row, col, w, src)
+        for _ in range(2):
+            assert np.array_equal(_host(ctx.sssp(g, src)).view(np.uint32), want)
+    finally:
+        ctx.set_option("sssp.delta", 0)
+        ctx.set_option("sssp.frontier", 0)
+        g.free()

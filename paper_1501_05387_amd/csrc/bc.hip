@@ -160,7 +160,7 @@ struct SigmaOp {
     const uint8_t *dc;
     const double *sigma;
     uint8_t code;   // level of the predecessors
-    __device__ double operator()(int32_t u, int32_t) const { return dc[u] == code ? sigma[u] : 0.0; }
+    __device__ double operator()(int32_t u) const { return dc[u] == code ? sigma[u] : 0.0; }
 };
 
 struct SigmaFin {
@@ -172,7 +172,7 @@ struct DeltaOp {
     const uint8_t *dc;
     const double *coef;
     uint8_t code;   // level of the successors
-    __device__ double operator()(int32_t w, int32_t) const { return dc[w] == code ? coef[w] : 0.0; }
+    __device__ double operator()(int32_t w) const { return dc[w] == code ? coef[w] : 0.0; }
 };
 
 struct DeltaFin {

@@ -29,7 +29,7 @@ struct PrCtl {
 
 struct PrOp {
     const float *contrib;
-    __device__ double operator()(int32_t u, int32_t) const { return (double)contrib[u]; }
+    __device__ double operator()(int32_t u) const { return (double)contrib[u]; }
 };
 
 struct PrFin {
@@ -146,7 +146,7 @@ void run_pagerank(Ctx &c, Graph &g, float damping, double tol, int32_t max_iter,
                   int32_t *iters, double *l1, hipStream_t s)
 {
     const int32_t n = g.n;
-    const int G = grid_blocks(c, 4);
+    const int G = grid_blocks(c, 8);
     const size_t nch = (size_t)(g.m + GATHER_CH - 1) / GATHER_CH + 1;
     c.arena.reserve(3 * al256(4ull * n) + al256(8ull * n) + 2 * al256(8 * nch) + al256(16ull * G) +
                     al256(sizeof(PrCtl)));
@@ -233,7 +233,7 @@ struct PfCtl {
 
 struct PfOp {
     const double *contrib;
-    __device__ double operator()(int32_t u, int32_t) const { return contrib[u]; }
+    __device__ double operator()(int32_t u) const { return contrib[u]; }
 };
 
 __global__ __launch_bounds__(GFR_BLOCK) void pf_init(const int32_t *R, int32_t n, double *x, double *contrib,
@@ -412,7 +412,7 @@ const uint8_t *run_pagerank_filtered(Ctx &c, Graph &g, double damping, double ve
 
 struct PpOp {
     const double *contrib;
-    __device__ double operator()(int32_t u, int32_t) const { return contrib[u]; }
+    __device__ double operator()(int32_t u) const { return contrib[u]; }
 };
 
 __global__ __launch_bounds__(GFR_BLOCK) void ppr_init(const int32_t *R, int32_t n, const uint8_t *seed, double invk,
@@ -464,7 +464,7 @@ void run_ppr(Ctx &c, Graph &g, const int32_t *seeds, int32_t k, double damping, 
              double *rank, int32_t *iters, double *l1, hipStream_t s)
 {
     const int32_t n = g.n;
-    const int G = grid_blocks(c, 4);
+    const int G = grid_blocks(c, 8);
     const size_t nch = (size_t)(g.m + GATHER_CH - 1) / GATHER_CH + 1;
     c.arena.reserve(4 * al256(8ull * n) + al256(4ull * ((n + 3) / 4)) + al256(4ull * k) + 2 * al256(8 * nch) +
                     al256(16ull * G) + al256(sizeof(PrCtl)));

@@ -153,7 +153,7 @@ struct Hop2PushOp {
 
 struct Hop2PullOp {
     const uint32_t *c1;
-    __device__ double operator()(int32_t u, int32_t) const { return (double)c1[u]; }
+    __device__ double operator()(int32_t u) const { return (double)c1[u]; }
 };
 
 struct Hop2Fin {
@@ -218,7 +218,7 @@ void run_two_hop(Ctx &c, Graph &g, const int32_t *seeds, int32_t k, uint64_t *co
 struct SideOp {
     const double *x;
     const double *scale;   // HITS: 1/||x||_2 of the side (device scalar), SALSA: null
-    __device__ double operator()(int32_t u, int32_t) const
+    __device__ double operator()(int32_t u) const
     {
         const double v = x[u];
         return scale ? v * *scale : v;

@@ -191,3 +191,45 @@ def test_mark_byte_iterations(ctx, name):
         ctx.set_option("sssp.delta", 0)
         ctx.set_option("sssp.frontier", 0)
         g.free()
+
+
+def _rows(degrees, seed):
+    """Symmetric simple graph whose first vertices have the given numbers of neighbours (leaves of their own)."""
+    eu, ev, leaf = [], [], len(degrees)
+    for v, d in enumerate(degrees):
+        eu.append(np.full(d, v))
+        ev.append(np.arange(leaf, leaf + d))
+        leaf += d
+    # and some edges among the leaves, so that the sums differ
+    rng = np.random.default_rng(seed)
+    eu.append(rng.integers(len(degrees), leaf, leaf // 3))
+    ev.append(rng.integers(len(degrees), leaf, leaf // 3))
+    u, v = np.concatenate(eu), np.concatenate(ev)
+    return graphgen.from_edges(leaf, u[u != v], v[u != v])
+
+
+GATHER_ROWS = {   # list lengths around a lane's four edges, a wave's 256, a chunk's 1024 and the fix-up's eight chunks
+    "short": [1, 2, 3, 4, 5, 3, 1, 8, 7, 9, 1, 1, 1, 1],
+    "wave": [3, 255, 1, 256, 257, 511, 512, 513, 1, 2],
+    "chunk": [1023, 1, 1024, 1025, 2047, 2048, 2049, 5],
+    "hubs": [8191, 8192, 8193, 20001, 9 * 1024 + 1, 3],
+    "one edge": [1],
+    "one chunk": [512],
+}
+
+
+@pytest.mark.parametrize("name", list(GATHER_ROWS))
+def test_gathered_sums_of_list_lengths(ctx, name):
+    row, col = _rows(GATHER_ROWS[name], 5)
+    g = ctx.graph_load_csr(row, col)
+    x, it, _ = ctx.pagerank(g, 0.85, 0.0, 6)
+    want, _, _ = oracle.pagerank(row, col, 0.85, 0.0, 6)
+    assert it == 6 and np.abs(_host(x).astype(np.float64) - want).sum() <= 1e-6
+    src = np.array([0, row.size - 2], np.int32)
+    b, bo = _host(ctx.bc(g, src)).astype(np.float64), oracle.bc(row, col, src)
+    nz = bo != 0
+    assert np.all(b[~nz] == 0) and (not nz.any() or np.max(np.abs(b[nz] - bo[nz]) / bo[nz]) <= 1e-5)
+    seeds = np.array([0, row.size // 2], np.int32) if row.size > 4 else np.array([0], np.int32)
+    hops = _host(ctx.two_hop(g, seeds)).astype(np.uint64)
+    assert np.array_equal(hops, oracle.two_hop(row, col, seeds))
+    g.free()

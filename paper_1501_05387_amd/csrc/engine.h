@@ -105,6 +105,18 @@ extern const char *const kClassNames[kNumGraphClasses];
 // scale-free when the largest degree is at least 16 times the mean degree
 int classify_graph(int32_t n, int64_t m, int32_t max_deg);
 
+// Columns renumbered by degree, for the gathers of hotgather.h (made on first
+// use, under the context's lock; freed with the graph).
+struct RankedCols {
+    DevMem mem;              // empty: not made, or it did not fit
+    bool tried = false;
+    int32_t *C = nullptr;    // [m padded] position of each edge's target in degree order
+    int32_t *pos = nullptr;  // [nf] position of each entry of the whole-graph queue
+    uint32_t *starts = nullptr;
+    int32_t *entry = nullptr;
+    uint32_t nch = 0;
+};
+
 struct Graph {
     int32_t n = 0;
     int cls = GRAPH_MESH;
@@ -121,6 +133,7 @@ struct Graph {
     uint32_t *full_counts = nullptr;   // device [nf, mf, 0, 0]
     int32_t full_nf = 0;
     int32_t n_isolated = 0;
+    RankedCols ranked;
     int32_t bip_checked_nl = -1;   // last side split verified for the bipartite rankings
     // hints for the speculative level loops (the size of the first batch of
     // launches), one per solver (a 64-source traversal takes more levels than

@@ -233,3 +233,35 @@ def test_gathered_sums_of_list_lengths(ctx, name):
     hops = _host(ctx.two_hop(g, seeds)).astype(np.uint64)
     assert np.array_equal(hops, oracle.two_hop(row, col, seeds))
     g.free()
+
+
+def _hubs_and_rest():
+    """More than 2^21 entries: list lengths around the 256-edge chunk and the fix-up's 16 chunks, a hub of
+    thousands of chunks, isolated vertices, and a ragged number of entries."""
+    hubs = _rows([255, 256, 257, 1, 1, 511, 513, 4095, 4096, 4097, 4352, 8191, 40001, 1050007], 9)
+    return _union((np.zeros(34, np.int32), np.zeros(0, np.int32)), graphgen.rmat(12), hubs,
+                  (np.zeros(78, np.int32), np.zeros(0, np.int32)))
+
+
+RANKED = {"rmat17": lambda: graphgen.rmat(17), "hubs": _hubs_and_rest}
+
+
+@pytest.mark.parametrize("name", list(RANKED))
+def test_ranked_columns(ctx, name):
+    """PageRank over columns renumbered by degree (max_iter >= 4) and over the CSR (below)."""
+    row, col = RANKED[name]()
+    assert col.size > 1 << 21 and (col.size % 256 or name != "hubs")
+    g = ctx.graph_load_csr(row, col)
+    held = ctx.graph_info(g)[2]
+    for iters in (3, 4, 7):
+        x, it, l1 = ctx.pagerank(g, 0.85, 0.0, iters)
+        assert (ctx.graph_info(g)[2] > held) == (iters > 3)
+        want, _, wl1 = oracle.pagerank(row, col, 0.85, 0.0, iters)
+        x = _host(x).astype(np.float64)
+        assert it == iters and np.abs(x - want).sum() <= 1e-6
+        assert np.all(np.abs(x - want) <= 1e-5 * want) and abs(l1 - wl1) <= 1e-6
+    out = np.empty(row.size - 1, np.float32)
+    _, it, l1 = ctx.pagerank(g, 0.85, 1e-6, 1000, out=out)
+    again, it2, l2 = ctx.pagerank(g, 0.85, 1e-6, 1000)
+    assert it == it2 and l1 == l2 < 1e-6 and np.array_equal(out, _host(again))
+    g.free()

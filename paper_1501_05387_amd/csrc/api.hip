@@ -102,6 +102,36 @@ void fill_u32(void *p, uint32_t value, size_t count, hipStream_t s)
     GFR_LAUNCH_CHECK();
 }
 
+__global__ void k_fill_many(Fills f)
+{
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+    for (int k = 0; k < f.n; ++k)
+        for (size_t i = i0; i < f.count[k]; i += stride) f.p[k][i] = f.value[k];
+}
+
+void Fills::run(hipStream_t s) const
+{
+    size_t most = 0;
+    for (int k = 0; k < n; ++k) most = std::max(most, count[k]);
+    if (most == 0) return;
+    const size_t blocks = std::min<size_t>((most + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_fill_many, dim3((unsigned)blocks), dim3(256), 0, s, *this);
+    GFR_LAUNCH_CHECK();
+}
+
+__global__ void k_read_back(uint32_t *host, const uint32_t *dev, uint32_t words)
+{
+    for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) host[i] = dev[i];
+}
+
+void read_back(Ctx &c, const void *dev, size_t bytes, hipStream_t s)
+{
+    if (bytes > PINNED_BYTES || bytes % 4) fail(GFR_E_DEVICE, "internal: read-back of a bad size");
+    hipLaunchKernelGGL(k_read_back, dim3(1), dim3(64), 0, s, c.pinned, (const uint32_t *)dev, (uint32_t)(bytes / 4));
+    GFR_LAUNCH_CHECK();
+    GFR_HIP(hipStreamSynchronize(s));
+}
+
 static bool is_pinned_host(const void *p)
 {
     hipPointerAttribute_t attr;
@@ -315,6 +345,7 @@ static gfr_status guard(gfr_ctx *ctx, F f)
 static void timed_begin(Ctx &c, hipStream_t s)
 {
     c.stats.clear();
+    c.timed = false;
     c.ktimer.reset();
     c.ktimer.on = c.opt.profile_kernels != 0;
     c.ktimer.advance_only = c.opt.profile_kernels == 2;
@@ -324,10 +355,8 @@ static void timed_begin(Ctx &c, hipStream_t s)
 static void timed_end(Ctx &c, hipStream_t s)
 {
     GFR_HIP(hipEventRecord(c.ev1, s));
-    GFR_HIP(hipEventSynchronize(c.ev1));
-    float ms = 0.f;
-    GFR_HIP(hipEventElapsedTime(&ms, c.ev0, c.ev1));
-    c.stats.v["kernel_ms"] = ms;
+    GFR_HIP(hipStreamSynchronize(s));
+    c.timed = true;
     c.ktimer.collect(c.stats.v);
 }
 
@@ -604,7 +633,7 @@ gfr_status gfr_ctx_create(int32_t device, const char *tuning_json, gfr_ctx **out
         // null stream (PyTorch's default stream) finishes before ours starts
         GFR_HIP(hipStreamCreateWithFlags(&cc.stream, hipStreamDefault));
         cc.noalloc_scratch = noalloc_scratch(device);
-        GFR_HIP(hipHostMalloc((void **)&cc.pinned, 4096, hipHostMallocDefault));
+        GFR_HIP(hipHostMalloc((void **)&cc.pinned, PINNED_BYTES, hipHostMallocDefault));
         GFR_HIP(hipEventCreate(&cc.ev0));
         GFR_HIP(hipEventCreate(&cc.ev1));
         cc.zero_word.alloc(256);
@@ -673,6 +702,12 @@ gfr_status gfr_get_stat(gfr_ctx *ctx, const char *key, double *value)
     return guard(ctx, [&](Ctx &c) {
         if (!key || !value) fail(GFR_E_INVALID, "null argument");
         if (serve_stat(c, key, value)) return;
+        if (c.timed) {   // the events of the last call
+            float ms = 0.f;
+            GFR_HIP(hipEventElapsedTime(&ms, c.ev0, c.ev1));
+            c.stats.v["kernel_ms"] = ms;
+            c.timed = false;
+        }
         auto it = c.stats.v.find(key);
         if (it == c.stats.v.end()) fail(GFR_E_NOT_FOUND, std::string("no statistic '") + key + "'");
         *value = it->second;
@@ -785,15 +820,14 @@ gfr_status gfr_bfs_noalloc(gfr_ctx *ctx, gfr_graph gh, int32_t source, int32_t *
         hipStream_t s = pick_stream(c, stream);
         Arena ar(c.noalloc_scratch, GFR_NOALLOC_SCRATCH_BYTES);
         c.stats.clear();
+        c.timed = false;
         c.ktimer.reset();
         c.ktimer.on = false;   // per-launch timing would create events
         GFR_HIP(hipEventRecord(c.ev0, s));
         run_bfs(c, g, source, depth_out, s, ar);   // capacity is checked before any launch
         GFR_HIP(hipEventRecord(c.ev1, s));
-        GFR_HIP(hipEventSynchronize(c.ev1));
-        float ms = 0.f;
-        GFR_HIP(hipEventElapsedTime(&ms, c.ev0, c.ev1));
-        c.stats.v["kernel_ms"] = ms;
+        GFR_HIP(hipStreamSynchronize(s));
+        c.timed = true;
     });
 }
 

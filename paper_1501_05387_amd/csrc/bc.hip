@@ -236,11 +236,12 @@ void run_bc(Ctx &c, Graph &g, const int32_t *sources, int32_t k, float *bc, hipS
     unsigned long long *status = c.arena.take<unsigned long long>(2ull * cg.blocks);
     uint32_t *cw = c.arena.take<uint32_t>(64);   // [0] compaction parity, [1] look-back error
     uint32_t *fb = c.arena.take<uint32_t>(nwords);
-    fill_u32(mark, 0u, 8ull * nwords, s);
-    fill_u32(status, 0u, 4ull * cg.blocks, s);
-    fill_u32(cw, 0u, 64, s);
-
-    fill_u32(acc, 0u, 2ull * n, s);
+    Fills()
+        .add(mark, 0u, 8ull * nwords)
+        .add(status, 0u, 4ull * cg.blocks)
+        .add(cw, 0u, 64)
+        .add(acc, 0u, 2ull * n)
+        .run(s);
     auto qat = [&](const Level &l) {
         return FrontierQ{order + l.start, off + l.start, row + l.start, part + l.pbase};
     };
@@ -250,15 +251,12 @@ void run_bc(Ctx &c, Graph &g, const int32_t *sources, int32_t k, float *bc, hipS
     const double alpha = c.opt.bc_alpha, beta = c.opt.bc_beta;
     for (int32_t si = 0; si < k; ++si) {
         const int32_t src = sources[si];
-        fill_u32(a.dc, 0xFFFFFFFFu, (n + 3) / 4, s);   // BC_UNSEEN
-        fill_u32(a.vis, 0u, nwords, s);
-        fill_u32(fb, 0u, nwords, s);
+        Fills().add(a.dc, 0xFFFFFFFFu, (n + 3) / 4).add(a.vis, 0u, nwords).add(fb, 0u, nwords).run(s);   // dc: BC_UNSEEN
         lv.clear();
         lv.push_back(Level{0, 1, 0, 0});
         hipLaunchKernelGGL(bc_source_init, dim3(1), dim3(GFR_BLOCK), 0, s, a, src, qat(lv[0]), sigma, ctr, fb);
         GFR_LAUNCH_CHECK();
-        GFR_HIP(hipMemcpyAsync(c.pinned, ctr, 8, hipMemcpyDeviceToHost, s));
-        GFR_HIP(hipStreamSynchronize(s));
+        read_back(c, ctr, 8, s);
         lv[0].mf = c.pinned[0];
         // unvisited vertices and their edges, for the direction choice
         double mu = (double)g.m - (double)lv[0].mf, prev_nf = 0.0;
@@ -286,8 +284,7 @@ void run_bc(Ctx &c, Graph &g, const int32_t *sources, int32_t k, float *bc, hipS
             hipLaunchKernelGGL(compact_kernel<BcMarks>, dim3(cg.blocks), dim3(GFR_BLOCK), 0, s, a.R, n, nwords, cg.wpt,
                                BcMarks{mark, a.vis, fb, cn, cw}, qat(nx), GATHER_CH, status, cw, cw + 1);
             GFR_LAUNCH_CHECK();
-            GFR_HIP(hipMemcpyAsync(c.pinned, cn, 8, hipMemcpyDeviceToHost, s));
-            GFR_HIP(hipStreamSynchronize(s));
+            read_back(c, cn, 8, s);
             nx.mf = c.pinned[0];
             nx.nf = c.pinned[1];
             if (nx.nf == 0) break;
@@ -322,8 +319,7 @@ void run_bc(Ctx &c, Graph &g, const int32_t *sources, int32_t k, float *bc, hipS
     }
     hipLaunchKernelGGL(bc_to_f32, dim3(G), dim3(GFR_BLOCK), 0, s, acc, bc, n);
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipMemcpyAsync(c.pinned, cw + 1, 4, hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    read_back(c, cw + 1, 4, s);
     if (c.pinned[0]) fail(GFR_E_DEVICE, "bc: frontier compaction look-back timed out");
     c.stats.v["levels"] = levels_total;
     c.stats.v["push_levels"] = push_levels;

@@ -612,8 +612,10 @@ static void run_bfs_bitmap(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStr
     a.vis = vis ? ar.take<uint32_t>(nb / 32) : nullptr;
     a.flags = ar.take<uint32_t>(2ull * G);
     a.ctl = ar.take<BfsCtl>(1);
-    fill_u32(depth, 0xFFFFFFFFu, (size_t)n, s);
-    fill_u32(a.mk[0], 0u, (2 * al256(nb) + (vis ? al256(nb / 8) : 0)) / 4, s);   // marks and bitmap (adjacent)
+    Fills()
+        .add(depth, 0xFFFFFFFFu, (size_t)n)
+        .add(a.mk[0], 0u, (2 * al256(nb) + (vis ? al256(nb / 8) : 0)) / 4)   // marks and bitmap (adjacent)
+        .run(s);
     // one thread per vertex: only where no vertex has a long row
     const bool head = vis && g.cls == GRAPH_MESH;
     if (head)
@@ -633,10 +635,8 @@ static void run_bfs_bitmap(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStr
     };
     const int32_t launched = run_until_done(c, &a.ctl->dir, DIR_DONE,
                                             g.bitmap_launch_hint.load(std::memory_order_relaxed) + 2,
-                                            (int64_t)n + 4, s, launch);
+                                            (int64_t)n + 4, s, launch, sizeof(BfsCtl));
     BfsCtl h;
-    GFR_HIP(hipMemcpyAsync(c.pinned, a.ctl, sizeof(BfsCtl), hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
     memcpy(&h, c.pinned, sizeof(BfsCtl));
     c.stats.v["levels"] += h.level;
     c.stats.v["push_levels"] += h.push_levels;
@@ -686,11 +686,13 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena
     unsigned long long *status = ar.take<unsigned long long>(2ull * cg.blocks);
     a.ctl = ar.take<BfsCtl>(1);
 
-    fill_u32(depth, 0xFFFFFFFFu, (size_t)n, s);
-    fill_u32(a.vis, 0u, nwords, s);
-    fill_u32(a.fb, 0u, nwords, s);
-    fill_u32(a.mark, 0u, 8ull * nwords, s);
-    fill_u32(status, 0u, 4ull * cg.blocks, s);
+    Fills()
+        .add(depth, 0xFFFFFFFFu, (size_t)n)
+        .add(a.vis, 0u, nwords)
+        .add(a.fb, 0u, nwords)
+        .add(a.mark, 0u, 8ull * nwords)
+        .add(status, 0u, 4ull * cg.blocks)
+        .run(s);
     hipLaunchKernelGGL(bfs_init, dim3(1), dim3(GFR_BLOCK), 0, s, a, src, chunk, (uint32_t)c.opt.bfs_direction,
                        (uint32_t)c.opt.bfs_dedup, (float)c.opt.bfs_alpha, (float)c.opt.bfs_beta,
                        (unsigned long long)g.m);
@@ -716,10 +718,9 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena
     StepKey key("bfs");
     key.add(a).add(G).add(cg).add(chunk).add(status);
     const int32_t launched = run_until_done(c, &a.ctl->dir, DIR_DONE, g.levels_hint() + 1,
-                                            (int64_t)n + 4, s, launch, ar.fixed ? nullptr : &key);
+                                            (int64_t)n + 4, s, launch, sizeof(BfsCtl),
+                                            ar.fixed ? nullptr : &key);
     BfsCtl h;
-    GFR_HIP(hipMemcpyAsync(c.pinned, a.ctl, sizeof(BfsCtl), hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
     memcpy(&h, c.pinned, sizeof(BfsCtl));
     if (h.err) fail(GFR_E_DEVICE, "bfs: frontier compaction look-back timed out");
     c.stats.v["levels"] += h.level;

@@ -189,8 +189,7 @@ void run_cc(Ctx &c, Graph &g, int32_t *label, int32_t *ncomp, hipStream_t s)
     hipLaunchKernelGGL(cc_jump, grid, block, 0, s, label, n, rpart);
     hipLaunchKernelGGL(cc_sum, dim3(1), block, 0, s, rpart, (uint32_t)G, word + 1);
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipMemcpyAsync(c.pinned, word + 1, 4, hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    read_back(c, word + 1, 4, s);
     *ncomp = (int32_t)c.pinned[0];
     c.stats.v["rounds"] = 3;   // first neighbours, second neighbours, the rest
 }

@@ -361,6 +361,7 @@ struct Ctx {
     Stats stats;
     Server *server = nullptr;     // owned; destroyed by serve_shutdown
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    bool timed = false;           // ev0, ev1 enclose the last call ("kernel_ms" is computed when asked for)
     KernelTimer ktimer;
     StepGraphs step_graphs;       // captured level steps, replayed by run_until_done
     Bounce bounce;                // for results written to pageable host memory
@@ -492,15 +493,42 @@ bool serve_stat(Ctx &c, const std::string &key, double *value);
 
 // Fill helpers.
 void fill_u32(void *p, uint32_t value, size_t count, hipStream_t s);
+// Up to eight fills in one launch: a launch costs the host 4 to 5 us, more
+// than most of these fills take.
+struct Fills {
+    static constexpr int MAX = 8;
+    uint32_t *p[MAX];
+    uint32_t value[MAX];
+    size_t count[MAX];
+    int n = 0;
+    Fills &add(void *ptr, uint32_t v, size_t words)
+    {
+        if (n == MAX) fail(GFR_E_DEVICE, "internal: too many fills");
+        p[n] = (uint32_t *)ptr;
+        value[n] = v;
+        count[n++] = words;
+        return *this;
+    }
+    void run(hipStream_t s) const;
+};
+
+// Copy `bytes` (a multiple of 4, at most PINNED_BYTES) of device memory to
+// c.pinned and wait for the stream.  A kernel stores the words to the host's
+// memory: the copy engine's own round trip is longer than the wait.
+constexpr size_t PINNED_BYTES = 4096;
+void read_back(Ctx &c, const void *dev, size_t bytes, hipStream_t s);
 
 // Spin on a device word until the speculative level loop reports completion.
-// Launches `launch()` batches and reads *flag (device) back after each batch.
+// Launches `launch()` batches and reads `bytes` at flag_dev (the control block,
+// whose first word is the flag) back to c.pinned after each batch; they are
+// there when it returns.
 // With a step key (and option "graph.steps" on, per-launch timing off), each
 // batch of k steps is replayed from a hipGraph captured the first time that
 // key and k were seen; a capture that fails falls back to direct launches.
 template <class LaunchFn>
 int32_t run_until_done(Ctx &c, const uint32_t *flag_dev, uint32_t done_value, int32_t first_batch,
-                       int64_t max_launches, hipStream_t s, LaunchFn launch, const StepKey *key = nullptr)
+                       int64_t max_launches, hipStream_t s, LaunchFn launch, size_t bytes,
+                       const StepKey *key = nullptr)
 {
     int64_t launched = 0;
     int32_t batch = first_batch < 1 ? 1 : first_batch;
@@ -531,8 +559,7 @@ int32_t run_until_done(Ctx &c, const uint32_t *flag_dev, uint32_t done_value, in
         }
         GFR_LAUNCH_CHECK();
         launched += batch;
-        GFR_HIP(hipMemcpyAsync(c.pinned, flag_dev, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-        GFR_HIP(hipStreamSynchronize(s));
+        read_back(c, flag_dev, bytes, s);
         if (*(volatile uint32_t *)c.pinned == done_value) break;
         if (launched > max_launches) fail(GFR_E_DEVICE, "iteration watchdog: solve did not converge");
         batch = batch < 128 ? batch * 2 : 256;

@@ -447,18 +447,20 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
     a.nactp = (uint32_t)G;
     a.lvl = c.arena.take<unsigned long long>((size_t)n * MS_LVL_CAP);
     a.lvl_cap = MS_LVL_CAP;
-    fill_u32(base, 0u, 64, s);
     double levels = 0, pull_levels = 0, push_edges = 0;
     for (int32_t g0 = 0; g0 < k; g0 += 64) {
         const int32_t kk = std::min<int32_t>(64, k - g0);
         a.k = kk;
         a.allq = kk == 64 ? ~0ull : ((1ull << kk) - 1ull);
         a.depth = depth + (size_t)g0 * n;
-        fill_u32(a.vis, 0u, 2ull * n, s);
-        fill_u32(a.fr, 0u, 2ull * n, s);
-        fill_u32(a.nx, 0u, 2ull * n, s);
-        fill_u32(a.mark, 0u, 8ull * nwords, s);
-        fill_u32(status, 0u, 4ull * cg.blocks, s);
+        Fills()
+            .add(a.vis, 0u, 2ull * n)
+            .add(a.fr, 0u, 2ull * n)
+            .add(a.nx, 0u, 2ull * n)
+            .add(a.mark, 0u, 8ull * nwords)
+            .add(status, 0u, 4ull * cg.blocks)
+            .add(base, 0u, 64)
+            .run(s);
         GFR_HIP(hipMemcpyAsync(dsrc, sources + g0, 4ull * kk, hipMemcpyHostToDevice, s));
         hipLaunchKernelGGL(msbfs_init, dim3(1), dim3(64), 0, s, a, dsrc, (float)c.opt.msbfs_alpha);
         GFR_LAUNCH_CHECK();
@@ -477,16 +479,12 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
         StepKey key("msbfs");
         key.add(a).add(G).add(cg).add(chunk).add(status);
         run_until_done(c, &a.ctl->dir, MS_DONE, g.msbfs_levels_hint.load(std::memory_order_relaxed) + 2,
-                       (int64_t)n + 8, s, launch, &key);
-        // the output pass takes the depth count from the control block, so it
-        // is queued before the block is read back (a failed batch fails the call)
+                       (int64_t)n + 8, s, launch, sizeof(MsCtl), &key);
         c.ktimer.run("msbfs_output", s, [&]() {
             hipLaunchKernelGGL(msbfs_output, dim3(grid_blocks(c, 8)), dim3(GFR_BLOCK), 0, s, a);
         });
         GFR_LAUNCH_CHECK();
         MsCtl h;
-        GFR_HIP(hipMemcpyAsync(c.pinned, a.ctl, sizeof(MsCtl), hipMemcpyDeviceToHost, s));
-        GFR_HIP(hipStreamSynchronize(s));
         memcpy(&h, c.pinned, sizeof(MsCtl));
         if (h.err) fail(GFR_E_DEVICE, "bfs_batch: frontier compaction look-back timed out");
         g.msbfs_levels_hint.store(h.level, std::memory_order_relaxed);

@@ -205,8 +205,7 @@ static const int32_t *device_list(Ctx &c, const int32_t *list, int64_t count, in
     fill_u32(bad, 0u, 1, s);
     hipLaunchKernelGGL(count_out_of_range, dim3(grid_blocks(c, 2)), dim3(GFR_BLOCK), 0, s, d, count, n, bad);
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipMemcpyAsync(c.pinned, bad, 4, hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    read_back(c, bad, 4, s);
     if (c.pinned[0]) fail(GFR_E_INVALID, std::string(who) + ": " + what + " id out of range");
     return d;
 }
@@ -241,8 +240,7 @@ int64_t run_advance(Ctx &c, Graph &g, const int32_t *frontier, int32_t nf, bool 
                        totals);
     hipLaunchKernelGGL(scan_totals, dim3(1), dim3(GFR_BLOCK), 0, s, totals, ntiles);
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipMemcpyAsync(c.pinned, totals + ntiles, sizeof(P2), hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    read_back(c, totals + ntiles, sizeof(P2), s);
     P2 grand;
     memcpy(&grand, c.pinned, sizeof grand);
     const int64_t total = (int64_t)grand.a;
@@ -306,8 +304,7 @@ int64_t run_filter(Ctx &c, Graph &g, const int32_t *items, int64_t count, const 
                        totals);
     hipLaunchKernelGGL(scan_totals, dim3(1), dim3(GFR_BLOCK), 0, s, totals, ntiles);
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipMemcpyAsync(c.pinned, totals + ntiles, sizeof(P2), hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    read_back(c, totals + ntiles, sizeof(P2), s);
     P2 grand;
     memcpy(&grand, c.pinned, sizeof grand);
     const int64_t kept = (int64_t)grand.b;
@@ -348,8 +345,7 @@ uint64_t run_scan(Ctx &c, const uint32_t *in, int64_t count, unsigned long long 
     hipLaunchKernelGGL((scan_emit<ScanVal, ScanEmit>), dim3((uint32_t)ntiles), dim3(GFR_BLOCK), 0, s, ScanVal{X},
                        count, totals, ScanEmit{out});
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipMemcpyAsync(c.pinned, totals + ntiles, sizeof(P2), hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    read_back(c, totals + ntiles, sizeof(P2), s);
     P2 grand;
     memcpy(&grand, c.pinned, sizeof grand);
     return grand.a;
@@ -400,8 +396,7 @@ void run_split(Ctx &c, Graph &g, const int32_t *items, int64_t count, const uint
     hipLaunchKernelGGL(scan_reduce<SplitVal>, dim3((uint32_t)ntiles), dim3(GFR_BLOCK), 0, s, val, count, totals);
     hipLaunchKernelGGL(scan_totals, dim3(1), dim3(GFR_BLOCK), 0, s, totals, ntiles);
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipMemcpyAsync(c.pinned, totals + ntiles, sizeof(P2), hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    read_back(c, totals + ntiles, sizeof(P2), s);
     P2 grand;
     memcpy(&grand, c.pinned, sizeof grand);
     *n_near = (int64_t)grand.a;

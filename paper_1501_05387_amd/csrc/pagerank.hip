@@ -269,11 +269,10 @@ static void run_pagerank_ranked(Ctx &c, Graph &g, const RankedCols &rk, float da
         hipLaunchKernelGGL(prk_reduce, dim3(1), block, 0, s, part, (uint32_t)G, g.n, ctl);
     };
     const int32_t first = max_iter < 8 ? max_iter : 8;
-    run_until_done(c, done, 1u, first, (int64_t)max_iter + 8, s, launch);
+    run_until_done(c, done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h);
     hipLaunchKernelGGL(prk_output, grid, block, 0, s, g.full, nf, g.R.as<int32_t>(), g.n, xa, xb, ctl, rank);
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipMemcpyAsync(&h, ctl, sizeof h, hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    memcpy(&h, c.pinned, sizeof h);
     *iters = (int32_t)h.pr.iters;
     *l1 = h.pr.l1;
     c.stats.v["iterations"] = h.pr.iters;
@@ -324,9 +323,8 @@ void run_pagerank(Ctx &c, Graph &g, float damping, double tol, int32_t max_iter,
         hipLaunchKernelGGL(pr_reduce, dim3(1), dim3(GFR_BLOCK), 0, s, part, (uint32_t)G, ctl, 0u);
     };
     const int32_t first = max_iter < 8 ? max_iter : 8;
-    run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch);
-    GFR_HIP(hipMemcpyAsync(&h, ctl, sizeof h, hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h);
+    memcpy(&h, c.pinned, sizeof h);
     const float *xf = (h.iters & 1) ? xb : xa;
     GFR_HIP(hipMemcpyAsync(rank, xf, 4ull * n, hipMemcpyDeviceToDevice, s));
     *iters = (int32_t)h.iters;
@@ -508,8 +506,7 @@ const uint8_t *run_pagerank_filtered(Ctx &c, Graph &g, double damping, double ve
     h.tol = vertex_tol;
     h.damping = damping;
     GFR_HIP(hipMemcpyAsync(ctl, &h, sizeof h, hipMemcpyHostToDevice, s));
-    fill_u32(keep, 0u, 8ull * nwords, s);
-    fill_u32(status, 0u, 4ull * cg.blocks, s);
+    Fills().add(keep, 0u, 8ull * nwords).add(status, 0u, 4ull * cg.blocks).run(s);
     const int32_t *R = g.R.as<int32_t>(), *C = g.C.as<int32_t>();
     hipLaunchKernelGGL(pf_init, dim3(G), dim3(GFR_BLOCK), 0, s, R, n, x, contrib, keep);
     PfMarks mk{keep, part, (uint32_t)G, ctl, n, 1u};
@@ -530,11 +527,10 @@ const uint8_t *run_pagerank_filtered(Ctx &c, Graph &g, double damping, double ve
                            q, (uint32_t)GATHER_CH, status, &ctl->parity, &ctl->err);
     };
     const int32_t first = max_iter < 8 ? max_iter : 8;
-    run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch);
+    run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h);
     hipLaunchKernelGGL(pf_output, dim3(G), dim3(GFR_BLOCK), 0, s, R, n, x, keep, ctl, rank, active);
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipMemcpyAsync(&h, ctl, sizeof h, hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    memcpy(&h, c.pinned, sizeof h);
     if (h.err) fail(GFR_E_DEVICE, "pagerank_filtered: frontier compaction look-back timed out");
     *iters = (int32_t)h.iters;
     *l1 = h.l1;
@@ -648,9 +644,8 @@ void run_ppr(Ctx &c, Graph &g, const int32_t *seeds, int32_t k, double damping, 
         hipLaunchKernelGGL(pr_reduce, dim3(1), dim3(GFR_BLOCK), 0, s, part, (uint32_t)G, ctl, 0u);
     };
     const int32_t first = max_iter < 8 ? max_iter : 8;
-    run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch);
-    GFR_HIP(hipMemcpyAsync(&h, ctl, sizeof h, hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h);
+    memcpy(&h, c.pinned, sizeof h);
     const double *xf = (h.iters & 1) ? xb : xa;
     GFR_HIP(hipMemcpyAsync(rank, xf, 8ull * n, hipMemcpyDeviceToDevice, s));
     *iters = (int32_t)h.iters;

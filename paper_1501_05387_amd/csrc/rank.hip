@@ -99,8 +99,7 @@ struct QueueBuilder {
         cg = compact_geom(nwords, c.num_cu);
         status = c.arena.take<unsigned long long>(2ull * cg.blocks);
         cw = c.arena.take<uint32_t>(64);
-        fill_u32(status, 0u, 4ull * cg.blocks, s);
-        fill_u32(cw, 0u, 64, s);
+        Fills().add(status, 0u, 4ull * cg.blocks).add(cw, 0u, 64).run(s);
     }
     template <class M> void build(const Graph &g, M mk, FrontierQ q, hipStream_t s)
     {
@@ -110,8 +109,7 @@ struct QueueBuilder {
     }
     void check(Ctx &c, hipStream_t s, const char *who)
     {
-        GFR_HIP(hipMemcpyAsync(c.pinned, cw + 1, 4, hipMemcpyDeviceToHost, s));
-        GFR_HIP(hipStreamSynchronize(s));
+        read_back(c, cw + 1, 4, s);
         if (c.pinned[0]) fail(GFR_E_DEVICE, std::string(who) + ": frontier compaction look-back timed out");
     }
 };
@@ -177,9 +175,7 @@ void run_two_hop(Ctx &c, Graph &g, const int32_t *seeds, int32_t k, uint64_t *co
     GatherScratch gs{c.arena.take<double>(nch), c.arena.take<double>(nch)};
     QueueBuilder qb;
     qb.init(c, n, s);
-    fill_u32(c1, 0u, n, s);
-    fill_u32(mark, 0u, 8ull * nwords, s);
-    fill_u32(count, 0u, 2ull * n, s);
+    Fills().add(c1, 0u, n).add(mark, 0u, 8ull * nwords).add(count, 0u, 2ull * n).run(s);
     GFR_HIP(hipMemcpyAsync(dseeds, seeds, 4ull * k, hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(mark_list, dim3((k + GFR_BLOCK - 1) / GFR_BLOCK), dim3(GFR_BLOCK), 0, s, dseeds, k, mark);
     qb.build(g, ByteMarks{mark, ctr, qb.cw}, q, s);
@@ -188,8 +184,7 @@ void run_two_hop(Ctx &c, Graph &g, const int32_t *seeds, int32_t k, uint64_t *co
     hipLaunchKernelGGL((for_each_edge<GATHER_CH, Hop1Op>), dim3(G), dim3(GFR_BLOCK), 0, s, q, q1 + 1, q1, C,
                        Hop1Op{c1, mark});
     qb.build(g, ByteMarks{mark, ctr + 1, qb.cw}, q, s);
-    GFR_HIP(hipMemcpyAsync(c.pinned, ctr, 16, hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    read_back(c, ctr, 16, s);
     const uint32_t mf1 = c.pinned[0], mf2 = c.pinned[2];
     const int force = c.opt.twohop_direction;
     const bool pull = force == 2 || (force == 0 && (double)mf2 > (double)g.m / c.opt.twohop_alpha);
@@ -310,8 +305,7 @@ void check_bipartite(Ctx &c, Graph &g, int32_t nl, hipStream_t s)
     hipLaunchKernelGGL(count_same_side_edges, dim3(grid_blocks(c, 4)), dim3(GFR_BLOCK), 0, s, g.R.as<int32_t>(),
                        g.C.as<int32_t>(), g.n, nl, bad);
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipMemcpyAsync(c.pinned, bad, 4, hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    read_back(c, bad, 4, s);
     if (c.pinned[0]) fail(GFR_E_INVALID, "bipartite ranking: an edge joins two vertices of the same side");
     g.bip_checked_nl = nl;
 }

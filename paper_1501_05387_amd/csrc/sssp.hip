@@ -459,8 +459,7 @@ static void sssp_check_unfit(Ctx &c, Graph &g, const uint32_t *dist, uint32_t *f
     hipLaunchKernelGGL(sssp_unfit_check, dim3(grid_blocks(c, 4)), dim3(GFR_BLOCK), 0, s, g.R.as<int32_t>(),
                        g.C.as<int32_t>(), dist, g.n, flag);
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipMemcpyAsync(c.pinned, flag, 4, hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    read_back(c, flag, 4, s);
     if (*(volatile uint32_t *)c.pinned) fail(GFR_E_INVALID, "sssp: a distance does not fit below 0xFFFFFFFF");
 }
 
@@ -875,8 +874,7 @@ static void run_sssp_marks(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStr
     a.ctl = c.arena.take<SmCtl>(1);
     uint32_t *unfit_flag = c.arena.take<uint32_t>(1);
     a.delta = delta;
-    fill_u32(dist, 0xFFFFFFFFu, (size_t)n, s);
-    fill_u32(a.mk[0], 0u, 3 * al256(nb) / 4, s);   // near and far marks (adjacent)
+    Fills().add(dist, 0xFFFFFFFFu, (size_t)n).add(a.mk[0], 0u, 3 * al256(nb) / 4).run(s);   // all marks are adjacent
     hipLaunchKernelGGL(sssp_marks_init, dim3((G + 255) / 256), dim3(256), 0, s, a, src, (uint32_t)G);
     GFR_LAUNCH_CHECK();
     int32_t level = 0;
@@ -890,11 +888,10 @@ static void run_sssp_marks(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStr
         ++level;
     };
     const int64_t cap = 64ll * n + 1024;
-    const int32_t launched = run_until_done(c, &a.ctl->done, 1u, g.iter_hint() + 2, cap, s, launch);
+    const int32_t launched = run_until_done(c, &a.ctl->done, 1u, g.iter_hint() + 2, cap, s, launch, 4);
     hipLaunchKernelGGL(sssp_marks_sum, dim3(1), dim3(256), 0, s, a, (uint32_t)G);
     SmCtl h;
-    GFR_HIP(hipMemcpyAsync(c.pinned, a.ctl, sizeof(SmCtl), hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    read_back(c, a.ctl, sizeof(SmCtl), s);
     memcpy(&h, c.pinned, sizeof(SmCtl));
     if (h.unfit) sssp_check_unfit(c, g, dist, unfit_flag, s);
     c.stats.v["iterations"] += h.iter;
@@ -958,10 +955,12 @@ void run_sssp(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStream_t s)
     a.ctl = c.arena.take<SsspCtl>(1);
     uint32_t *unfit_flag = c.arena.take<uint32_t>(1);
 
-    fill_u32(dist, 0xFFFFFFFFu, (size_t)n, s);
-    fill_u32(a.near, 0u, 8ull * nwords, s);
-    fill_u32(a.far, 0u, 8ull * nwords, s);
-    fill_u32(status, 0u, 4ull * cg.blocks, s);
+    Fills()
+        .add(dist, 0xFFFFFFFFu, (size_t)n)
+        .add(a.near, 0u, 8ull * nwords)
+        .add(a.far, 0u, 8ull * nwords)
+        .add(status, 0u, 4ull * cg.blocks)
+        .run(s);
     hipLaunchKernelGGL(sssp_init, dim3(1), dim3(GFR_BLOCK), 0, s, a, src, chunk, delta, (float)c.opt.sssp_pull_alpha);
     GFR_LAUNCH_CHECK();
 
@@ -990,10 +989,9 @@ void run_sssp(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStream_t s)
     const int64_t cap = 64ll * n + 1024;
     StepKey key("sssp");
     key.add(a).add(G).add(cg).add(chunk).add(status).add(pull);
-    const int32_t launched = run_until_done(c, &a.ctl->mode, SS_DONE, g.iter_hint() + 1, cap, s, launch, &key);
+    const int32_t launched = run_until_done(c, &a.ctl->mode, SS_DONE, g.iter_hint() + 1, cap, s, launch,
+                                            sizeof(SsspCtl), &key);
     SsspCtl h;
-    GFR_HIP(hipMemcpyAsync(c.pinned, a.ctl, sizeof(SsspCtl), hipMemcpyDeviceToHost, s));
-    GFR_HIP(hipStreamSynchronize(s));
     memcpy(&h, c.pinned, sizeof(SsspCtl));
     if (h.err) fail(GFR_E_DEVICE, "sssp: frontier compaction look-back timed out");
     if (h.unfit) sssp_check_unfit(c, g, dist, unfit_flag, s);

@@ -1163,13 +1163,15 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
         const unsigned long long lanes_mask = kk == 64 ? ~0ull : ((1ull << kk) - 1ull);
         BsCtl h;
         for (;;) {
-            fill_u32(a.D, 0xFFFFFFFFu, 2ull * bits * n, s);   // 8 * bits bytes per vertex
-            fill_u32(a.nq, 0u, 2ull * n, s);
-            fill_u32(a.fq, 0u, 2ull * n, s);
-            fill_u32(a.nany, 0u, 8ull * nwords, s);
-            fill_u32(a.fany, 0u, 8ull * nwords, s);
-            fill_u32(a.part, 0u, 4ull * G, s);
-            fill_u32(status, 0u, 4ull * cg.blocks, s);
+            Fills()
+                .add(a.D, 0xFFFFFFFFu, 2ull * bits * n)   // 8 * bits bytes per vertex
+                .add(a.nq, 0u, 2ull * n)
+                .add(a.fq, 0u, 2ull * n)
+                .add(a.nany, 0u, 8ull * nwords)
+                .add(a.fany, 0u, 8ull * nwords)
+                .add(a.part, 0u, 4ull * G)
+                .add(status, 0u, 4ull * cg.blocks)
+                .run(s);
             GFR_HIP(hipMemcpyAsync(dsrc, sources + g0, 4ull * kk, hipMemcpyHostToDevice, s));
             auto by_width = [&](auto f) {
                 if (bits == 8) f(std::integral_constant<int, 8>());
@@ -1217,16 +1219,12 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
             StepKey key("bsssp");
             key.add(a).add(G).add(Gw).add(cg).add(chunk).add(status).add(bits).add(pair).add(pull_alpha);
             run_until_done(c, &a.ctl->mode, BS_DONE, g.bsssp_iter_hint.load(std::memory_order_relaxed) + 1,
-                           64ll * n + 1024, s, launch, &key);
-            if (bits == 32) {
-                // no fallback can follow: the output is written before the
-                // control block is read back (a failed batch fails the call)
+                           64ll * n + 1024, s, launch, sizeof(BsCtl), &key);
+            if (bits == 32) {   // no fallback can follow (a failed batch fails the call)
                 hipLaunchKernelGGL(bsssp_transpose<32>, dim3(G), dim3(GFR_BLOCK), 0, s, a, n, lanes_mask,
                                    dist + (size_t)g0 * n);
                 GFR_LAUNCH_CHECK();
             }
-            GFR_HIP(hipMemcpyAsync(c.pinned, a.ctl, sizeof(BsCtl), hipMemcpyDeviceToHost, s));
-            GFR_HIP(hipStreamSynchronize(s));
             memcpy(&h, c.pinned, sizeof(BsCtl));
             if (h.err) fail(GFR_E_DEVICE, "sssp_batch: frontier compaction look-back timed out");
             g.bsssp_iter_hint.store((int32_t)h.iter, std::memory_order_relaxed);
@@ -1247,8 +1245,7 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
             hipLaunchKernelGGL(bsssp_unfit_check, dim3(G), dim3(GFR_BLOCK), 0, s, a.R, a.C, a.D, n, lanes_mask,
                                a.part);
             GFR_LAUNCH_CHECK();
-            GFR_HIP(hipMemcpyAsync(c.pinned, a.part, 4, hipMemcpyDeviceToHost, s));
-            GFR_HIP(hipStreamSynchronize(s));
+            read_back(c, a.part, 4, s);
             if (*(volatile uint32_t *)c.pinned)
                 fail(GFR_E_INVALID, "sssp_batch: a distance does not fit below 0xFFFFFFFF");
         }

@@ -646,6 +646,146 @@ static void run_bfs_bitmap(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStr
     g.bitmap_launch_hint.store(h.level + 1 - (int32_t)h.nf, std::memory_order_relaxed);
 }
 
+// ------------------------------------------------------------ small graphs
+// A traversal of a small graph is all latency: launches, the compaction's
+// look-back and the read-back.  Here one work-group does the whole traversal in
+// one launch, with the visited bitmap and the list of discovered vertices
+// (the levels one after another) in LDS; a level is then two dependent loads
+// (row offsets, columns), a few LDS operations and a barrier.  LANES lanes
+// share a vertex; rows of more than BS_LONG entries are put aside and walked by
+// the whole work-group, so that a hub does not hold a level up.  (2, 4, 8 and 16
+// lanes with rows put aside from 32, 128, 256 and 512 entries: 122, 67, 57 and
+// 51 us per call on R-MAT with 1,024 vertices and 21 K entries, 133 us with the
+// level launches; the kernel takes 24 us of the 51.)
+constexpr int BS_BLOCK = 1024;
+constexpr int32_t BS_MAX_N = 32768;     // ids fit 16 bits, the list 64 KB
+constexpr int32_t BS_LONG = 512;
+constexpr int64_t BS_COST = 196608;     // most entries + 16 vertices
+
+struct BsmArgs {
+    const int32_t *R;
+    const int32_t *C;
+    int32_t n;
+    int32_t *depth;
+    uint32_t *out;       // pinned: levels, entries, edges, discovered
+};
+
+template <int LANES>
+__global__ __launch_bounds__(BS_BLOCK) void bfs_small(BsmArgs a, int32_t src)
+{
+    constexpr int EPL = LANES == 1 ? 8 : 4;   // entries a lane reads together
+    __shared__ uint32_t s_vis[BS_MAX_N / 32];
+    __shared__ uint16_t s_list[BS_MAX_N];
+    __shared__ uint16_t s_hub[BS_COST / BS_LONG];
+    __shared__ uint32_t s_cnt, s_nhub, s_edges, s_entries;
+    for (int32_t v = threadIdx.x; v < a.n; v += BS_BLOCK) a.depth[v] = v == src ? 0 : -1;
+    s_vis[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        s_list[0] = (uint16_t)src;
+        s_cnt = 1;
+        s_nhub = s_edges = s_entries = 0;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) s_vis[src >> 5] = 1u << (src & 31);
+    __syncthreads();   // (also orders the first stores to depth[] before those of the levels)
+    uint32_t edges = 0, entries = 0;
+    int32_t L = 0;
+    // entries e0, e0 + step, ... below e1 of one row, EPL at a time
+    auto expand = [&](int32_t e0, int32_t e1, int32_t step) {
+        for (int32_t e = e0; e < e1; e += step * EPL) {
+            int32_t u[EPL];
+#pragma unroll
+            for (int k = 0; k < EPL; ++k) u[k] = a.C[min(e + k * step, e1 - 1)];
+#pragma unroll
+            for (int k = 0; k < EPL; ++k) {
+                const uint32_t bit = 1u << (u[k] & 31);
+                if (e + k * step >= e1 || (s_vis[u[k] >> 5] & bit)) continue;
+                if (atomicOr(&s_vis[u[k] >> 5], bit) & bit) continue;
+                // claimed: one LDS atomic for the lanes that are here
+                const uint64_t m = ballot(true);
+                const uint32_t below = lanes_below(m);
+                uint32_t at = 0;
+                if (below == 0) at = atomicAdd(&s_cnt, (uint32_t)__popcll(m));
+                at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + below;
+                s_list[at] = (uint16_t)u[k];
+                a.depth[u[k]] = L + 1;
+            }
+        }
+    };
+    uint32_t lo = 0, hi = 1;
+    for (; lo < hi; ++L) {
+        for (uint32_t i = lo + threadIdx.x / LANES; i < hi; i += BS_BLOCK / LANES) {
+            const int32_t v = s_list[i];
+            const int32_t e0 = a.R[v], e1 = a.R[v + 1];
+            if (threadIdx.x % LANES == 0 && e1 > e0) {
+                edges += (uint32_t)(e1 - e0);
+                ++entries;
+            }
+            if (e1 - e0 > BS_LONG) {
+                if (threadIdx.x % LANES == 0) s_hub[atomicAdd(&s_nhub, 1u)] = (uint16_t)v;
+            } else {
+                expand(e0 + (int32_t)(threadIdx.x % LANES), e1, LANES);
+            }
+        }
+        __syncthreads();
+        const uint32_t nhub = s_nhub;
+        if (nhub) {   // uniform
+            for (uint32_t h = 0; h < nhub; ++h) {
+                const int32_t v = s_hub[h];
+                expand(a.R[v] + (int32_t)threadIdx.x, a.R[v + 1], BS_BLOCK);
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) s_nhub = 0;
+        }
+        lo = hi;
+        hi = s_cnt;
+        __syncthreads();
+    }
+    if (edges) atomicAdd(&s_edges, edges);
+    if (entries) atomicAdd(&s_entries, entries);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        a.out[0] = (uint32_t)L;
+        a.out[1] = s_entries;
+        a.out[2] = s_edges;
+        a.out[3] = s_cnt - 1u;
+    }
+}
+
+// Where one work-group is faster than the chip.  Per call, R-MAT with 4 or 16
+// edges drawn per vertex: 8,192 vertices and 57 K entries 103 us (125 by level
+// launches), 4,096 and 110 K 97 (118); beyond the line, 16,384 and 116 K 171
+// (128), 8,192 and 220 K 166 (120).  Rows of at most 16 entries (lattices) take
+// a thread each, and any number of them that fits the list: 33^2, 100^2 and
+// 181^2 81, 130 and 248 us (303, 441 and 656 before).
+static bool bfs_small_fits(const Ctx &c, const Graph &g)
+{
+    const Options &o = c.opt;
+    return g.n <= BS_MAX_N && (g.max_deg <= 16 || g.m + 16ll * g.n <= BS_COST) && o.bfs_direction != 2 &&
+           o.bfs_frontier == 0 && o.advance_mapping == 1 && !o.step_graphs;
+}
+
+static void run_bfs_small(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s)
+{
+    const BsmArgs a{g.R.as<int32_t>(), g.C.as<int32_t>(), g.n, depth, c.pinned};
+    c.ktimer.run("bfs_small_level", s, [&]() {
+        if (g.max_deg <= 16) hipLaunchKernelGGL(bfs_small<1>, dim3(1), dim3(BS_BLOCK), 0, s, a, src);
+        else hipLaunchKernelGGL(bfs_small<16>, dim3(1), dim3(BS_BLOCK), 0, s, a, src);
+    });
+    GFR_LAUNCH_CHECK();
+    GFR_HIP(hipStreamSynchronize(s));
+    const volatile uint32_t *h = c.pinned;
+    c.stats.v["levels"] += h[0];
+    c.stats.v["push_levels"] += h[0];
+    c.stats.v["pull_levels"] += 0.0;
+    c.stats.v["edges_inspected"] += h[2];
+    c.stats.v["push_entries"] += h[1];
+    c.stats.v["push_edges"] += h[2];
+    c.stats.v["push_new"] += h[3];
+    c.stats.v["launches"] += 1.0;
+    c.stats.v["solves"] += 1.0;
+}
+
 void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s) { run_bfs(c, g, src, depth, s, c.arena); }
 
 void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena &ar)
@@ -653,6 +793,10 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena
     // mark-byte levels on mesh-like graphs (bfs.frontier 0 auto, 1 queue, 2 mark bytes); a forced pull
     // direction needs the queue path's frontier bitmap
     const int fr = c.opt.bfs_frontier;
+    if (bfs_small_fits(c, g)) {
+        run_bfs_small(c, g, src, depth, s);
+        return;
+    }
     if (c.opt.bfs_direction != 2 && (fr == 2 || (fr == 0 && g.cls == GRAPH_MESH))) {
         run_bfs_bitmap(c, g, src, depth, s, ar);
         return;

@@ -265,3 +265,36 @@ def test_ranked_columns(ctx, name):
     again, it2, l2 = ctx.pagerank(g, 0.85, 1e-6, 1000)
     assert it == it2 and l1 == l2 < 1e-6 and np.array_equal(out, _host(again))
     g.free()
+
+
+SMALL = {   # name: (graph, source): around the rules of the one-work-group traversal, both lane counts
+    "one vertex": (lambda: (np.zeros(2, np.int32), np.zeros(0, np.int32)), 0),
+    "no edges at the source": (lambda: _union((np.zeros(6, np.int32), np.zeros(0, np.int32)), graphgen.rmat(9)), 2),
+    "row at the hub's line": (lambda: _rows([511, 512, 513, 1025, 3], 1), 0),
+    "hub": (lambda: _rows([60000, 700], 2), 60001),
+    "rmat": (lambda: graphgen.rmat(12), 5),
+    "most vertices": (lambda: graphgen.from_edges(32768, np.arange(32767), np.arange(1, 32768)), 32767),
+    "past the list": (lambda: graphgen.from_edges(32769, np.arange(32768), np.arange(1, 32769)), 3),
+    "row of 16": (lambda: _rows([16, 16, 1, 15], 3), 0),
+    "row of 17": (lambda: _rows([17, 16, 1, 15], 3), 0),
+    "lattice": (lambda: graphgen.grid(181), 77),
+}
+
+
+@pytest.mark.parametrize("name", list(SMALL))
+def test_small_graph_bfs(ctx, name):
+    make, src = SMALL[name]
+    row, col = make()
+    g = ctx.graph_load_csr(row, col)
+    want = oracle.bfs(row, col, src)
+    for direction in (0, 1, 2):
+        ctx.set_option("bfs.direction", direction)
+        try:
+            d = ctx.bfs(g, src)
+        finally:
+            ctx.set_option("bfs.direction", 0)
+        assert np.array_equal(_host(d), want)
+        if direction < 2 and row[src + 1] > row[src]:
+            assert ctx.stat("levels") == want.max() + 1
+    assert np.array_equal(_host(ctx.bfs_noalloc(g, src, d)), want)
+    g.free()

@@ -439,6 +439,16 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
 void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_t *dist,
                     hipStream_t s);
 
+// The sources of one batch, passed to its first kernel by value (a copy from
+// pageable host memory would be waited for).
+struct Sources64 {
+    int32_t v[64];
+    Sources64(const int32_t *s, int32_t k)
+    {
+        for (int32_t i = 0; i < 64; ++i) v[i] = i < k ? s[i] : 0;
+    }
+};
+
 // Edges per chunk of the gather / for-each-edge kernels and of the full queue.
 constexpr uint32_t GATHER_CH = 1024;
 

@@ -387,10 +387,11 @@ struct MsMarks {
     }
 };
 
-__global__ void msbfs_init(MsArgs a, const int32_t *src, float alpha)
+// one thread per source (two of them may be the same vertex)
+__global__ void msbfs_init(MsArgs a, Sources64 src, float alpha)
 {
+    if ((int32_t)threadIdx.x < a.k) atomicOr(a.nx + src.v[threadIdx.x], 1ull << threadIdx.x);
     if (threadIdx.x == 0) {
-        for (int32_t q = 0; q < a.k; ++q) a.nx[src[q]] |= 1ull << q;
         MsCtl *ctl = a.ctl;
         ctl->dir = MS_PUSH;
         ctl->level = -1;
@@ -419,7 +420,7 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
     const CompactGeom cg = compact_geom(nwords, c.num_cu);
     // level records: 8 bytes per vertex and depth, for the first MS_LVL_CAP depths
     c.arena.reserve(3 * al256(8ull * n) + al256(32ull * nwords) + 3 * al256(4ull * n) + al256(4 * nparts) +
-                    al256(16ull * cg.blocks) + al256(sizeof(MsCtl)) + 2 * al256(4 * 64) + al256(8ull * G) +
+                    al256(16ull * cg.blocks) + al256(sizeof(MsCtl)) + al256(4 * 64) + al256(8ull * G) +
                     al256(8ull * n * MS_LVL_CAP));
     MsArgs a;
     memset(&a, 0, sizeof a);   // padding too: the bytes key the captured steps
@@ -440,7 +441,6 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
     a.q.part = c.arena.take<int32_t>(nparts);
     unsigned long long *status = c.arena.take<unsigned long long>(2ull * cg.blocks);
     a.ctl = c.arena.take<MsCtl>(1);
-    int32_t *dsrc = c.arena.take<int32_t>(64);
     int32_t *base = c.arena.take<int32_t>(64);   // every source starts at level 0
     a.base = base;
     a.actp = c.arena.take<unsigned long long>(G);
@@ -461,8 +461,8 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
             .add(status, 0u, 4ull * cg.blocks)
             .add(base, 0u, 64)
             .run(s);
-        GFR_HIP(hipMemcpyAsync(dsrc, sources + g0, 4ull * kk, hipMemcpyHostToDevice, s));
-        hipLaunchKernelGGL(msbfs_init, dim3(1), dim3(64), 0, s, a, dsrc, (float)c.opt.msbfs_alpha);
+        hipLaunchKernelGGL(msbfs_init, dim3(1), dim3(64), 0, s, a, Sources64(sources + g0, kk),
+                           (float)c.opt.msbfs_alpha);
         GFR_LAUNCH_CHECK();
         auto launch = [&]() {
             c.ktimer.run("msbfs_level", s, [&]() {

@@ -1004,16 +1004,18 @@ struct BsMarks {
     }
 };
 
+// one thread per source (two of them may be the same vertex)
 template <int BITS>
-__global__ void bsssp_init(BsArgs a, const int32_t *src, int32_t k, uint32_t delta, float pull_alpha)
+__global__ void bsssp_init(BsArgs a, Sources64 src, int32_t k, uint32_t delta, float pull_alpha)
 {
+    const int32_t q = (int32_t)threadIdx.x;
+    if (q < k) {
+        const int32_t v = src.v[q];
+        bs_store<BITS>(a, (size_t)v, q, 0u);
+        atomicOr(a.nq + v, 1ull << q);
+        a.nany[v] = 1;
+    }
     if (threadIdx.x == 0) {
-        for (int32_t q = 0; q < k; ++q) {
-            const int32_t v = src[q];
-            bs_store<BITS>(a, (size_t)v, q, 0u);
-            a.nq[v] |= 1ull << q;
-            a.nany[v] = 1;
-        }
         BsCtl *ctl = a.ctl;
         ctl->mode = BS_RELAX;
         ctl->nf = ctl->mf = 0;
@@ -1086,17 +1088,26 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
         for (int32_t i = 0; i < k; ++i) run_sssp(c, g, sources[i], dist + (size_t)i * n, s);
         return;
     }
-    const uint32_t chunk = 1024;
+    // 1024 edges per work-group, or 256 on graphs whose 1024-edge chunks do not
+    // fill the chip: a wave relaxes its share of a chunk as a chain of row
+    // loads, 8 edges at a time, so the launch takes as long as that chain.  21
+    // and 64 queries on R-MAT graphs (16 edges drawn per vertex) of 1,000,
+    // 10,000, 50,021, 200,000 and 1 M vertices: 416 / 453, 591 / 666, 843 / 950,
+    // 1,704 / 1,988 and 5,519 / 6,874 us with 256; 648 / 736, 785 / 878, 1,012 /
+    // 1,166, 1,704 / 2,003 and 5,367 / 6,751 with 1024.  (Narrow rows and the
+    // paired and pull kernels keep 1024.)
+    const bool fine = g.m < (1 << 22) && c.opt.batch_narrow == 0 && !c.opt.batch_pair && !(c.opt.batch_pull_alpha > 0);
+    const uint32_t chunk = fine ? 256 : 1024;
     const uint32_t nwords = (uint32_t)(((int64_t)n + 63) / 64) * 2u;
     const size_t nparts = (size_t)(g.m / chunk) + 2;
     // relax / pull grid per row width: the option's work-groups per CU (or as
-    // many as are resident at once), at most one per 1024-edge chunk of the
+    // many as are resident at once), at most one per chunk of the
     // whole graph.  Many more work-groups than fit at once let the hardware
     // hand chunks of uneven cost to whichever CU frees first (R-MAT s22, 64
     // queries: 35.5 ms per batch at 8 per CU, 32.9 at 16, 30.3 at 64).  G
     // sizes the per-work-group partials.
     const int bpc = c.opt.batch_blocks_per_cu;
-    const int gcap = (int)std::min<int64_t>(64ll * c.num_cu, std::max<int64_t>(c.num_cu, g.m / 1024 + 1));
+    const int gcap = (int)std::min<int64_t>(64ll * c.num_cu, std::max<int64_t>(c.num_cu, g.m / chunk + 1));
     auto grid_of = [&](const void *relax, const void *pull) {
         return std::min(gcap, std::max(resident_grid(c, relax, bpc), resident_grid(c, pull, bpc)));
     };
@@ -1114,7 +1125,7 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
     else if (c.opt.batch_delta_factor > 0) delta = sssp_auto_delta(g, c.opt.batch_delta_factor);
     c.arena.reserve(al256(256ull * n) + al256(8ull * n) + 2 * al256(8ull * n) + 2 * al256(32ull * nwords) +
                     3 * al256(4ull * n) + al256(4 * nparts) + al256(16ull * G) + al256(16ull * cg.blocks) +
-                    al256(sizeof(BsCtl)) + al256(4 * 64) + al256(8ull * cg.blocks) + al256(4ull * nwords));
+                    al256(sizeof(BsCtl)) + al256(8ull * cg.blocks) + al256(4ull * nwords));
     BsArgs a;
     memset(&a, 0, sizeof a);   // padding too: the bytes key the captured steps
     a.R = g.R.as<int32_t>();
@@ -1137,7 +1148,6 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
     a.part = c.arena.take<uint32_t>(4ull * G);
     unsigned long long *status = c.arena.take<unsigned long long>(2ull * cg.blocks);
     a.ctl = c.arena.take<BsCtl>(1);
-    int32_t *dsrc = c.arena.take<int32_t>(64);
     a.actp = c.arena.take<unsigned long long>(cg.blocks);
     a.fbits = c.arena.take<uint32_t>(nwords);
     a.pending = c.opt.batch_pending != 0;
@@ -1172,15 +1182,14 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
                 .add(a.part, 0u, 4ull * G)
                 .add(status, 0u, 4ull * cg.blocks)
                 .run(s);
-            GFR_HIP(hipMemcpyAsync(dsrc, sources + g0, 4ull * kk, hipMemcpyHostToDevice, s));
             auto by_width = [&](auto f) {
                 if (bits == 8) f(std::integral_constant<int, 8>());
                 else if (bits == 16) f(std::integral_constant<int, 16>());
                 else f(std::integral_constant<int, 32>());
             };
             by_width([&](auto B) {
-                hipLaunchKernelGGL(bsssp_init<decltype(B)::value>, dim3(1), dim3(64), 0, s, a, dsrc, kk, delta,
-                                   pull_alpha);
+                hipLaunchKernelGGL(bsssp_init<decltype(B)::value>, dim3(1), dim3(64), 0, s, a,
+                                   Sources64(sources + g0, kk), kk, delta, pull_alpha);
             });
             auto compact = [&]() {
                 c.ktimer.run("bsssp_compact", s, [&]() {
@@ -1197,7 +1206,9 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
             auto launch = [&]() {
                 const int Gb = Gw[bits == 8 ? 0 : bits == 16 ? 1 : 2];
                 c.ktimer.run("bsssp_relax", s, [&]() {
-                    if (bits == 32 && pair)
+                    if (fine)
+                        hipLaunchKernelGGL((bsssp_relax<256, 32>), dim3(Gb), dim3(GFR_BLOCK), 0, s, a);
+                    else if (bits == 32 && pair)
                         hipLaunchKernelGGL(bsssp_relax2<1024>, dim3(Gb), dim3(GFR_BLOCK), 0, s, a);
                     else
                         by_width([&](auto B) {

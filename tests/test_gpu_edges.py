@@ -298,3 +298,36 @@ def test_small_graph_bfs(ctx, name):
             assert ctx.stat("levels") == want.max() + 1
     assert np.array_equal(_host(ctx.bfs_noalloc(g, src, d)), want)
     g.free()
+
+
+@pytest.mark.parametrize("k", [2, 24, 31, 32, 33, 64, 65, 97])
+@pytest.mark.parametrize("name", ["rmat", "hub rows", "lattice", "no edges at a source"])
+def test_batches_part_filled(ctx, name, k):
+    """Batches of every fill, duplicated sources among them, on graphs of one chunk and of many."""
+    row, col = {"rmat": lambda: graphgen.rmat(13), "hub rows": lambda: _rows([255, 256, 257, 1024, 1025, 3, 9000], 4),
+                "lattice": lambda: graphgen.grid(70),
+                "no edges at a source": lambda: _union((np.zeros(4, np.int32), np.zeros(0, np.int32)),
+                                                       graphgen.rmat(9))}[name]()
+    n = row.size - 1
+    w = graphgen.weights(row, col, 64)
+    g = ctx.graph_load_csr(row, col, w)
+    src = np.random.default_rng(k).integers(0, n, k).astype(np.int32)
+    src[-1] = src[0]
+    if name == "no edges at a source":
+        src[k // 2] = 1
+    ctx.set_option("batch.min_sssp", 2)
+    ctx.set_option("batch.min_bfs", 2)
+    try:
+        for delta in (0, 70):
+            ctx.set_option("batch.delta", delta)
+            d = _host(ctx.sssp_batch(g, src)).view(np.uint32).reshape(k, n)
+            for i in set([0, 1, k // 2, k - 2, k - 1]):
+                assert np.array_equal(d[i], oracle.sssp(row, col, w, int(src[i])))
+        b = _host(ctx.bfs_batch(g, src)).reshape(k, n)
+        for i in set([0, 1, k // 2, k - 1]):
+            assert np.array_equal(b[i], oracle.bfs(row, col, int(src[i])))
+    finally:
+        ctx.set_option("batch.delta", 0)
+        ctx.set_option("batch.min_sssp", 24)
+        ctx.set_option("batch.min_bfs", 8)
+        g.free()

@@ -102,6 +102,7 @@ struct BsArgs {
     FrontierQ full;              // every vertex with edges (pull sweeps)
     uint32_t full_nf, full_mf;
     BsCtl *ctl;
+    uint32_t width;              // words of a 32-bit distance row: 64, or 32 for batches of at most 32
 };
 
 constexpr int BS_UNROLL = 8;   // edges relaxed together (two distance rows each)
@@ -376,6 +377,189 @@ __global__ __launch_bounds__(GFR_BLOCK) void bsssp_relax(BsArgs a)
     if (unf) ctl->unfit = 1u;
     __shared__ uint32_t s_a[GFR_WAVES], s_b[GFR_WAVES], s_c[GFR_WAVES];
     nimp = wave_sum_u32(nimp);
+    nlr = wave_sum_u32(nlr);
+    if (lane == 0) {
+        s_a[wave] = nimp;
+        s_b[wave] = nfar;
+        s_c[wave] = nlr;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t x = 0, y = 0, z = 0;
+        for (int k = 0; k < GFR_WAVES; ++k) {
+            x += s_a[k];
+            y += s_b[k];
+            z += s_c[k];
+        }
+        a.part[4 * blockIdx.x] = x;
+        a.part[4 * blockIdx.x + 1] = y;
+        a.part[4 * blockIdx.x + 2] = z;
+    }
+}
+
+// The relaxation of bsssp_relax for batches of at most 32 queries: distance
+// rows of 32 words, two edges per row instruction (each half-wave one edge,
+// lane = query).  With 64-word rows half of every row and of every lane's work
+// would be empty; a random row costs about the same per instruction whatever
+// its width, so this halves the instructions per edge and the
+// bytes.  21 queries on R-MAT graphs (16 edges drawn per vertex) of 50,021,
+// 1 M and 4 M vertices: 702, 3,794 and 14,675 us per batch, 843, 5,367 and
+// 21,489 with 64-word rows.
+constexpr int BH_UNROLL = 8;    // edge pairs relaxed together (source and target rows of each)
+
+template <int CH>
+__global__ __launch_bounds__(GFR_BLOCK) void bsssp_relax_half(BsArgs a)
+{
+    BsCtl *ctl = a.ctl;
+    if (ctl->mode != BS_RELAX || ctl->dir != BS_PUSH) return;
+    const uint32_t hi = ctl->hi, nf = ctl->nf, mf = ctl->mf;
+    const FrontierQ q = a.q;
+    __shared__ uint32_t s_off[CH + 1];
+    __shared__ int32_t s_row[CH + 1];
+    __shared__ int32_t s_v[CH + 1];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int half = lane >> 5, ql = lane & 31;
+    // the masks of 64 queries hold these in their low words
+    const uint32_t *qm = (const uint32_t *)a.qm;
+    uint32_t *nq = (uint32_t *)a.nq, *fq = (uint32_t *)a.fq;
+    constexpr uint32_t QW = CH / GFR_WAVES;
+    const uint32_t nchunks = (mf + CH - 1) / CH;
+    uint32_t nimp = 0, nfar = 0, nlr = 0;
+    bool unf = false;
+    for (uint32_t c = blockIdx.x; c < nchunks; c += gridDim.x) {
+        const uint32_t e0 = c * CH;
+        const uint32_t e1 = min(e0 + (uint32_t)CH, mf);
+        const int s = q.part[c];
+        const int t = (c + 1 < nchunks) ? q.part[c + 1] : (int)nf - 1;
+        const int cnt = t - s + 1;
+        __syncthreads();
+        for (int i = threadIdx.x; i < cnt; i += GFR_BLOCK) {
+            s_off[i] = q.off[s + i];
+            s_row[i] = q.row[s + i];
+            s_v[i] = q.v[s + i];
+        }
+        __syncthreads();
+        const uint32_t eb = e0 + wave * QW, ee = min(eb + QW, e1);
+        if (eb >= ee) continue;
+        int ilo = upper_index(s_off, 0, cnt - 1, eb);
+        // lane l of a group describes edge e + l; the next group's loads are
+        // issued before this group relaxes (as in bsssp_relax)
+        auto fetch = [&](uint32_t e, int nbx, int32_t &vx, int32_t &wx, int32_t &ux, uint32_t &qx) {
+            const uint32_t el = e + (uint32_t)min(lane, nbx - 1);
+            const int il = upper_index(s_off, ilo, min(cnt - 1, ilo + lane + 1), el);
+            const int32_t idx = s_row[il] + (int32_t)(el - s_off[il]);
+            vx = a.C[idx];
+            wx = (int32_t)a.W[idx];
+            ux = s_v[il];
+            qx = qm[2 * (size_t)ux];
+            if (a.pending) qx |= nq[2 * (size_t)ux];
+            ilo = lane_bcast(il, nbx - 1);
+        };
+        int nbn = (int)min(64u, ee - eb);
+        int32_t vn, wn, un;
+        uint32_t qn;
+        fetch(eb, nbn, vn, wn, un, qn);
+        for (uint32_t e = eb; e < ee; e += 64) {
+            const int nb = nbn;
+            const int32_t vl = vn, wl = wn, ul = un;
+            const uint32_t qe = qn;
+            if (e + 64 < ee) {
+                nbn = (int)min(64u, ee - (e + 64));
+                fetch(e + 64, nbn, vn, wn, un, qn);
+            }
+            if (a.sparse != 0u && !ballot(lane < nb && (uint32_t)__popc(qe) > a.sparse)) {
+                // few queries per edge: lane = edge, one query per turn (see bsssp_relax)
+                uint32_t rem = lane < nb ? qe : 0u;
+                while (ballot(rem != 0u)) {
+                    const bool has = rem != 0u;
+                    const int qq = has ? __ffs(rem) - 1 : 0;
+                    rem &= rem - 1u;
+                    const uint32_t du = has ? a.D[(size_t)ul * 32 + qq] : BS_INF;
+                    const uint32_t dv = has ? a.D[(size_t)vl * 32 + qq] : 0u;
+                    const bool act = has & (du != BS_INF);
+                    const unsigned long long nd64 = (unsigned long long)du + (uint32_t)wl;
+                    const bool fits = nd64 < 0xFFFFFFFFull;
+                    const uint32_t nd = (uint32_t)nd64;
+                    const bool imp = act & fits & (nd < dv);
+                    unf |= act & !fits;
+                    nlr += act ? 1u : 0u;
+                    nimp += imp ? 1u : 0u;
+                    if (imp) {
+                        atomicMin(a.D + (size_t)vl * 32 + qq, nd);
+                        if (nd < hi) {
+                            atomicOr(nq + 2 * (size_t)vl, 1u << qq);
+                            a.nany[vl] = 1;
+                        } else {
+                            atomicOr(fq + 2 * (size_t)vl, 1u << qq);
+                            a.fany[vl] = 1;
+                        }
+                    }
+                    if (ballot(imp & (nd >= hi)) != 0ull && lane == 0) ++nfar;
+                }
+                continue;
+            }
+            // one edge (u, v, w) per half-wave, this lane's query
+            auto relax = [&](int32_t v, uint32_t w, uint32_t du, uint32_t dv, bool act) {
+                const unsigned long long nd64 = (unsigned long long)du + w;
+                const bool fits = nd64 < 0xFFFFFFFFull;
+                const uint32_t nd = (uint32_t)nd64;
+                const bool imp = act & fits & (nd < dv);
+                unf |= act & !fits;
+                nlr += act ? 1u : 0u;
+                nimp += imp ? 1u : 0u;
+                const uint64_t bn = ballot(imp & (nd < hi)), bf = ballot(imp & (nd >= hi));
+                if ((bn | bf) == 0ull) return;   // uniform
+                if (imp) atomicMin(a.D + (size_t)v * 32 + ql, nd);
+                const uint32_t hn = (uint32_t)(bn >> (32 * half)), hf = (uint32_t)(bf >> (32 * half));
+                if (ql == 0) {
+                    if (hn) {
+                        atomicOr(nq + 2 * (size_t)v, hn);
+                        a.nany[v] = 1;
+                    }
+                    if (hf) {
+                        atomicOr(fq + 2 * (size_t)v, hf);
+                        a.fany[v] = 1;
+                        ++nfar;
+                    }
+                }
+            };
+            const int32_t u_first = lane_bcast(ul, 0);
+            const bool one = u_first == lane_bcast(ul, nb - 1);   // the whole group leaves one vertex
+            uint32_t du1 = 0;
+            bool act1 = false;
+            if (one) {
+                du1 = a.D[(size_t)u_first * 32 + ql];
+                act1 = (((uint32_t)lane_bcast((int32_t)qe, 0) >> ql) & 1u) != 0;
+            }
+            for (int j0 = 0; j0 < nb; j0 += 2 * BH_UNROLL) {
+                uint32_t du[BH_UNROLL], dv[BH_UNROLL], ww[BH_UNROLL];
+                int32_t vv[BH_UNROLL];
+                bool act[BH_UNROLL];
+#pragma unroll
+                for (int j = 0; j < BH_UNROLL; ++j) {
+                    const int src = min(j0 + 2 * j + half, nb - 1);   // a padded edge repeats the last one
+                    act[j] = j0 + 2 * j + half < nb;
+                    vv[j] = __shfl(vl, src, 64);
+                    ww[j] = (uint32_t)__shfl(wl, src, 64);
+                    dv[j] = a.D[(size_t)vv[j] * 32 + ql];
+                    du[j] = du1;
+                    if (one) {
+                        act[j] &= act1;
+                    } else {
+                        du[j] = a.D[(size_t)__shfl(ul, src, 64) * 32 + ql];
+                        act[j] &= ((shfl_u32(qe, src) >> ql) & 1u) != 0;
+                    }
+                }
+                // (a pending query whose distance has not arrived keeps its mark)
+#pragma unroll
+                for (int j = 0; j < BH_UNROLL; ++j) relax(vv[j], ww[j], du[j], dv[j], act[j] & (du[j] != BS_INF));
+            }
+        }
+    }
+    if (unf) ctl->unfit = 1u;
+    __shared__ uint32_t s_a[GFR_WAVES], s_b[GFR_WAVES], s_c[GFR_WAVES];
+    nimp = wave_sum_u32(nimp);
+    nfar = wave_sum_u32(nfar);
     nlr = wave_sum_u32(nlr);
     if (lane == 0) {
         s_a[wave] = nimp;
@@ -840,7 +1024,7 @@ struct BsMarks {
             while (fm) {
                 const int qq = __ffsll(fm) - 1;
                 fm &= fm - 1;
-                const uint32_t d = bs_load<BITS>(a, (size_t)v, qq);
+                const uint32_t d = BITS == 32 ? a.D[(size_t)v * a.width + qq] : bs_load<BITS>(a, (size_t)v, qq);
                 if (d < hi) {
                     if (d >= lo) nm |= 1ull << qq;
                 } else {
@@ -1011,7 +1195,8 @@ __global__ void bsssp_init(BsArgs a, Sources64 src, int32_t k, uint32_t delta, f
     const int32_t q = (int32_t)threadIdx.x;
     if (q < k) {
         const int32_t v = src.v[q];
-        bs_store<BITS>(a, (size_t)v, q, 0u);
+        if (BITS == 32) a.D[(size_t)v * a.width + q] = 0u;
+        else bs_store<BITS>(a, (size_t)v, q, 0u);
         atomicOr(a.nq + v, 1ull << q);
         a.nany[v] = 1;
     }
@@ -1037,9 +1222,9 @@ __global__ void bsssp_init(BsArgs a, Sources64 src, int32_t k, uint32_t delta, f
     }
 }
 
-// out[q][v] = D[v][q] for the queries q in `lanes`: 64 vertices x 64 queries
+// out[q][v] = D[v][q] for the queries q in `lanes`: 64 vertices x WIDTH queries
 // per tile through LDS (narrow rows widened, unreached -> 0xFFFFFFFF)
-template <int BITS>
+template <int BITS, int WIDTH = 64>
 __global__ __launch_bounds__(GFR_BLOCK) void bsssp_transpose(BsArgs a, int32_t n, unsigned long long lanes,
                                                              uint32_t *out)
 {
@@ -1048,12 +1233,14 @@ __global__ __launch_bounds__(GFR_BLOCK) void bsssp_transpose(BsArgs a, int32_t n
     for (int32_t tb = blockIdx.x; tb < ntiles; tb += gridDim.x) {
         const int32_t v0 = tb * 64;
         __syncthreads();
-        for (int i = threadIdx.x; i < 64 * 64; i += GFR_BLOCK) {
-            const int r = i / 64, q = i % 64;
-            tile[r][q] = (v0 + r < n) ? bs_load<BITS>(a, (size_t)(v0 + r), q) : 0u;
+        for (int i = threadIdx.x; i < 64 * WIDTH; i += GFR_BLOCK) {
+            const int r = i / WIDTH, q = i % WIDTH;
+            uint32_t x = 0u;
+            if (v0 + r < n) x = BITS == 32 ? a.D[(size_t)(v0 + r) * WIDTH + q] : bs_load<BITS>(a, (size_t)(v0 + r), q);
+            tile[r][q] = x;
         }
         __syncthreads();
-        for (int i = threadIdx.x; i < 64 * 64; i += GFR_BLOCK) {
+        for (int i = threadIdx.x; i < 64 * WIDTH; i += GFR_BLOCK) {
             const int q = i / 64, r = i % 64;
             if (((lanes >> q) & 1ull) && v0 + r < n) out[(size_t)q * n + v0 + r] = tile[r][q];
         }
@@ -1065,15 +1252,16 @@ __global__ __launch_bounds__(GFR_BLOCK) void bsssp_transpose(BsArgs a, int32_t n
 // `lanes`, a vertex left unreached next to a reached one.  Wave per vertex,
 // lane = query.
 __global__ __launch_bounds__(GFR_BLOCK) void bsssp_unfit_check(const int32_t *R, const int32_t *C, const uint32_t *D,
-                                                                int32_t n, unsigned long long lanes, uint32_t *flag)
+                                                                int32_t n, unsigned long long lanes, uint32_t width,
+                                                                uint32_t *flag)
 {
     const int lane = lane_id();
-    const bool mine = (lanes >> lane) & 1ull;
+    const bool mine = (lanes >> lane) & 1ull;   // (lanes hold a query only below width)
     const uint32_t waves = gridDim.x * GFR_WAVES;
     for (uint32_t v = blockIdx.x * GFR_WAVES + threadIdx.x / 64; v < (uint32_t)n; v += waves) {
-        if (!mine || D[(size_t)v * 64 + lane] != BS_INF) continue;
+        if (!mine || D[(size_t)v * width + lane] != BS_INF) continue;
         for (int32_t e = R[v]; e < R[v + 1]; ++e)
-            if (D[(size_t)C[e] * 64 + lane] != BS_INF) {
+            if (D[(size_t)C[e] * width + lane] != BS_INF) {
                 *flag = 1u;
                 break;
             }
@@ -1091,12 +1279,13 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
     // 1024 edges per work-group, or 256 on graphs whose 1024-edge chunks do not
     // fill the chip: a wave relaxes its share of a chunk as a chain of row
     // loads, 8 edges at a time, so the launch takes as long as that chain.  21
-    // and 64 queries on R-MAT graphs (16 edges drawn per vertex) of 1,000,
-    // 10,000, 50,021, 200,000 and 1 M vertices: 416 / 453, 591 / 666, 843 / 950,
-    // 1,704 / 1,988 and 5,519 / 6,874 us with 256; 648 / 736, 785 / 878, 1,012 /
-    // 1,166, 1,704 / 2,003 and 5,367 / 6,751 with 1024.  (Narrow rows and the
-    // paired and pull kernels keep 1024.)
-    const bool fine = g.m < (1 << 22) && c.opt.batch_narrow == 0 && !c.opt.batch_pair && !(c.opt.batch_pull_alpha > 0);
+    // and 64 queries in 64-word rows on R-MAT graphs (16 edges drawn per vertex)
+    // of 1,000, 10,000, 50,021, 200,000 and 1 M vertices: 416 / 453, 591 / 666,
+    // 843 / 950, 1,704 / 1,988 and 5,519 / 6,874 us with 256; 648 / 736, 785 /
+    // 878, 1,012 / 1,166, 1,704 / 2,003 and 5,367 / 6,751 with 1024.  (Narrow rows
+    // and the paired and pull kernels keep 1024.)
+    const bool plain = c.opt.batch_narrow == 0 && !c.opt.batch_pair && !(c.opt.batch_pull_alpha > 0);
+    const bool fine = plain && g.m < (1 << 22);
     const uint32_t chunk = fine ? 256 : 1024;
     const uint32_t nwords = (uint32_t)(((int64_t)n + 63) / 64) * 2u;
     const size_t nparts = (size_t)(g.m / chunk) + 2;
@@ -1108,8 +1297,13 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
     // sizes the per-work-group partials.
     const int bpc = c.opt.batch_blocks_per_cu;
     const int gcap = (int)std::min<int64_t>(64ll * c.num_cu, std::max<int64_t>(c.num_cu, g.m / chunk + 1));
+    // (small chunks: eight groups per CU.  A mesh runs hundreds of thin launches,
+    // whose idle groups cost it 16.9 ms per 24-query batch on the 1000^2 lattice
+    // with a group per chunk, 13.4 ms so.)
+    const int gfine = 8 * c.num_cu;
     auto grid_of = [&](const void *relax, const void *pull) {
-        return std::min(gcap, std::max(resident_grid(c, relax, bpc), resident_grid(c, pull, bpc)));
+        const int cap = fine ? std::min(gcap, gfine) : gcap;
+        return std::min(cap, std::max(resident_grid(c, relax, bpc), resident_grid(c, pull, bpc)));
     };
     const int Gw[3] = {grid_of((const void *)bsssp_relax<1024, 8>, (const void *)bsssp_pull<1024, 8>),
                        grid_of((const void *)bsssp_relax<1024, 16>, (const void *)bsssp_pull<1024, 16>),
@@ -1171,10 +1365,12 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
     for (int32_t g0 = 0; g0 < k; g0 += 64) {
         const int32_t kk = std::min<int32_t>(64, k - g0);
         const unsigned long long lanes_mask = kk == 64 ? ~0ull : ((1ull << kk) - 1ull);
+        const bool half = plain && kk <= 32;   // rows of 32 words, two edges per row instruction
+        a.width = half ? 32u : 64u;
         BsCtl h;
         for (;;) {
             Fills()
-                .add(a.D, 0xFFFFFFFFu, 2ull * bits * n)   // 8 * bits bytes per vertex
+                .add(a.D, 0xFFFFFFFFu, (half ? 32ull : 2ull * bits) * n)   // 8 * bits bytes per vertex
                 .add(a.nq, 0u, 2ull * n)
                 .add(a.fq, 0u, 2ull * n)
                 .add(a.nany, 0u, 8ull * nwords)
@@ -1206,7 +1402,11 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
             auto launch = [&]() {
                 const int Gb = Gw[bits == 8 ? 0 : bits == 16 ? 1 : 2];
                 c.ktimer.run("bsssp_relax", s, [&]() {
-                    if (fine)
+                    if (half && fine)
+                        hipLaunchKernelGGL(bsssp_relax_half<256>, dim3(Gb), dim3(GFR_BLOCK), 0, s, a);
+                    else if (half)
+                        hipLaunchKernelGGL(bsssp_relax_half<1024>, dim3(Gb), dim3(GFR_BLOCK), 0, s, a);
+                    else if (fine)
                         hipLaunchKernelGGL((bsssp_relax<256, 32>), dim3(Gb), dim3(GFR_BLOCK), 0, s, a);
                     else if (bits == 32 && pair)
                         hipLaunchKernelGGL(bsssp_relax2<1024>, dim3(Gb), dim3(GFR_BLOCK), 0, s, a);
@@ -1232,8 +1432,12 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
             run_until_done(c, &a.ctl->mode, BS_DONE, g.bsssp_iter_hint.load(std::memory_order_relaxed) + 1,
                            64ll * n + 1024, s, launch, sizeof(BsCtl), &key);
             if (bits == 32) {   // no fallback can follow (a failed batch fails the call)
-                hipLaunchKernelGGL(bsssp_transpose<32>, dim3(G), dim3(GFR_BLOCK), 0, s, a, n, lanes_mask,
-                                   dist + (size_t)g0 * n);
+                if (half)
+                    hipLaunchKernelGGL((bsssp_transpose<32, 32>), dim3(G), dim3(GFR_BLOCK), 0, s, a, n, lanes_mask,
+                                       dist + (size_t)g0 * n);
+                else
+                    hipLaunchKernelGGL(bsssp_transpose<32>, dim3(G), dim3(GFR_BLOCK), 0, s, a, n, lanes_mask,
+                                       dist + (size_t)g0 * n);
                 GFR_LAUNCH_CHECK();
             }
             memcpy(&h, c.pinned, sizeof(BsCtl));
@@ -1254,7 +1458,7 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
             // 32-bit rows (narrow batches fall back instead): was an unfit sum a distance?
             fill_u32(a.part, 0u, 1, s);
             hipLaunchKernelGGL(bsssp_unfit_check, dim3(G), dim3(GFR_BLOCK), 0, s, a.R, a.C, a.D, n, lanes_mask,
-                               a.part);
+                               a.width, a.part);
             GFR_LAUNCH_CHECK();
             read_back(c, a.part, 4, s);
             if (*(volatile uint32_t *)c.pinned)
@@ -1405,6 +1609,7 @@ struct BsSession final : LaneSession {
         a.W = g.W.as<uint32_t>();
         a.n = g.n;
         a.nwords = nwords;
+        a.width = 64;
         a.D = (uint32_t *)take(256 * L.n);
         a.D16 = nullptr;   // sessions keep 32-bit rows (lanes join at different times; no batch to solve again)
         a.D8 = nullptr;

@@ -38,12 +38,40 @@ struct BcArgs {
     uint32_t *vis;
 };
 
+// One level of the forward pass: where its vertices lie in the BFS order.
+struct BcLevel {
+    uint32_t mf, nf;         // edges, entries (0, 0: not reached)
+    uint32_t start, pbase;   // first entry and first chunk index
+};
+
+// The forward pass runs from device memory alone: the host queues levels ahead
+// (each launch knows its level) and waits once per source, for their number.
+// Waiting for every level's size took about 25 us a level.
+struct BcCtl {
+    uint32_t done;           // first word: read back by the host
+    uint32_t levels;         // levels found
+    uint32_t pull;           // the next discovery pulls
+    uint32_t parity, err;    // of the compaction
+    uint32_t force;          // 0 auto, 1 push, 2 pull
+    uint32_t push_levels, pull_levels;
+    double mu, prev_nf;      // edges of unvisited vertices; size of the level before
+    double alpha, beta;
+};
+
+// the direction of the discovery from a level of nf vertices and mf edges
+__device__ __forceinline__ uint32_t bc_direction(const BcCtl *ctl, uint32_t nf, uint32_t mf, int32_t n)
+{
+    if (ctl->force) return ctl->force == 2;
+    if (!ctl->pull) return (double)mf > ctl->mu / ctl->alpha && (double)nf > ctl->prev_nf;
+    return !((double)nf < (double)n / ctl->beta && (double)nf < ctl->prev_nf);
+}
+
 // push advance of one level (load-balanced edge chunks): an unvisited
 // neighbour gets its depth code and a mark byte (plain stores; duplicates write
 // the same values and collapse in the compaction)
 template <int CH>
-__global__ __launch_bounds__(GFR_BLOCK) void bc_discover(BcArgs a, FrontierQ qin, uint32_t nf, uint32_t mf,
-                                                         int32_t L, uint8_t *mark)
+__device__ __forceinline__ void bc_push_discover(const BcArgs &a, const FrontierQ &qin, uint32_t nf, uint32_t mf,
+                                                 int32_t L, uint8_t *mark)
 {
     __shared__ uint32_t s_off[CH + 1];
     __shared__ int32_t s_row[CH + 1];
@@ -76,8 +104,8 @@ __global__ __launch_bounds__(GFR_BLOCK) void bc_discover(BcArgs a, FrontierQ qin
 
 // pull discovery of level L+1: every unvisited vertex (lane = vertex) scans
 // its list four neighbours at a time until one is in the level-L bitmap
-__global__ __launch_bounds__(GFR_BLOCK) void bc_pull_discover(BcArgs a, int32_t n, const uint32_t *fb, int32_t L,
-                                                              uint8_t *mark)
+__device__ __forceinline__ void bc_pull_discover(const BcArgs &a, int32_t n, const uint32_t *fb, int32_t L,
+                                                 uint8_t *mark)
 {
     const uint32_t waves = gridDim.x * GFR_WAVES;
     const int lane = lane_id();
@@ -110,15 +138,41 @@ __global__ __launch_bounds__(GFR_BLOCK) void bc_pull_discover(BcArgs a, int32_t 
     }
 }
 
-// compaction of one BFS level into its slice of the BFS order (vertex order);
+// discovery of level L + 1
+template <int CH>
+__global__ __launch_bounds__(GFR_BLOCK) void bc_discover(BcArgs a, int32_t n, FrontierQ order, const BcLevel *lv,
+                                                         const BcCtl *ctl, const uint32_t *fb, int32_t L,
+                                                         uint8_t *mark)
+{
+    if (ctl->done) return;
+    if (ctl->pull) {
+        bc_pull_discover(a, n, fb, L, mark);
+    } else {
+        const BcLevel l = lv[L];
+        bc_push_discover<CH>(a, QueueAt{&lv[L].start}(order), l.nf, l.mf, L, mark);
+    }
+}
+
+// compaction of level L + 1 into its slice of the BFS order (vertex order);
 // also writes the level's bitmap for a following pull discovery
 struct BcMarks {
     uint8_t *mark;
     uint32_t *vis;
     uint32_t *fb;
-    unsigned long long *out;   // packed (entries << 32 | edges) of the new level
-    uint32_t *parity;
-    __device__ bool skip() const { return false; }
+    BcLevel *lv;
+    BcCtl *ctl;
+    int32_t L, n;
+    __device__ bool skip() const { return ctl->done != 0; }
+    __device__ BcLevel next() const
+    {
+        const BcLevel l = lv[L];
+        return BcLevel{0u, 0u, l.start + l.nf, l.pbase + (l.mf + GATHER_CH - 1) / GATHER_CH + 1u};
+    }
+    __device__ FrontierQ place(const FrontierQ &q) const
+    {
+        const BcLevel x = next();
+        return FrontierQ{q.v + x.start, q.off + x.start, q.row + x.start, q.part + x.pbase};
+    }
     __device__ uint32_t mask(uint32_t w) const
     {
         const uint32_t m = marks_to_mask(mark + 32ull * w);
@@ -132,15 +186,28 @@ struct BcMarks {
     __device__ void partial(uint32_t) {}
     __device__ void control(uint32_t nf, uint32_t mf) const
     {
-        if (threadIdx.x == 0) {
-            *out = ((unsigned long long)nf << 32) | mf;
-            *parity ^= 1u;
+        if (threadIdx.x != 0) return;
+        ctl->parity ^= 1u;
+        if (ctl->pull) ctl->pull_levels += 1u;
+        else ctl->push_levels += 1u;
+        if (nf == 0) {
+            ctl->done = 1u;
+            return;
         }
+        BcLevel x = next();
+        x.nf = nf;
+        x.mf = mf;
+        lv[L + 1] = x;
+        ctl->levels += 1u;
+        ctl->mu -= (double)mf;
+        ctl->prev_nf = (double)lv[L].nf;
+        ctl->pull = bc_direction(ctl, nf, mf, n);
     }
 };
 
-__global__ void bc_source_init(BcArgs a, int32_t src, FrontierQ q0, double *sigma, unsigned long long *ctr0,
-                               uint32_t *fb)
+// (lv[] is zero but for what the forward pass writes)
+__global__ void bc_source_init(BcArgs a, int32_t src, int32_t n, FrontierQ q0, double *sigma, BcLevel *lv, BcCtl *ctl,
+                               uint32_t *fb, uint32_t force, double alpha, double beta)
 {
     const int32_t rs = a.R[src], deg = a.R[src + 1] - rs;
     if (threadIdx.x == 0) {
@@ -151,7 +218,16 @@ __global__ void bc_source_init(BcArgs a, int32_t src, FrontierQ q0, double *sigm
         q0.v[0] = src;
         q0.off[0] = 0;
         q0.row[0] = rs;
-        *ctr0 = (1ull << 32) | (unsigned long long)(uint32_t)deg;
+        lv[0] = BcLevel{(uint32_t)deg, 1u, 0u, 0u};
+        ctl->done = deg == 0;
+        ctl->levels = 1;
+        ctl->pull = 0;
+        ctl->force = force;
+        ctl->alpha = alpha;
+        ctl->beta = beta;
+        ctl->mu = (double)a.R[n] - (double)deg;
+        ctl->prev_nf = 0.0;
+        ctl->pull = bc_direction(ctl, 1u, (uint32_t)deg, n);
     }
     for (uint32_t c = threadIdx.x; (uint64_t)c * GATHER_CH < (uint64_t)deg; c += blockDim.x) q0.part[c] = 0;
 }
@@ -187,8 +263,10 @@ struct DeltaFin {
     }
 };
 
-__global__ void bc_leaf_coef(const FrontierQ q, uint32_t nf, const double *sigma, double *coef)
+__global__ void bc_leaf_coef(FrontierQ q, const BcLevel *l, const double *sigma, double *coef)
 {
+    const uint32_t nf = l->nf;
+    q = QueueAt{&l->start}(q);
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nf; i += gridDim.x * blockDim.x) {
         const int32_t v = q.v[i];
         coef[v] = 1.0 / sigma[v];
@@ -201,10 +279,6 @@ __global__ void bc_to_f32(const double *acc, float *out, int32_t n)
         out[v] = (float)acc[v];
 }
 
-struct Level {
-    uint32_t start, nf, mf, pbase;
-};
-
 void run_bc(Ctx &c, Graph &g, const int32_t *sources, int32_t k, float *bc, hipStream_t s)
 {
     const int32_t n = g.n;
@@ -213,7 +287,7 @@ void run_bc(Ctx &c, Graph &g, const int32_t *sources, int32_t k, float *bc, hipS
     const size_t nch = (size_t)(g.m / GATHER_CH) + 2;
     const size_t nlev = (size_t)n + 2;
     c.arena.reserve(al256(4ull * n) + al256(4ull * nwords) + al256(32ull * nwords) + 3 * al256(8ull * n) + 3 * al256(4ull * n) +
-                    al256(4 * nparts) + 2 * al256(8 * nch) + al256(8 * nlev) +
+                    al256(4 * nparts) + 2 * al256(8 * nch) + al256(sizeof(BcLevel) * nlev) +
                     al256(16ull * (uint64_t)compact_geom(nwords, c.num_cu).blocks) + al256(256) +
                     al256(4ull * nwords));
     BcArgs a;
@@ -229,101 +303,77 @@ void run_bc(Ctx &c, Graph &g, const int32_t *sources, int32_t k, float *bc, hipS
     int32_t *row = c.arena.take<int32_t>(n);
     int32_t *part = c.arena.take<int32_t>(nparts);
     GatherScratch gs{c.arena.take<double>(nch), c.arena.take<double>(nch)};
-    unsigned long long *ctr = c.arena.take<unsigned long long>(nlev);
+    BcLevel *lv = c.arena.take<BcLevel>(nlev);
     const int G = grid_blocks(c, 4);
     const CompactGeom cg = compact_geom(nwords, c.num_cu);
     uint8_t *mark = c.arena.take<uint8_t>(32ull * nwords);
     unsigned long long *status = c.arena.take<unsigned long long>(2ull * cg.blocks);
-    uint32_t *cw = c.arena.take<uint32_t>(64);   // [0] compaction parity, [1] look-back error
+    BcCtl *ctl = c.arena.take<BcCtl>(1);
     uint32_t *fb = c.arena.take<uint32_t>(nwords);
     Fills()
         .add(mark, 0u, 8ull * nwords)
         .add(status, 0u, 4ull * cg.blocks)
-        .add(cw, 0u, 64)
+        .add(ctl, 0u, sizeof(BcCtl) / 4)
+        .add(lv, 0u, nlev * sizeof(BcLevel) / 4)
         .add(acc, 0u, 2ull * n)
         .run(s);
-    auto qat = [&](const Level &l) {
-        return FrontierQ{order + l.start, off + l.start, row + l.start, part + l.pbase};
-    };
-    std::vector<Level> lv;
-    double levels_total = 0, push_levels = 0, pull_levels = 0;
-    const int force = c.opt.bc_direction;
-    const double alpha = c.opt.bc_alpha, beta = c.opt.bc_beta;
+    const FrontierQ q{order, off, row, part};
+    const uint32_t *zero = c.zero_word.as<uint32_t>();
+    const dim3 grid(G), block(GFR_BLOCK);
+    double levels_total = 0;
+    BcCtl h{};
+    uint32_t used = 1;   // levels of the source before
     for (int32_t si = 0; si < k; ++si) {
         const int32_t src = sources[si];
-        Fills().add(a.dc, 0xFFFFFFFFu, (n + 3) / 4).add(a.vis, 0u, nwords).add(fb, 0u, nwords).run(s);   // dc: BC_UNSEEN
-        lv.clear();
-        lv.push_back(Level{0, 1, 0, 0});
-        hipLaunchKernelGGL(bc_source_init, dim3(1), dim3(GFR_BLOCK), 0, s, a, src, qat(lv[0]), sigma, ctr, fb);
+        Fills()
+            .add(a.dc, 0xFFFFFFFFu, (n + 3) / 4)   // BC_UNSEEN
+            .add(a.vis, 0u, nwords)
+            .add(fb, 0u, nwords)
+            .add(lv, 0u, used * sizeof(BcLevel) / 4)
+            .run(s);
+        hipLaunchKernelGGL(bc_source_init, dim3(1), block, 0, s, a, src, n, q, sigma, lv, ctl, fb,
+                           (uint32_t)c.opt.bc_direction, c.opt.bc_alpha, c.opt.bc_beta);
         GFR_LAUNCH_CHECK();
-        read_back(c, ctr, 8, s);
-        lv[0].mf = c.pinned[0];
-        // unvisited vertices and their edges, for the direction choice
-        double mu = (double)g.m - (double)lv[0].mf, prev_nf = 0.0;
-        bool pull = false;
-        // forward
-        for (;;) {
-            const Level cur = lv.back();
-            const int32_t L = (int32_t)lv.size() - 1;
-            if (cur.mf == 0) break;
-            if (force == 1) pull = false;
-            else if (force == 2) pull = true;
-            else if (!pull) pull = (double)cur.mf > mu / alpha && (double)cur.nf > prev_nf;
-            else pull = !((double)cur.nf < (double)n / beta && (double)cur.nf < prev_nf);
-            prev_nf = (double)cur.nf;
-            Level nx{cur.start + cur.nf, 0, 0, cur.pbase + (cur.mf + GATHER_CH - 1) / GATHER_CH + 1};
-            unsigned long long *cn = ctr + lv.size();
-            if (pull) {
-                hipLaunchKernelGGL(bc_pull_discover, dim3(G), dim3(GFR_BLOCK), 0, s, a, n, fb, L, mark);
-                pull_levels += 1;
-            } else {
-                hipLaunchKernelGGL(bc_discover<GATHER_CH>, dim3(G), dim3(GFR_BLOCK), 0, s, a, qat(cur), cur.nf,
-                                   cur.mf, L, mark);
-                push_levels += 1;
-            }
-            hipLaunchKernelGGL(compact_kernel<BcMarks>, dim3(cg.blocks), dim3(GFR_BLOCK), 0, s, a.R, n, nwords, cg.wpt,
-                               BcMarks{mark, a.vis, fb, cn, cw}, qat(nx), GATHER_CH, status, cw, cw + 1);
-            GFR_LAUNCH_CHECK();
-            read_back(c, cn, 8, s);
-            nx.mf = c.pinned[0];
-            nx.nf = c.pinned[1];
-            if (nx.nf == 0) break;
-            mu -= (double)nx.mf;
-            lv.push_back(nx);
-            const uint32_t *cw = (const uint32_t *)cn;
-            hipLaunchKernelGGL((gather_chunks<GATHER_CH, SigmaOp, SigmaFin>), dim3(G), dim3(GFR_BLOCK), 0, s,
-                               qat(nx), cw + 1, cw, a.C, SigmaOp{a.dc, sigma, level_code(L)}, SigmaFin{sigma}, gs,
-                               c.zero_word.as<uint32_t>());
-            hipLaunchKernelGGL((gather_fixup<GATHER_CH, SigmaFin>), dim3(G), dim3(GFR_BLOCK), 0, s, qat(nx), cw + 1,
-                               cw, SigmaFin{sigma}, gs, c.zero_word.as<uint32_t>());
-            GFR_LAUNCH_CHECK();
+        // forward: launch i discovers level i + 1 and counts its paths
+        int32_t L = 0;
+        auto launch = [&]() {
+            if (L > n) return;   // (there are at most n levels)
+            hipLaunchKernelGGL(bc_discover<GATHER_CH>, grid, block, 0, s, a, n, q, lv, ctl, fb, L, mark);
+            hipLaunchKernelGGL(compact_kernel<BcMarks>, dim3(cg.blocks), block, 0, s, a.R, n, nwords, cg.wpt,
+                               BcMarks{mark, a.vis, fb, lv, ctl, L, n}, q, GATHER_CH, status, &ctl->parity, &ctl->err);
+            const BcLevel *x = lv + L + 1;
+            const QueueAt at{&x->start};
+            hipLaunchKernelGGL((gather_chunks<GATHER_CH, SigmaOp, SigmaFin>), grid, block, 0, s, q, &x->nf, &x->mf,
+                               a.C, SigmaOp{a.dc, sigma, level_code(L)}, SigmaFin{sigma}, gs, zero, at);
+            hipLaunchKernelGGL((gather_fixup<GATHER_CH, SigmaFin>), grid, block, 0, s, q, &x->nf, &x->mf,
+                               SigmaFin{sigma}, gs, zero, at);
+            ++L;
+        };
+        const int32_t hint = g.bc_levels_hint.load(std::memory_order_relaxed);
+        run_until_done(c, &ctl->done, 1u, hint + hint / 32, (int64_t)n + 8, s, launch, sizeof(BcCtl));
+        memcpy(&h, c.pinned, sizeof h);
+        if (h.err) fail(GFR_E_DEVICE, "bc: frontier compaction look-back timed out");
+        g.bc_levels_hint.store((int32_t)h.levels, std::memory_order_relaxed);
+        used = h.levels + 1;
+        levels_total += (double)h.levels;
+        // backward: the deepest level has no successors
+        const int32_t Lmax = (int32_t)h.levels - 1;
+        if (Lmax >= 1) hipLaunchKernelGGL(bc_leaf_coef, grid, block, 0, s, q, lv + Lmax, sigma, coef);
+        for (int32_t l = Lmax - 1; l >= 1; --l) {
+            const QueueAt at{&lv[l].start};
+            hipLaunchKernelGGL((gather_chunks<GATHER_CH, DeltaOp, DeltaFin>), grid, block, 0, s, q, &lv[l].nf,
+                               &lv[l].mf, a.C, DeltaOp{a.dc, coef, level_code(l + 1)}, DeltaFin{sigma, coef, acc}, gs,
+                               zero, at);
+            hipLaunchKernelGGL((gather_fixup<GATHER_CH, DeltaFin>), grid, block, 0, s, q, &lv[l].nf, &lv[l].mf,
+                               DeltaFin{sigma, coef, acc}, gs, zero, at);
         }
-        levels_total += (double)lv.size();
-        // backward: deepest level has no successors
-        const int32_t Lmax = (int32_t)lv.size() - 1;
-        if (Lmax >= 1) {
-            const Level &d = lv[Lmax];
-            hipLaunchKernelGGL(bc_leaf_coef, dim3(G), dim3(GFR_BLOCK), 0, s, qat(d), d.nf, sigma, coef);
-            GFR_LAUNCH_CHECK();
-        }
-        for (int32_t L = Lmax - 1; L >= 1; --L) {
-            const Level &l = lv[L];
-            const uint32_t *cw = (const uint32_t *)(ctr + L);
-            hipLaunchKernelGGL((gather_chunks<GATHER_CH, DeltaOp, DeltaFin>), dim3(G), dim3(GFR_BLOCK), 0, s, qat(l),
-                               cw + 1, cw, a.C, DeltaOp{a.dc, coef, level_code(L + 1)}, DeltaFin{sigma, coef, acc}, gs,
-                               c.zero_word.as<uint32_t>());
-            hipLaunchKernelGGL((gather_fixup<GATHER_CH, DeltaFin>), dim3(G), dim3(GFR_BLOCK), 0, s, qat(l), cw + 1, cw,
-                               DeltaFin{sigma, coef, acc}, gs, c.zero_word.as<uint32_t>());
-            GFR_LAUNCH_CHECK();
-        }
+        GFR_LAUNCH_CHECK();
     }
     hipLaunchKernelGGL(bc_to_f32, dim3(G), dim3(GFR_BLOCK), 0, s, acc, bc, n);
     GFR_LAUNCH_CHECK();
-    read_back(c, cw + 1, 4, s);
-    if (c.pinned[0]) fail(GFR_E_DEVICE, "bc: frontier compaction look-back timed out");
     c.stats.v["levels"] = levels_total;
-    c.stats.v["push_levels"] = push_levels;
-    c.stats.v["pull_levels"] = pull_levels;
+    c.stats.v["push_levels"] = (double)h.push_levels;   // summed over the sources
+    c.stats.v["pull_levels"] = (double)h.pull_levels;
 }
 
 }  // namespace gfr

@@ -250,6 +250,13 @@ __device__ __forceinline__ uint32_t run_degrees(const int32_t *R, int32_t n, uin
     return (active && bits) ? word_degrees(R, n, w, bits) : 0u;
 }
 
+// Where the queue goes: q, unless the functor places it (member place(q)).
+template <class M> __device__ __forceinline__ auto placed(const M &m, const FrontierQ &q, int) -> decltype(m.place(q))
+{
+    return m.place(q);
+}
+template <class M> __device__ __forceinline__ FrontierQ placed(const M &, const FrontierQ &q, long) { return q; }
+
 // Compaction kernel.  M: functor with
 //     bool skip() const                  whole launch is a no-op (uniform)
 //     uint32_t mask(uint32_t w)          marks of vertices 32w..32w+31 (may consume / update state)
@@ -263,6 +270,7 @@ __global__ __launch_bounds__(GFR_BLOCK) void compact_kernel(const int32_t *R, in
                                                             uint32_t *err)
 {
     if (mk.skip()) return;
+    q = placed(mk, q, 0);
     const uint32_t p = *parity;
     unsigned long long *status = status2 + (size_t)p * gridDim.x;
     const uint32_t w0 = (blockIdx.x * GFR_BLOCK + threadIdx.x) * wpt;

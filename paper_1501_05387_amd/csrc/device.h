@@ -105,6 +105,17 @@ struct FrontierQ {
     int32_t *part;
 };
 
+// A level's slice of a longer queue: entry and chunk-index places of its start
+// (null: the queue itself).
+struct QueueAt {
+    const uint32_t *at;   // [0] first entry, [1] first chunk index
+    __device__ FrontierQ operator()(const FrontierQ &q) const
+    {
+        if (!at) return q;
+        return FrontierQ{q.v + at[0], q.off + at[0], q.row + at[0], q.part + at[1]};
+    }
+};
+
 // Largest i in [lo, hi] with a[i] <= key (a sorted ascending, a[lo] <= key).
 __device__ __forceinline__ int upper_index(const uint32_t *a, int lo, int hi, uint32_t key)
 {

@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <condition_variable>
 #include <map>
@@ -143,6 +144,7 @@ struct Graph {
     std::atomic<int32_t> bitmap_launch_hint{8};
     std::atomic<int32_t> sssp_iter_hint{16};
     std::atomic<int32_t> msbfs_levels_hint{8};
+    std::atomic<int32_t> bc_levels_hint{8};
     std::atomic<int32_t> bsssp_iter_hint{16};
     int32_t levels_hint() const { return bfs_levels_hint.load(std::memory_order_relaxed); }
     int32_t iter_hint() const { return sssp_iter_hint.load(std::memory_order_relaxed); }
@@ -572,7 +574,10 @@ int32_t run_until_done(Ctx &c, const uint32_t *flag_dev, uint32_t done_value, in
         read_back(c, flag_dev, bytes, s);
         if (*(volatile uint32_t *)c.pinned == done_value) break;
         if (launched > max_launches) fail(GFR_E_DEVICE, "iteration watchdog: solve did not converge");
-        batch = batch < 128 ? batch * 2 : 256;
+        // double while little is known; later a quarter more at a time, as a
+        // traversal a few levels longer than the last one would otherwise
+        // queue its whole length again in launches that return at once
+        batch = launched < 32 ? (int32_t)launched : (int32_t)std::min<int64_t>(std::max<int64_t>(8, launched / 4), 256);
     }
     return (int32_t)launched;
 }

@@ -35,13 +35,15 @@ template <int CH, class Op, class Fin>
 __global__ __launch_bounds__(GFR_BLOCK) void gather_chunks(FrontierQ q, const uint32_t *nf_p,
                                                            const uint32_t *mf_p, const int32_t *C,
                                                            Op op, Fin fin, GatherScratch gs,
-                                                           const uint32_t *stop)
+                                                           const uint32_t *stop, QueueAt at = QueueAt{nullptr})
 {
     constexpr int EPL = 4;   // consecutive edges per lane
     static_assert(CH == GFR_BLOCK * EPL && CH / 32 <= 64, "a chunk is four edges per thread");
     if (*stop) return;
     const uint32_t nf = *nf_p, mf = *mf_p;
     const uint32_t nchunks = (mf + CH - 1) / CH;
+    if (blockIdx.x >= nchunks) return;
+    q = at(q);
     __shared__ uint32_t s_flag[CH / 32];    // bit k: a list starts at edge k of the chunk
     __shared__ int32_t s_delta[CH + 1];     // per entry: its place in C less its edge offset
     __shared__ int32_t s_v[CH + 1];
@@ -153,11 +155,14 @@ __global__ __launch_bounds__(GFR_BLOCK) void gather_chunks(FrontierQ q, const ui
 template <int CH, class Fin>
 __global__ __launch_bounds__(GFR_BLOCK) void gather_fixup(FrontierQ q, const uint32_t *nf_p,
                                                           const uint32_t *mf_p, Fin fin,
-                                                          GatherScratch gs, const uint32_t *stop)
+                                                          GatherScratch gs, const uint32_t *stop,
+                                                          QueueAt at = QueueAt{nullptr})
 {
     if (*stop) return;
     const uint32_t nf = *nf_p, mf = *mf_p;
     const uint32_t nchunks = (mf + CH - 1) / CH;
+    if (blockIdx.x * GFR_BLOCK >= nchunks) return;
+    q = at(q);
     for (uint32_t c = blockIdx.x * GFR_BLOCK + threadIdx.x; c < nchunks; c += gridDim.x * GFR_BLOCK) {
         const uint32_t e0 = c * CH, e1 = min(e0 + (uint32_t)CH, mf);
         const int t = (c + 1 < nchunks) ? q.part[c + 1] : (int)nf - 1;

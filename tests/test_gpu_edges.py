@@ -331,3 +331,45 @@ def test_batches_part_filled(ctx, name, k):
         ctx.set_option("batch.min_sssp", 24)
         ctx.set_option("batch.min_bfs", 8)
         g.free()
+
+
+@pytest.mark.parametrize("count", [1, 2047, 2048, 2049, 2048 * 1024, 2048 * 1024 + 1])
+def test_operator_lists_at_tile_edges(ctx, count):
+    """Lists of one tile to one past what every work-group sums itself; a bad last id or a list that
+    does not fit leaves the outputs as they were."""
+    import ctypes
+    import torch
+    import paper_1501_05387_amd as gfr
+    n = max(count, 8)                                     # filter scans the vertices, the others the list
+    row = np.zeros(n + 1, np.int32)
+    row[-1] = 2                                           # the last vertex has two edges
+    col = np.array([0, n - 2], np.int32)
+    g = ctx.graph_load_csr(row, col)
+    X = np.random.default_rng(count).permutation(n).astype(np.int32) if count == n else np.array([n - 1], np.int32)
+    src, edge, dst = (np.full(2, n - 1, np.int32), np.arange(2, dtype=np.int32), col)
+    for got, want in zip(ctx.advance(g, torch.from_numpy(X).cuda()), (src, edge, dst)):
+        assert np.array_equal(_host(got), want)
+    assert np.array_equal(_host(ctx.filter(g, X)), np.sort(X))
+    dist = (np.arange(n) % 5).astype(np.uint32)
+    near, far = ctx.split(g, X, dist, 2)
+    assert np.array_equal(_host(near), X[dist[X] < 2]) and np.array_equal(_host(far), X[dist[X] >= 2])
+    outs = [torch.full((count + 2,), -7, dtype=torch.int32, device="cuda") for _ in range(3)]
+    a, b, c = (o.data_ptr() for o in outs)
+    k, k2 = ctypes.c_int64(), ctypes.c_int64()
+    L = gfr.lib()
+
+    def calls(items, cap):
+        i = items.ctypes.data
+        return (L.gfr_advance(ctx.ptr, g.handle, i, count, a, b, c, min(cap, 1), ctypes.byref(k), None),
+                L.gfr_filter(ctx.ptr, g.handle, i, count, None, a, cap, ctypes.byref(k), None),
+                L.gfr_split(ctx.ptr, g.handle, i, count, dist.ctypes.data, 9, a, b, cap, ctypes.byref(k),
+                            ctypes.byref(k2), None))
+
+    assert calls(X, count - 1) == (gfr.GFR_E_CAPACITY,) * 3
+    for bad in (n, -1):
+        Y = X.copy()
+        Y[-1] = bad
+        assert calls(Y, count + 2) == (gfr.GFR_E_INVALID,) * 3
+    torch.cuda.synchronize()
+    assert all(bool((o == -7).all()) for o in outs)
+    g.free()

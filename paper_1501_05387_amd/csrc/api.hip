@@ -3,6 +3,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <map>
 #include <mutex>
 #include <cmath>
@@ -119,17 +120,40 @@ void Fills::run(hipStream_t s) const
     GFR_LAUNCH_CHECK();
 }
 
-__global__ void k_read_back(uint32_t *host, const uint32_t *dev, uint32_t words)
+__global__ void k_read_back(uint32_t *host, const uint32_t *dev, uint32_t words, uint32_t number)
 {
     for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) host[i] = dev[i];
+    __syncthreads();
+    if (threadIdx.x == 0) arrive(host, number);
+}
+
+void alloc_pinned(Ctx &c)
+{
+    GFR_HIP(hipHostMalloc((void **)&c.pinned, PINNED_BYTES + 64, hipHostMallocCoherent));
+    memset(c.pinned, 0, PINNED_BYTES + 64);
+}
+
+void await_arrival(Ctx &c, hipStream_t s)
+{
+    const uint32_t *word = c.pinned + ARRIVAL_WORD;
+    const auto t0 = std::chrono::steady_clock::now();
+    for (;;) {
+        for (int i = 0; i < 64; ++i) {
+            if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == c.arrivals) return;
+            __builtin_ia32_pause();
+        }
+        if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(SPIN_US)) break;
+    }
+    GFR_HIP(hipStreamSynchronize(s));
 }
 
 void read_back(Ctx &c, const void *dev, size_t bytes, hipStream_t s)
 {
     if (bytes > PINNED_BYTES || bytes % 4) fail(GFR_E_DEVICE, "internal: read-back of a bad size");
-    hipLaunchKernelGGL(k_read_back, dim3(1), dim3(64), 0, s, c.pinned, (const uint32_t *)dev, (uint32_t)(bytes / 4));
+    hipLaunchKernelGGL(k_read_back, dim3(1), dim3(64), 0, s, c.pinned, (const uint32_t *)dev, (uint32_t)(bytes / 4),
+                       ++c.arrivals);
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipStreamSynchronize(s));
+    await_arrival(c, s);
 }
 
 static bool is_pinned_host(const void *p)
@@ -293,8 +317,7 @@ struct OutBuf {
     }
     void finish(Ctx &c, hipStream_t s)
     {
-        if (staged) copy_to_host(c.bounce, user, dev, bytes, s);
-        GFR_HIP(hipStreamSynchronize(s));
+        if (staged) copy_to_host(c.bounce, user, dev, bytes, s);   // (otherwise complete: timed_end has waited)
     }
 };
 
@@ -346,6 +369,7 @@ static void timed_begin(Ctx &c, hipStream_t s)
 {
     c.stats.clear();
     c.timed = false;
+    c.waited = false;
     c.ktimer.reset();
     c.ktimer.on = c.opt.profile_kernels != 0;
     c.ktimer.advance_only = c.opt.profile_kernels == 2;
@@ -355,7 +379,7 @@ static void timed_begin(Ctx &c, hipStream_t s)
 static void timed_end(Ctx &c, hipStream_t s)
 {
     GFR_HIP(hipEventRecord(c.ev1, s));
-    GFR_HIP(hipStreamSynchronize(s));
+    if (!c.waited) read_back(c, nullptr, 0, s);
     c.timed = true;
     c.ktimer.collect(c.stats.v);
 }
@@ -595,6 +619,7 @@ static void with_pred(Ctx &c, Graph &g, int32_t *pred_out, hipStream_t s, Run ru
     c.arena.reserve((dev ? 0 : al256(4ull * g.n)) + pred_scratch_bytes(g));   // the solve's scratch is no longer needed
     if (!dev) pd = c.arena.take<int32_t>(g.n);
     run(pd);
+    c.waited = false;
     if (!dev) deliver(c, pred_out, pd, 4ull * g.n, s);
 }
 
@@ -633,7 +658,7 @@ gfr_status gfr_ctx_create(int32_t device, const char *tuning_json, gfr_ctx **out
         // null stream (PyTorch's default stream) finishes before ours starts
         GFR_HIP(hipStreamCreateWithFlags(&cc.stream, hipStreamDefault));
         cc.noalloc_scratch = noalloc_scratch(device);
-        GFR_HIP(hipHostMalloc((void **)&cc.pinned, PINNED_BYTES, hipHostMallocDefault));
+        alloc_pinned(cc);
         GFR_HIP(hipEventCreate(&cc.ev0));
         GFR_HIP(hipEventCreate(&cc.ev1));
         cc.zero_word.alloc(256);
@@ -704,6 +729,7 @@ gfr_status gfr_get_stat(gfr_ctx *ctx, const char *key, double *value)
         if (serve_stat(c, key, value)) return;
         if (c.timed) {   // the events of the last call
             float ms = 0.f;
+            GFR_HIP(hipEventSynchronize(c.ev1));
             GFR_HIP(hipEventElapsedTime(&ms, c.ev0, c.ev1));
             c.stats.v["kernel_ms"] = ms;
             c.timed = false;
@@ -825,8 +851,7 @@ gfr_status gfr_bfs_noalloc(gfr_ctx *ctx, gfr_graph gh, int32_t source, int32_t *
         c.ktimer.on = false;   // per-launch timing would create events
         GFR_HIP(hipEventRecord(c.ev0, s));
         run_bfs(c, g, source, depth_out, s, ar);   // capacity is checked before any launch
-        GFR_HIP(hipEventRecord(c.ev1, s));
-        GFR_HIP(hipStreamSynchronize(s));
+        GFR_HIP(hipEventRecord(c.ev1, s));   // (run_bfs has waited)
         c.timed = true;
     });
 }
@@ -929,12 +954,7 @@ gfr_status gfr_pagerank_filtered(gfr_ctx *ctx, gfr_graph gh, double damping, dou
         timed_begin(c, s);
         const uint8_t *act = run_pagerank_filtered(c, g, damping, vertex_tol, max_iter, (double *)o.dev, &it, &l1, s);
         timed_end(c, s);
-        if (active_out) {
-            if (is_device_ptr(active_out))
-                GFR_HIP(hipMemcpyAsync(active_out, act, (size_t)g.n, hipMemcpyDeviceToDevice, s));
-            else
-                copy_to_host(c.bounce, active_out, act, (size_t)g.n, s);
-        }
+        if (active_out) deliver(c, active_out, act, (size_t)g.n, s);
         o.finish(c, s);
         if (iters_out) *iters_out = it;
         if (final_l1_out) *final_l1_out = l1;

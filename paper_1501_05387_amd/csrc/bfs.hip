@@ -656,7 +656,8 @@ static void run_bfs_bitmap(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStr
 // the whole work-group, so that a hub does not hold a level up.  (2, 4, 8 and 16
 // lanes with rows put aside from 32, 128, 256 and 512 entries: 122, 67, 57 and
 // 51 us per call on R-MAT with 1,024 vertices and 21 K entries, 133 us with the
-// level launches; the kernel takes 24 us of the 51.)
+// level launches; the kernel takes 24 us of the 51.  All with a wait for the
+// stream; 41 us since the kernel itself tells the host that it is done.)
 constexpr int BS_BLOCK = 1024;
 constexpr int32_t BS_MAX_N = 32768;     // ids fit 16 bits, the list 64 KB
 constexpr int32_t BS_LONG = 512;
@@ -668,6 +669,7 @@ struct BsmArgs {
     int32_t n;
     int32_t *depth;
     uint32_t *out;       // pinned: levels, entries, edges, discovered
+    uint32_t number;     // of this arrival
 };
 
 template <int LANES>
@@ -743,12 +745,14 @@ __global__ __launch_bounds__(BS_BLOCK) void bfs_small(BsmArgs a, int32_t src)
     }
     if (edges) atomicAdd(&s_edges, edges);
     if (entries) atomicAdd(&s_entries, entries);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // every wave's depths have left it
     __syncthreads();
     if (threadIdx.x == 0) {
         a.out[0] = (uint32_t)L;
         a.out[1] = s_entries;
         a.out[2] = s_edges;
         a.out[3] = s_cnt - 1u;
+        arrive(a.out, a.number);
     }
 }
 
@@ -767,13 +771,13 @@ static bool bfs_small_fits(const Ctx &c, const Graph &g)
 
 static void run_bfs_small(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s)
 {
-    const BsmArgs a{g.R.as<int32_t>(), g.C.as<int32_t>(), g.n, depth, c.pinned};
+    const BsmArgs a{g.R.as<int32_t>(), g.C.as<int32_t>(), g.n, depth, c.pinned, ++c.arrivals};
     c.ktimer.run("bfs_small_level", s, [&]() {
         if (g.max_deg <= 16) hipLaunchKernelGGL(bfs_small<1>, dim3(1), dim3(BS_BLOCK), 0, s, a, src);
         else hipLaunchKernelGGL(bfs_small<16>, dim3(1), dim3(BS_BLOCK), 0, s, a, src);
     });
     GFR_LAUNCH_CHECK();
-    GFR_HIP(hipStreamSynchronize(s));
+    await_arrival(c, s);
     const volatile uint32_t *h = c.pinned;
     c.stats.v["levels"] += h[0];
     c.stats.v["push_levels"] += h[0];
@@ -786,7 +790,11 @@ static void run_bfs_small(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStre
     c.stats.v["solves"] += 1.0;
 }
 
-void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s) { run_bfs(c, g, src, depth, s, c.arena); }
+void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s)
+{
+    run_bfs(c, g, src, depth, s, c.arena);
+    c.waited = true;   // each path ends with a read-back
+}
 
 void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena &ar)
 {

@@ -190,6 +190,7 @@ void run_cc(Ctx &c, Graph &g, int32_t *label, int32_t *ncomp, hipStream_t s)
     hipLaunchKernelGGL(cc_sum, dim3(1), block, 0, s, rpart, (uint32_t)G, word + 1);
     GFR_LAUNCH_CHECK();
     read_back(c, word + 1, 4, s);
+    c.waited = true;
     *ncomp = (int32_t)c.pinned[0];
     c.stats.v["rounds"] = 3;   // first neighbours, second neighbours, the rest
 }

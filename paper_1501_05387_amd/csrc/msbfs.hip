@@ -413,6 +413,7 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
         for (int32_t i = 0; i < k; ++i) run_bfs(c, g, sources[i], depth + (size_t)i * n, s);
         return;
     }
+    c.waited = false;   // (the output kernel)
     const uint32_t chunk = 1024;
     const uint32_t nwords = (uint32_t)(((int64_t)n + 63) / 64) * 2u;
     const size_t nparts = (size_t)(g.m / chunk) + 2;

@@ -37,7 +37,7 @@
 // id was bad.  On R-MAT with 260,017 vertices, an advance of 3,781
 // vertices (180 K edges), a filter of the result and a split of what is left
 // took 74, 65 and 66 us with a wait for each of these checks, 57, 46 and 46 us
-// so.
+// so (43, 33 and 33 with the wait of read_back since).
 #include <string.h>
 
 #include <algorithm>
@@ -291,6 +291,7 @@ static Grand grand_back(Ctx &c, const Grand *grand, hipStream_t s, const char *w
 {
     Grand h;
     read_back(c, grand, sizeof h, s);
+    c.waited = true;
     memcpy(&h, c.pinned, sizeof h);
     if (h.bad) fail(GFR_E_INVALID, std::string(who) + ": " + what + " id out of range");
     return h;

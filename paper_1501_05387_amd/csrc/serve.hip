@@ -247,7 +247,7 @@ struct SingleCtx {
         c.device = main.device;
         c.num_cu = main.num_cu;
         GFR_HIP(hipStreamCreateWithFlags(&c.stream, hipStreamNonBlocking));
-        GFR_HIP(hipHostMalloc((void **)&c.pinned, 4096, hipHostMallocDefault));
+        alloc_pinned(c);
     }
     ~SingleCtx()
     {

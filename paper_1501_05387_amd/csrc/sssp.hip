@@ -907,8 +907,10 @@ static void run_sssp_marks(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStr
     g.sssp_iter_hint.store((int32_t)h.iter, std::memory_order_relaxed);
 }
 
+// (each path ends with a read-back)
 void run_sssp(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStream_t s)
 {
+    c.waited = true;
     if (!g.weighted) fail(GFR_E_INVALID, "sssp: graph was loaded without weights");
     const int32_t n = g.n;
     const uint32_t chunk = (uint32_t)c.opt.advance_chunk;

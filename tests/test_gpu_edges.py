@@ -373,3 +373,38 @@ def test_operator_lists_at_tile_edges(ctx, count):
     torch.cuda.synchronize()
     assert all(bool((o == -7).all()) for o in outs)
     g.free()
+
+
+def test_results_are_complete_on_return(ctx):
+    """Two contexts in two threads, short and long solves in turn, each result read at once on another stream."""
+    import threading
+    import torch
+    import paper_1501_05387_amd as gfr
+    row, col = graphgen.rmat(10)
+    lrow, lcol = graphgen.grid(400)
+    w = graphgen.weights(lrow, lcol, 64)
+    want = [oracle.bfs(row, col, s) for s in range(8)]
+    long = [oracle.sssp(lrow, lcol, w, s) for s in (0, 1)]
+    X = np.arange(0, row.size - 1, 3, dtype=np.int32)
+    bad = []
+
+    def work():
+        c, st = gfr.Context(0), torch.cuda.Stream()
+        g, lg = c.graph_load_csr(row, col), c.graph_load_csr(lrow, lcol, w)
+        with torch.cuda.stream(st):
+            for i in range(40):
+                got = c.bfs(g, i % 8).clone()
+                kept = c.filter(g, X).clone()
+                d = c.sssp(lg, i % 2).clone() if i % 10 == 0 else None
+                if not (np.array_equal(_host(got), want[i % 8]) and np.array_equal(_host(kept), X)):
+                    bad.append(i)
+                if d is not None and not np.array_equal(_host(d).view(np.uint32), long[i % 2]):
+                    bad.append(-i)
+        c.close()
+
+    ts = [threading.Thread(target=work) for _ in range(2)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad

@@ -9,11 +9,11 @@
 // This kernel turns the marks into the next frontier queue in vertex order.
 // Every thread owns `wpt` consecutive groups of 32 vertices ("words"); the
 // caller's functor reads (and consumes) the marks of a word and returns them
-// as a 32-bit mask.  Pass 1 counts vertices and their degrees; a block scan
-// and a decoupled look-back across work-groups give every thread its global
-// slot and edge offset; pass 2 stages the group's entries in LDS and writes
-// (vertex, edge offset, row start) contiguously, plus the chunk index used by
-// the load-balanced advance.  No counter is shared by all work-groups (on
+// as a 32-bit mask.  Pass 1 counts vertices and their degrees (with one word a
+// thread the row offsets stay in LDS); a block scan and a decoupled look-back
+// across work-groups give every thread its global slot and edge offset; pass 2
+// stages the group's entries in LDS and writes (vertex, edge offset, row start)
+// contiguously, plus the chunk index used by the load-balanced advance.  No counter is shared by all work-groups (on
 // MI355X same-address atomics serialise at ~11 ns each): the only
 // cross-group traffic is one 64-bit status word per work-group, and the last
 // work-group, which learns the grand totals, runs the caller's control.
@@ -163,7 +163,8 @@ __device__ __forceinline__ unsigned long long lookback_prefix(unsigned long long
 // return the sum of their degrees.  The 33 row offsets are fetched with
 // independent loads (vector loads when the run lies inside R), so the latency
 // is paid once per word, not once per vertex.
-__device__ __forceinline__ uint32_t word_degrees(const int32_t *R, int32_t n, uint32_t w, uint32_t &bits)
+__device__ __forceinline__ uint32_t word_degrees(const int32_t *R, int32_t n, uint32_t w, uint32_t &bits,
+                                                 int32_t *slice = nullptr)
 {
     const int32_t v0 = (int32_t)(w * 32u);
     int32_t r[33];
@@ -181,6 +182,10 @@ __device__ __forceinline__ uint32_t word_degrees(const int32_t *R, int32_t n, ui
     } else {
 #pragma unroll
         for (int i = 0; i < 33; ++i) r[i] = (v0 + i <= n) ? R[v0 + i] : r[i > 0 ? i - 1 : 0];
+    }
+    if (slice) {   // as run_degrees leaves them
+#pragma unroll
+        for (int i = 0; i < 33; ++i) slice[i < 32 ? i : 33] = r[i];
     }
     uint32_t s = 0, keep = 0;
 #pragma unroll
@@ -202,7 +207,8 @@ __device__ __forceinline__ uint32_t word_degrees(const int32_t *R, int32_t n, ui
 // 33-entry slices from there (offset j at j + j/32, so that the lanes' slices
 // fall in different banks), instead of 33 offsets a lane 128 bytes apart.
 // Otherwise as word_degrees.  s_r: this wave's 2,113 LDS words (one run per
-// wave and launch).
+// wave and launch), where the lanes that hold marks leave their 33 offsets, at
+// 33 * lane and (the last) one past the next lane's first, for the second pass.
 constexpr int COMPACT_RUN_LDS = 2 * 1024 + 64 + 1;
 
 __device__ __forceinline__ uint32_t run_degrees(const int32_t *R, int32_t n, uint32_t w, bool active, uint32_t &bits,
@@ -247,7 +253,7 @@ __device__ __forceinline__ uint32_t run_degrees(const int32_t *R, int32_t n, uin
             return sum;
         }
     }
-    return (active && bits) ? word_degrees(R, n, w, bits) : 0u;
+    return (active && bits) ? word_degrees(R, n, w, bits, s_r + 33 * lane_id()) : 0u;
 }
 
 // Where the queue goes: q, unless the functor places it (member place(q)).
@@ -278,8 +284,8 @@ __global__ __launch_bounds__(GFR_BLOCK) void compact_kernel(const int32_t *R, in
     uint32_t cnt = 0, edges = 0;
 #pragma unroll
     for (int i = 0; i < COMPACT_MAX_WPT; ++i) words[i] = 0;
+    __shared__ int32_t s_run[GFR_WAVES][COMPACT_RUN_LDS];
     if (wpt == 1) {
-        __shared__ int32_t s_run[GFR_WAVES][COMPACT_RUN_LDS];
         const bool active = w0 < nwords;
         uint32_t bits = active ? mk.mask(w0) : 0u;
         edges = run_degrees(R, n, w0, active, bits, s_run[threadIdx.x / 64]);   // drops vertices without edges
@@ -307,71 +313,103 @@ __global__ __launch_bounds__(GFR_BLOCK) void compact_kernel(const int32_t *R, in
     const uint32_t slot0 = (uint32_t)(base >> 31);
     uint32_t eoff = (uint32_t)(base & 0x7FFFFFFFull);   // edge offset of the next staged entry
 
-    // pass 2: stage entries in LDS round by round, write them contiguously
-    __shared__ int32_t s_v[COMPACT_STAGE];
+    // Pass 2: stage entries in LDS round by round and write them contiguously,
+    // one entry a lane.  The chunk index is written from the staged offsets, one
+    // chunk a lane: R-MAT's hubs have neighbouring ids, and the thread that owns
+    // 32 of them would write thousands of chunk starts by itself.  BFS of R-MAT
+    // with 4 M vertices, the three fattest compactions: 36, 59 and 29 us when the
+    // owners wrote their entries' chunks and the degrees were loaded again here,
+    // 23, 56 and 19 from the offsets in LDS, 12, 44 and 21 so.
+    __shared__ int32_t s_v[COMPACT_STAGE], s_row[COMPACT_STAGE];
+    __shared__ uint32_t s_o[COMPACT_STAGE + 1];   // and the end of the last entry
     __shared__ uint32_t s_e[GFR_WAVES];
+    const uint32_t sh = (uint32_t)__builtin_ctz(chunk);   // (chunks are powers of two)
     uint32_t my = (uint32_t)(excl >> 31);   // block-local index of this thread's next entry
+    uint32_t off = eoff + (uint32_t)(excl & 0x7FFFFFFFull);   // its edge offset (one word a thread)
     int wi = 0;
     uint32_t cur = words[0];
     for (uint32_t r0 = 0; r0 < bcnt; r0 += COMPACT_STAGE) {
         const uint32_t r1 = r0 + COMPACT_STAGE;
-        // this thread's entries falling into [r0, r1)
-        while (my < r1 && wi < (int)wpt) {
-            if (!cur) {
-                if (++wi < (int)wpt) {
-#pragma unroll
-                    for (int i = 1; i < COMPACT_MAX_WPT; ++i)
-                        if (i == wi) cur = words[i];
-                }
-                continue;
-            }
-            const int bi = __ffs(cur) - 1;
-            cur &= cur - 1;
-            s_v[my - r0] = (int32_t)((w0 + wi) * 32u) + bi;
-            ++my;
-        }
-        __syncthreads();
         const uint32_t cntr = min((uint32_t)COMPACT_STAGE, bcnt - r0);
-        // each thread takes COMPACT_EPT consecutive staged entries
-        const uint32_t j0 = threadIdx.x * COMPACT_EPT;
-        int32_t vv[COMPACT_EPT], rr[COMPACT_EPT];
-        uint32_t dd[COMPACT_EPT], tsum = 0;
-#pragma unroll
-        for (int k = 0; k < COMPACT_EPT; ++k) {
-            dd[k] = 0;
-            vv[k] = 0;
-            rr[k] = 0;
-            if (j0 + k < cntr) {
-                vv[k] = s_v[j0 + k];
-                rr[k] = R[vv[k]];
-                dd[k] = (uint32_t)(R[vv[k] + 1] - rr[k]);
-                tsum += dd[k];
+        // this thread's entries falling into [r0, r1)
+        if (wpt == 1) {   // whole entries, from the offsets that pass 1 left in LDS
+            const int32_t *slice = s_run[threadIdx.x / 64] + 33 * lane_id();
+            while (cur && my < r1) {
+                const int bi = __ffs(cur) - 1;
+                cur &= cur - 1;
+                const int32_t row = slice[bi];
+                s_v[my - r0] = (int32_t)(w0 * 32u) + bi;
+                s_row[my - r0] = row;
+                s_o[my - r0] = off;
+                off += (uint32_t)(slice[bi == 31 ? 33 : bi + 1] - row);
+                ++my;
+                if (my - r0 == cntr) s_o[cntr] = off;
             }
-        }
-        // exclusive scan of the per-thread degree sums
-        uint32_t inc = wave_incl_scan(tsum);
-        if (lane_id() == 63) s_e[threadIdx.x / 64] = inc;
-        __syncthreads();
-        uint32_t before = 0, rtot = 0;
+            __syncthreads();
+        } else {
+            while (my < r1 && wi < (int)wpt) {
+                if (!cur) {
+                    if (++wi < (int)wpt) {
 #pragma unroll
-        for (int i = 0; i < GFR_WAVES; ++i) {
-            if (i < (int)(threadIdx.x / 64)) before += s_e[i];
-            rtot += s_e[i];
-        }
-        uint32_t o = eoff + before + inc - tsum;
-#pragma unroll
-        for (int k = 0; k < COMPACT_EPT; ++k) {
-            if (j0 + k < cntr) {
-                const uint32_t slot = slot0 + r0 + j0 + k;
-                q.v[slot] = vv[k];
-                q.off[slot] = o;
-                q.row[slot] = rr[k];
-                for (uint32_t c = (o + chunk - 1) / chunk; (uint64_t)c * chunk < (uint64_t)o + dd[k]; ++c)
-                    q.part[c] = (int32_t)slot;
-                o += dd[k];
+                        for (int i = 1; i < COMPACT_MAX_WPT; ++i)
+                            if (i == wi) cur = words[i];
+                    }
+                    continue;
+                }
+                const int bi = __ffs(cur) - 1;
+                cur &= cur - 1;
+                s_v[my - r0] = (int32_t)((w0 + wi) * 32u) + bi;
+                ++my;
             }
+            __syncthreads();
+            // each thread takes COMPACT_EPT consecutive staged entries
+            const uint32_t j0 = threadIdx.x * COMPACT_EPT;
+            int32_t rr[COMPACT_EPT];
+            uint32_t dd[COMPACT_EPT], tsum = 0;
+#pragma unroll
+            for (int k = 0; k < COMPACT_EPT; ++k) {
+                dd[k] = 0;
+                rr[k] = 0;
+                if (j0 + k < cntr) {
+                    const int32_t v = s_v[j0 + k];
+                    rr[k] = R[v];
+                    dd[k] = (uint32_t)(R[v + 1] - rr[k]);
+                    tsum += dd[k];
+                }
+            }
+            // exclusive scan of the per-thread degree sums
+            uint32_t inc = wave_incl_scan(tsum);
+            if (lane_id() == 63) s_e[threadIdx.x / 64] = inc;
+            __syncthreads();
+            uint32_t before = 0, rtot = 0;
+#pragma unroll
+            for (int i = 0; i < GFR_WAVES; ++i) {
+                if (i < (int)(threadIdx.x / 64)) before += s_e[i];
+                rtot += s_e[i];
+            }
+            uint32_t o = eoff + before + inc - tsum;
+#pragma unroll
+            for (int k = 0; k < COMPACT_EPT; ++k) {
+                if (j0 + k < cntr) {
+                    s_row[j0 + k] = rr[k];
+                    s_o[j0 + k] = o;
+                    o += dd[k];
+                }
+            }
+            eoff += rtot;
+            if (threadIdx.x == 0) s_o[cntr] = eoff;
+            __syncthreads();
         }
-        eoff += rtot;
+        for (uint32_t j = threadIdx.x; j < cntr; j += GFR_BLOCK) {
+            const uint32_t slot = slot0 + r0 + j;
+            q.v[slot] = s_v[j];
+            q.off[slot] = s_o[j];
+            q.row[slot] = s_row[j];
+        }
+        // edge offsets stay below 2^31, so chunk numbers and their first edges fit
+        const uint32_t oend = s_o[cntr];
+        for (uint32_t c = ((s_o[0] + chunk - 1) >> sh) + threadIdx.x; c << sh < oend; c += GFR_BLOCK)
+            q.part[c] = (int32_t)(slot0 + r0) + upper_index(s_o, 0, (int)cntr - 1, c << sh);
         __syncthreads();
     }
     // clear this group's slot of the other parity for the next launch

@@ -408,3 +408,43 @@ def test_results_are_complete_on_return(ctx):
     for t in ts:
         t.join()
     assert not bad
+
+
+def _hubs(rows, tail=0):
+    """Vertex 0 beside hubs 1..len(rows), hub i beside its own rows[i] - 1 leaves, `tail` vertices after
+    them in a chain that starts at the last leaf."""
+    k, first = len(rows), len(rows) + 1
+    eu, ev = [np.zeros(k, np.int64)], [np.arange(1, k + 1)]
+    for i, r in enumerate(rows):
+        eu.append(np.full(r - 1, i + 1))
+        ev.append(np.arange(first, first + r - 1))
+        first += r - 1
+    eu.append(np.arange(first - 1, first - 1 + tail))
+    ev.append(np.arange(first, first + tail))
+    return graphgen.from_edges(first + tail, np.concatenate(eu).astype(np.int32), np.concatenate(ev).astype(np.int32))
+
+
+# one word a thread up to 2^22 vertices on 256 CUs, several past it; rows at the chunk size, many chunks a thread
+QUEUES = {
+    "chunk rows": lambda: _hubs([1024, 1, 1023, 1, 1025, 2, 2048, 1024] * 9, 40),
+    "neighbouring hubs": lambda: _hubs([9000] * 64, 40),
+    "word ends": lambda: _hubs([2] * 2047, 33),
+    "one word a thread": lambda: _hubs([1 << 21, (1 << 21) - 4], 3),
+    "two words a thread": lambda: _hubs([1 << 21, (1 << 21) + 60], 3),
+}
+
+
+@pytest.mark.parametrize("name", list(QUEUES))
+def test_queues_at_chunk_and_word_edges(ctx, name):
+    row, col = QUEUES[name]()
+    g = ctx.graph_load_csr(row, col)
+    n = row.size - 1
+    ctx.set_option("bfs.frontier", 1)
+    ctx.set_option("bfs.direction", 1)
+    try:
+        for src in (0, 1, n - 1):
+            assert np.array_equal(_host(ctx.bfs(g, src)), oracle.bfs(row, col, src))
+    finally:
+        ctx.set_option("bfs.frontier", 0)
+        ctx.set_option("bfs.direction", 0)
+        g.free()

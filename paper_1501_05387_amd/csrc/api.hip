@@ -787,6 +787,7 @@ gfr_status gfr_graph_load_csr(gfr_ctx *ctx, int32_t n, int64_t m, const int32_t 
         g->max_deg = md;
         g->cls = classify_graph(n, m, md);
         build_full_queue(c, *g, R);
+        likely_neighbours(c, *g, c.stream);
         GFR_HIP(hipStreamSynchronize(c.stream));
         const int64_t h = c.next_handle++;
         {

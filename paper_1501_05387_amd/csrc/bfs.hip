@@ -13,7 +13,8 @@
 //               (With bfs.dedup = 0 the neighbour is first claimed with an
 //               atomicOr on the visited bitmap, the non-idempotent form.)
 //               Pull: every unvisited vertex scans its list until it meets a
-//               vertex of the current frontier bitmap.
+//               vertex of the current frontier bitmap; a lane takes the first
+//               entries of its vertex, then quarter waves the long lists left.
 //               Either way the new frontier is a byte array of marks.
 //   compact     the filter: the marks become the next queue in vertex order
 //               and the next frontier bitmap, visited is updated (compact.h),
@@ -72,6 +73,7 @@ struct BfsArgs {
     uint32_t *fb;         // current frontier bitmap (written by the compaction)
     uint8_t *mark;        // next-frontier marks, one byte per vertex
     FrontierQ q;
+    const int32_t *likely;   // first neighbour to probe in a pull level (-1: no edges), or null
     uint32_t *part_insp;   // per work-group edges inspected by a pull level
     BfsCtl *ctl;
     uint32_t mapping;        // push work mapping: 0 by frontier size, 1 edge chunks, 2 per-vertex groups
@@ -161,6 +163,69 @@ __device__ void bfs_push_twc(const BfsArgs &a, const FrontierQ &q, uint32_t nf, 
     }
 }
 
+// What holds a pull level up is the line of C, somewhere in memory, that each
+// unvisited vertex reads only to find that one of its first neighbours is in the
+// frontier, and the lane that scans a list of hundreds by itself.  On scale-free
+// graphs the neighbour of the largest degree is in the frontier more often than
+// any other, so its id is kept in an array of its own, made when the graph is
+// loaded and read in order: on R-MAT with 524,288 vertices and 15.5 M entries,
+// at the level that finds 68 % of the unvisited vertices with edges, it is a
+// frontier vertex for 62 %, the first of the list for 50 %.  Lists that a lane
+// has not settled after PULL_STEPS steps go to quarter waves.  R-MAT with 4 M
+// vertices, the three pull levels: 112, 27 and 14 us as it was, 87, 27 and 14
+// with the quarter waves, 63, 19 and 12 with the array as well, 61, 17 and 10
+// with the next vertices' words fetched ahead.  (The first LK_MAX neighbours are
+// looked at: hubs are hardly ever unvisited by then.)
+constexpr int LK_LANES = 16, LK_MAX = 64;
+constexpr int PULL_STEPS = 2;   // of 4 probes (1 and 3: the fat level 64 and 63 us, 61 with 2)
+// Below 8 M entries C is in the L2s, and the calls are no faster with the array
+// (524,288 vertices and 4 M entries 156 / 157 us; 2 M and 63 M 199 / 190).
+constexpr int64_t LK_MIN_EDGES = 1 << 23;
+
+__global__ __launch_bounds__(GFR_BLOCK) void likely_kernel(const int32_t *R, const int32_t *C, int32_t n,
+                                                           int32_t *likely)
+{
+    const int32_t lane = (int32_t)(threadIdx.x % LK_LANES);
+    const uint32_t groups = gridDim.x * (GFR_BLOCK / LK_LANES);
+    for (uint32_t v = (blockIdx.x * GFR_BLOCK + threadIdx.x) / LK_LANES; v < (uint32_t)n; v += groups) {
+        const int32_t r0 = R[v], r1 = min(R[v + 1], r0 + LK_MAX);
+        int32_t deg = 0, best = -1;
+        for (int32_t e = r0 + lane; e < r1; e += LK_LANES) {
+            const int32_t u = C[e], d = R[u + 1] - R[u];
+            if (d > deg) {
+                deg = d;
+                best = u;
+            }
+        }
+#pragma unroll
+        for (int k = LK_LANES / 2; k >= 1; k >>= 1) {
+            const int32_t od = __shfl_xor(deg, k, LK_LANES), ob = __shfl_xor(best, k, LK_LANES);
+            if (od > deg) {
+                deg = od;
+                best = ob;
+            }
+        }
+        // a directed edge may lead to a vertex without edges: any neighbour does then
+        if (lane == 0) likely[v] = best >= 0 || r1 == r0 ? best : C[r0];
+    }
+}
+
+void likely_neighbours(Ctx &c, Graph &g, hipStream_t s)
+{
+    if (g.cls == GRAPH_MESH || g.m < LK_MIN_EDGES) return;
+    try {
+        g.likely.alloc(4ull * g.n);
+    } catch (const Error &e) {
+        if (e.code != GFR_E_OOM) throw;
+        (void)hipGetLastError();   // the levels then read the lists
+        return;
+    }
+    g.bytes += g.likely.bytes;
+    hipLaunchKernelGGL(likely_kernel, dim3(grid_blocks(c, 8)), dim3(GFR_BLOCK), 0, s, g.R.as<int32_t>(),
+                       g.C.as<int32_t>(), g.n, g.likely.as<int32_t>());
+    GFR_LAUNCH_CHECK();
+}
+
 template <int CH>
 __global__ __launch_bounds__(GFR_BLOCK) void bfs_level(BfsArgs a)
 {
@@ -228,31 +293,68 @@ __global__ __launch_bounds__(GFR_BLOCK) void bfs_level(BfsArgs a)
         const uint32_t waves = gridDim.x * GFR_WAVES;
         const int lane = lane_id();
         uint32_t insp = 0;
-        for (uint32_t grp = blockIdx.x * GFR_WAVES + threadIdx.x / 64; grp * 64u < (uint32_t)a.n;
-             grp += waves) {
+        // (the next 64 vertices' words, offsets and likely neighbours are
+        // fetched beside these ones' probes)
+        const uint32_t end = ((uint32_t)a.n + 63u) / 64u;
+        uint32_t grp = blockIdx.x * GFR_WAVES + threadIdx.x / 64;
+        uint32_t visw_n = 0;
+        int32_t u_n = 0, e_n = 0, re_n = 0;
+        const auto fetch = [&](uint32_t gr) {
+            if (gr >= end) return;
+            const uint32_t x = min(gr * 64u + (uint32_t)lane, (uint32_t)a.n - 1u);
+            visw_n = a.vis[gr * 2u + (uint32_t)(lane >> 5)];
+            u_n = a.likely ? a.likely[x] : 0;
+            e_n = a.R[x];
+            re_n = a.R[x + 1u];
+        };
+        fetch(grp);
+        for (; grp < end; grp += waves) {
             const int32_t v = (int32_t)(grp * 64u) + lane;
-            const uint32_t word = grp * 2u + (uint32_t)(lane >> 5);
-            const uint32_t visw = a.vis[word];
+            const bool open = v < a.n && !(visw_n & (1u << (v & 31)));
+            const int32_t u = u_n;
+            int32_t e = open ? e_n : 0, re = open ? re_n : 0;
+            fetch(grp + waves);
             bool found = false;
-            if (v < a.n && !(visw & (1u << (v & 31)))) {
-                int32_t e = a.R[v];
-                const int32_t re = a.R[v + 1];
-                // four independent neighbour probes per step
-                while (e < re) {
-                    const int32_t k = min(4, re - e);
-                    int32_t u[4];
+            if (a.likely && e < re) {
+                ++insp;
+                found = (a.fb[u >> 5] >> (u & 31)) & 1u;
+            }
+            // a lane's first entries, four independent probes per step
+            for (int step = 0; step < PULL_STEPS && e < re && !found; ++step) {
+                const int32_t k = min(4, re - e);
+                int32_t u[4];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) u[j] = a.C[j < k ? e + j : e];
-                    uint32_t hit = 0;
+                for (int j = 0; j < 4; ++j) u[j] = a.C[j < k ? e + j : e];
+                uint32_t hit = 0;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) hit |= (j < k) ? (a.fb[u[j] >> 5] >> (u[j] & 31)) & 1u : 0u;
-                    insp += (uint32_t)k;
-                    if (hit) {
-                        found = true;
-                        break;
-                    }
-                    e += 4;
+                for (int j = 0; j < 4; ++j) hit |= (j < k) ? (a.fb[u[j] >> 5] >> (u[j] & 31)) & 1u : 0u;
+                insp += (uint32_t)k;
+                found = hit != 0;
+                e += 4;
+            }
+            // the rest of the long lists, four at a time by a quarter of the wave each
+            uint64_t todo = ballot(e < re && !found);
+            while (todo) {
+                uint64_t mine = todo;
+                for (int j = 0; j < lane / 16; ++j) mine &= mine - 1;
+                const int owner = mine ? __ffsll((unsigned long long)mine) - 1 : 0;
+                int32_t p = __shfl(e, owner, 64), end = __shfl(re, owner, 64);   // (the owner may sit in any quarter)
+                if (!mine) end = p;
+                bool hit = false;
+                while (p < end && !hit) {
+                    const int32_t i0 = p + lane % 16, i1 = i0 + 16;
+                    const int32_t u0 = a.C[min(i0, end - 1)], u1 = a.C[min(i1, end - 1)];
+                    const uint32_t f0 = a.fb[u0 >> 5] >> (u0 & 31), f1 = a.fb[u1 >> 5] >> (u1 & 31);
+                    hit = ((ballot((f0 | f1) & 1u) >> (lane & 48)) & 0xFFFFull) != 0;
+                    if (lane % 16 == 0) insp += (uint32_t)min(32, end - p);
+                    p += 32;
                 }
+                const uint64_t hits = ballot(hit);
+                if ((todo >> lane) & 1ull) {
+                    const int rank = __popcll(todo & ((1ull << lane) - 1ull));
+                    if (rank < 4) found = (hits >> (16 * rank)) & 1ull;
+                }
+                for (int j = 0; j < 4; ++j) todo &= todo - 1;
             }
             if (found) {
                 a.depth[v] = L + 1;
@@ -832,6 +934,7 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena
     a.q.off = ar.take<uint32_t>(n);
     a.q.row = ar.take<int32_t>(n);
     a.q.part = ar.take<int32_t>(nparts);
+    a.likely = g.likely.as<int32_t>();
     a.part_insp = ar.take<uint32_t>(G);
     a.mapping = (uint32_t)c.opt.advance_mapping;
     a.twc_threshold = (uint32_t)c.opt.twc_threshold;

@@ -135,6 +135,7 @@ struct Graph {
     int32_t full_nf = 0;
     int32_t n_isolated = 0;
     RankedCols ranked;
+    DevMem likely;   // [n] each vertex's neighbour a pull level probes first (likely_neighbours), or none
     int32_t bip_checked_nl = -1;   // last side split verified for the bipartite rankings
     // hints for the speculative level loops (the size of the first batch of
     // launches), one per solver (a 64-source traversal takes more levels than
@@ -398,6 +399,7 @@ int grid_blocks(const Ctx &c, int per_cu = 4);
 int resident_grid(const Ctx &c, const void *kernel, int per_cu);
 
 // Solvers (outputs are device pointers on the context's device).
+void likely_neighbours(Ctx &c, Graph &g, hipStream_t s);
 void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s);
 // the same with its scratch carved from `ar` (the context's arena, or fixed memory)
 void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena &ar);

@@ -448,3 +448,33 @@ def test_queues_at_chunk_and_word_edges(ctx, name):
         ctx.set_option("bfs.frontier", 0)
         ctx.set_option("bfs.direction", 0)
         g.free()
+
+
+@pytest.mark.parametrize("array", [False, True], ids=["lists", "likely neighbours"])
+@pytest.mark.parametrize("last", [True, False], ids=["hit at the end", "hit first"])
+def test_pull_list_lengths(ctx, last, array):
+    """Lists around the lane's and the quarter wave's steps, whole waves of them and mixed, found at level 2
+    through their one frontier neighbour."""
+    kinds = [1, 2, 3, 4, 5, 7, 8, 9, 10, 39, 40, 41, 72, 73, 300]
+    lens = np.concatenate([np.repeat(k, 64) for k in kinds] + [np.tile(kinds, 9)])
+    leaves, w = int((lens - 1).sum()), lens.size
+    own = np.repeat(np.arange(w), lens - 1)
+    if last:      # leaves, the vertices, their common neighbour x, the source
+        w0, x, src, l0 = leaves, leaves + w, leaves + w + 1, 0
+    else:         # the source, x, the vertices, leaves
+        w0, x, src, l0 = 2, 1, 0, 2 + w
+    eu = np.concatenate([w0 + own, w0 + np.arange(w), [x]])
+    ev = np.concatenate([l0 + np.arange(leaves), np.full(w, x), [src]])
+    row, col = graphgen.from_edges(leaves + w + 2, eu.astype(np.int32), ev.astype(np.int32))
+    if array:     # enough entries beside them that the array is made
+        row, col = _union((row, col), _hubs([1 << 21, (1 << 21) + 60], 3))
+    g = ctx.graph_load_csr(row, col)
+    ctx.set_option("bfs.frontier", 1)
+    ctx.set_option("bfs.direction", 2)
+    try:
+        for s in (src, l0, w0 + w - 1):
+            assert np.array_equal(_host(ctx.bfs(g, int(s))), oracle.bfs(row, col, int(s)))
+    finally:
+        ctx.set_option("bfs.frontier", 0)
+        ctx.set_option("bfs.direction", 0)
+        g.free()

@@ -263,6 +263,33 @@ template <class M> __device__ __forceinline__ auto placed(const M &m, const Fron
 }
 template <class M> __device__ __forceinline__ FrontierQ placed(const M &, const FrontierQ &q, long) { return q; }
 
+// For every chunk from c0 on that starts among the staged entries (their edge
+// offsets o[0 .. cnt), o[cnt] the end), the entry that holds its first edge.  A
+// lane searches for K chunks at once, as a search is a chain of LDS reads and
+// the group with R-MAT's hubs has tens of them per lane (one at a time, the
+// fattest compaction of a BFS on 4 M vertices takes 44 us, four at a time 34;
+// with at most one chunk per lane the other searches only cost: 20 and 22 us).
+// Offsets stay below 2^31, so the chunks' first edges fit.
+template <int K>
+__device__ __forceinline__ void chunk_starts(const uint32_t *o, uint32_t cnt, uint32_t c0, uint32_t sh, int32_t *part,
+                                             uint32_t slot)
+{
+    const uint32_t end = o[cnt];
+    for (uint32_t c = c0 + threadIdx.x; c << sh < end; c += K * GFR_BLOCK) {
+        uint32_t at[K] = {};
+#pragma unroll
+        for (uint32_t st = COMPACT_STAGE / 2; st; st >>= 1)
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                const uint32_t i = min(at[j] + st, cnt);
+                if (o[i] <= min((c + j * GFR_BLOCK) << sh, end - 1u)) at[j] = i;
+            }
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            if ((c + j * GFR_BLOCK) << sh < end) part[c + j * GFR_BLOCK] = (int32_t)(slot + at[j]);
+    }
+}
+
 // Compaction kernel.  M: functor with
 //     bool skip() const                  whole launch is a no-op (uniform)
 //     uint32_t mask(uint32_t w)          marks of vertices 32w..32w+31 (may consume / update state)
@@ -319,7 +346,7 @@ __global__ __launch_bounds__(GFR_BLOCK) void compact_kernel(const int32_t *R, in
     // 32 of them would write thousands of chunk starts by itself.  BFS of R-MAT
     // with 4 M vertices, the three fattest compactions: 36, 59 and 29 us when the
     // owners wrote their entries' chunks and the degrees were loaded again here,
-    // 23, 56 and 19 from the offsets in LDS, 12, 44 and 21 so.
+    // 23, 56 and 19 from the offsets in LDS, 12, 33 and 21 so.
     __shared__ int32_t s_v[COMPACT_STAGE], s_row[COMPACT_STAGE];
     __shared__ uint32_t s_o[COMPACT_STAGE + 1];   // and the end of the last entry
     __shared__ uint32_t s_e[GFR_WAVES];
@@ -406,10 +433,9 @@ __global__ __launch_bounds__(GFR_BLOCK) void compact_kernel(const int32_t *R, in
             q.off[slot] = s_o[j];
             q.row[slot] = s_row[j];
         }
-        // edge offsets stay below 2^31, so chunk numbers and their first edges fit
-        const uint32_t oend = s_o[cntr];
-        for (uint32_t c = ((s_o[0] + chunk - 1) >> sh) + threadIdx.x; c << sh < oend; c += GFR_BLOCK)
-            q.part[c] = (int32_t)(slot0 + r0) + upper_index(s_o, 0, (int)cntr - 1, c << sh);
+        const uint32_t c0 = (s_o[0] + chunk - 1) >> sh;
+        if ((c0 + GFR_BLOCK) << sh < s_o[cntr]) chunk_starts<4>(s_o, cntr, c0, sh, q.part, slot0 + r0);
+        else chunk_starts<1>(s_o, cntr, c0, sh, q.part, slot0 + r0);
         __syncthreads();
     }
     // clear this group's slot of the other parity for the next launch

@@ -557,14 +557,19 @@ __device__ __forceinline__ void arrive(uint32_t *pinned, uint32_t k)
 // Spin on a device word until the speculative level loop reports completion.
 // Launches `launch()` batches and reads `bytes` at flag_dev (the control block,
 // whose first word is the flag) back to c.pinned after each batch; they are
-// there when it returns.
+// there when it returns.  `output()` is launched before each read-back, for
+// kernels that write the results once the flag says so and return otherwise:
+// launched after the read-back they would start 20 us after the last level.
 // With a step key (and option "graph.steps" on, per-launch timing off), each
 // batch of k steps is replayed from a hipGraph captured the first time that
 // key and k were seen; a capture that fails falls back to direct launches.
-template <class LaunchFn>
+struct NoOutput {
+    void operator()() const {}
+};
+template <class LaunchFn, class OutputFn = NoOutput>
 int32_t run_until_done(Ctx &c, const uint32_t *flag_dev, uint32_t done_value, int32_t first_batch,
                        int64_t max_launches, hipStream_t s, LaunchFn launch, size_t bytes,
-                       const StepKey *key = nullptr)
+                       const StepKey *key = nullptr, OutputFn output = OutputFn())
 {
     int64_t launched = 0;
     int32_t batch = first_batch < 1 ? 1 : first_batch;
@@ -593,6 +598,7 @@ int32_t run_until_done(Ctx &c, const uint32_t *flag_dev, uint32_t done_value, in
         } else {
             for (int32_t i = 0; i < batch; ++i) launch();
         }
+        output();
         GFR_LAUNCH_CHECK();
         launched += batch;
         read_back(c, flag_dev, bytes, s);

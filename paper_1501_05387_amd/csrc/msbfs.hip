@@ -267,6 +267,7 @@ __device__ __forceinline__ int32_t ms_depth_of(const unsigned long long *plane, 
 
 __global__ __launch_bounds__(GFR_BLOCK) void msbfs_output(MsArgs a)
 {
+    if (a.ctl->dir != MS_DONE) return;
     // depths 0 .. level were recorded (the last record is the empty frontier)
     const int32_t nlev = min(MS_LVL_CAP, a.ctl->level + 1);
     const int32_t kq = a.k;
@@ -413,7 +414,6 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
         for (int32_t i = 0; i < k; ++i) run_bfs(c, g, sources[i], depth + (size_t)i * n, s);
         return;
     }
-    c.waited = false;   // (the output kernel)
     const uint32_t chunk = 1024;
     const uint32_t nwords = (uint32_t)(((int64_t)n + 63) / 64) * 2u;
     const size_t nparts = (size_t)(g.m / chunk) + 2;
@@ -479,12 +479,13 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
         };
         StepKey key("msbfs");
         key.add(a).add(G).add(cg).add(chunk).add(status);
+        const auto output = [&]() {
+            c.ktimer.run("msbfs_output", s, [&]() {
+                hipLaunchKernelGGL(msbfs_output, dim3(grid_blocks(c, 8)), dim3(GFR_BLOCK), 0, s, a);
+            });
+        };
         run_until_done(c, &a.ctl->dir, MS_DONE, g.msbfs_levels_hint.load(std::memory_order_relaxed) + 2,
-                       (int64_t)n + 8, s, launch, sizeof(MsCtl), &key);
-        c.ktimer.run("msbfs_output", s, [&]() {
-            hipLaunchKernelGGL(msbfs_output, dim3(grid_blocks(c, 8)), dim3(GFR_BLOCK), 0, s, a);
-        });
-        GFR_LAUNCH_CHECK();
+                       (int64_t)n + 8, s, launch, sizeof(MsCtl), &key, output);
         MsCtl h;
         memcpy(&h, c.pinned, sizeof(MsCtl));
         if (h.err) fail(GFR_E_DEVICE, "bfs_batch: frontier compaction look-back timed out");
@@ -493,6 +494,7 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
         pull_levels += (double)h.pull_levels;
         push_edges += (double)h.push_edges;
     }
+    c.waited = true;
     c.stats.v["levels"] += levels;
     c.stats.v["pull_levels"] += pull_levels;
     c.stats.v["push_edges"] += push_edges;

@@ -215,6 +215,7 @@ __global__ __launch_bounds__(GFR_BLOCK) void prk_output(FrontierQ full, uint32_t
 {
     const float *x = (ctl->pr.iters & 1) ? xb : xa;
     const float iso = ctl->iso;
+    if (!ctl->pr.done) return;
     const uint32_t stride = gridDim.x * GFR_BLOCK, i0 = blockIdx.x * GFR_BLOCK + threadIdx.x;
     for (uint32_t i = i0; i < nf; i += stride) rank[full.v[i]] = x[i];
     if (ctl->n_iso)
@@ -269,9 +270,11 @@ static void run_pagerank_ranked(Ctx &c, Graph &g, const RankedCols &rk, float da
         hipLaunchKernelGGL(prk_reduce, dim3(1), block, 0, s, part, (uint32_t)G, g.n, ctl);
     };
     const int32_t first = max_iter < 8 ? max_iter : 8;
-    run_until_done(c, done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h);
-    hipLaunchKernelGGL(prk_output, grid, block, 0, s, g.full, nf, g.R.as<int32_t>(), g.n, xa, xb, ctl, rank);
-    GFR_LAUNCH_CHECK();
+    const auto output = [&]() {
+        hipLaunchKernelGGL(prk_output, grid, block, 0, s, g.full, nf, g.R.as<int32_t>(), g.n, xa, xb, ctl, rank);
+    };
+    run_until_done(c, done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h, nullptr, output);
+    c.waited = true;
     memcpy(&h, c.pinned, sizeof h);
     *iters = (int32_t)h.pr.iters;
     *l1 = h.pr.l1;

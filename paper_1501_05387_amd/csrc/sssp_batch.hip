@@ -1223,12 +1223,14 @@ __global__ void bsssp_init(BsArgs a, Sources64 src, int32_t k, uint32_t delta, f
 }
 
 // out[q][v] = D[v][q] for the queries q in `lanes`: 64 vertices x WIDTH queries
-// per tile through LDS (narrow rows widened, unreached -> 0xFFFFFFFF)
+// per tile through LDS (narrow rows widened, unreached -> 0xFFFFFFFF).  With
+// `mode`, only when the traversal has ended.
 template <int BITS, int WIDTH = 64>
 __global__ __launch_bounds__(GFR_BLOCK) void bsssp_transpose(BsArgs a, int32_t n, unsigned long long lanes,
-                                                             uint32_t *out)
+                                                             uint32_t *out, const uint32_t *mode)
 {
     __shared__ uint32_t tile[64][65];
+    if (mode && *mode != BS_DONE) return;
     const int32_t ntiles = (n + 63) / 64;
     for (int32_t tb = blockIdx.x; tb < ntiles; tb += gridDim.x) {
         const int32_t v0 = tb * 64;
@@ -1429,17 +1431,17 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
             };
             StepKey key("bsssp");
             key.add(a).add(G).add(Gw).add(cg).add(chunk).add(status).add(bits).add(pair).add(pull_alpha);
-            run_until_done(c, &a.ctl->mode, BS_DONE, g.bsssp_iter_hint.load(std::memory_order_relaxed) + 1,
-                           64ll * n + 1024, s, launch, sizeof(BsCtl), &key);
-            if (bits == 32) {   // no fallback can follow (a failed batch fails the call)
+            const auto output = [&]() {
+                if (bits != 32) return;   // a fallback may follow (a failed batch of 32-bit rows fails the call)
                 if (half)
                     hipLaunchKernelGGL((bsssp_transpose<32, 32>), dim3(G), dim3(GFR_BLOCK), 0, s, a, n, lanes_mask,
-                                       dist + (size_t)g0 * n);
+                                       dist + (size_t)g0 * n, &a.ctl->mode);
                 else
                     hipLaunchKernelGGL(bsssp_transpose<32>, dim3(G), dim3(GFR_BLOCK), 0, s, a, n, lanes_mask,
-                                       dist + (size_t)g0 * n);
-                GFR_LAUNCH_CHECK();
-            }
+                                       dist + (size_t)g0 * n, &a.ctl->mode);
+            };
+            run_until_done(c, &a.ctl->mode, BS_DONE, g.bsssp_iter_hint.load(std::memory_order_relaxed) + 1,
+                           64ll * n + 1024, s, launch, sizeof(BsCtl), &key, output);
             memcpy(&h, c.pinned, sizeof(BsCtl));
             if (h.err) fail(GFR_E_DEVICE, "sssp_batch: frontier compaction look-back timed out");
             g.bsssp_iter_hint.store((int32_t)h.iter, std::memory_order_relaxed);
@@ -1466,10 +1468,10 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
         }
         if (bits == 8)
             hipLaunchKernelGGL(bsssp_transpose<8>, dim3(G), dim3(GFR_BLOCK), 0, s, a, n, lanes_mask,
-                               dist + (size_t)g0 * n);
+                               dist + (size_t)g0 * n, nullptr);
         else if (bits == 16)
             hipLaunchKernelGGL(bsssp_transpose<16>, dim3(G), dim3(GFR_BLOCK), 0, s, a, n, lanes_mask,
-                               dist + (size_t)g0 * n);
+                               dist + (size_t)g0 * n, nullptr);
         GFR_LAUNCH_CHECK();
         batches8 += bits == 8 ? 1 : 0;
         batches16 += bits == 16 ? 1 : 0;
@@ -1480,6 +1482,7 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
         lanes += (double)h.lane_relaxed;
         pairs += (double)h.pair_entries;
     }
+    c.waited = bits == 32;   // (narrow rows are written out after the read-back)
     c.stats.v["narrow_batches"] += batches8 + batches16;   // batches finished with 8- or 16-bit rows
     c.stats.v["batches_8bit"] += batches8;
     c.stats.v["batches_16bit"] += batches16;
@@ -1697,7 +1700,7 @@ struct BsSession final : LaneSession {
     {
         if (!lanes) return;
         hipLaunchKernelGGL(bsssp_transpose<32>, dim3(G), dim3(GFR_BLOCK), 0, stream, a, a.n, lanes,
-                           (uint32_t *)stage);
+                           (uint32_t *)stage, nullptr);
         GFR_LAUNCH_CHECK();
     }
 };

@@ -478,3 +478,22 @@ def test_pull_list_lengths(ctx, last, array):
         ctx.set_option("bfs.frontier", 0)
         ctx.set_option("bfs.direction", 0)
         g.free()
+
+
+def test_outputs_queued_before_the_end_is_known(ctx):
+    """A solve longer than the launches queued at first: the output kernels run again once it has ended."""
+    row, col = graphgen.grid(60)          # 119 levels, after a star's two
+    w = graphgen.weights(row, col, 64)
+    star, scol = graphgen.from_edges(70, np.zeros(69, np.int32), np.arange(1, 70, dtype=np.int32))
+    row, col = _union((star, scol), (row, col))
+    w = np.concatenate([np.ones(scol.size, np.uint32), w])
+    g = ctx.graph_load_csr(row, col, w)
+    for first in (0, 100):                # sources in the star, then in the lattice
+        src = (np.arange(30, dtype=np.int32) + first)
+        for _ in range(2):
+            b = _host(ctx.bfs_batch(g, src)).reshape(30, -1)
+            d = _host(ctx.sssp_batch(g, src)).view(np.uint32).reshape(30, -1)
+            for i in (0, 13, 29):
+                assert np.array_equal(b[i], oracle.bfs(row, col, int(src[i])))
+                assert np.array_equal(d[i], oracle.sssp(row, col, w, int(src[i])))
+    g.free()

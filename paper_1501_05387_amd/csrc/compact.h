@@ -73,15 +73,20 @@ __device__ __forceinline__ void clear_marks(uint8_t *p)
     *(uint4 *)(p + 16) = make_uint4(0, 0, 0, 0);
 }
 
-__device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long long x)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void scan_step_u64(unsigned long long &x)
 {
-    const int l = lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t lo = (uint32_t)__shfl_up((int)(uint32_t)x, d, 64);
-        const uint32_t hi = (uint32_t)__shfl_up((int)(uint32_t)(x >> 32), d, 64);
-        if (l >= d) x += ((unsigned long long)hi << 32) | lo;
-    }
+    x += (unsigned long long)dpp_u32<CTRL, ROWS>((uint32_t)(x >> 32)) << 32 | dpp_u32<CTRL, ROWS>((uint32_t)x);
+}
+
+__device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long long x)   // as wave_incl_scan
+{
+    scan_step_u64<0x111, 0xF>(x);
+    scan_step_u64<0x112, 0xF>(x);
+    scan_step_u64<0x114, 0xF>(x);
+    scan_step_u64<0x118, 0xF>(x);
+    scan_step_u64<0x142, 0xA>(x);
+    scan_step_u64<0x143, 0xC>(x);
     return x;
 }
 

@@ -31,6 +31,36 @@ struct GatherScratch {
     double *plast;    // per chunk: partial of the entry starting in it and continuing out
 };
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double x)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint64_t lo = dpp_u32<CTRL, ROWS>((uint32_t)b), hi = dpp_u32<CTRL, ROWS>((uint32_t)(b >> 32));
+    return __longlong_as_double((long long)(hi << 32 | lo));
+}
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void seg_scan_step(double &open, uint32_t &any)
+{
+    const double o = dpp_f64<CTRL, ROWS>(open);
+    const uint32_t oa = dpp_u32<CTRL, ROWS>(any);
+    open = any ? open : o + open;
+    any |= oa;
+}
+
+// open: sum of what each lane holds of the list open at its end; any: a list
+// starts in the lane.  Afterwards open reaches back to the list's start or the
+// wave's, and any says which.
+__device__ __forceinline__ void seg_scan(double &open, uint32_t &any)
+{
+    seg_scan_step<0x111, 0xF>(open, any);   // row_shr:1, :2, :4, :8
+    seg_scan_step<0x112, 0xF>(open, any);
+    seg_scan_step<0x114, 0xF>(open, any);
+    seg_scan_step<0x118, 0xF>(open, any);
+    seg_scan_step<0x142, 0xA>(open, any);   // row_bcast:15 into rows 1 and 3
+    seg_scan_step<0x143, 0xC>(open, any);   // row_bcast:31 into rows 2 and 3
+}
+
 template <int CH, class Op, class Fin>
 __global__ __launch_bounds__(GFR_BLOCK) void gather_chunks(FrontierQ q, const uint32_t *nf_p,
                                                            const uint32_t *mf_p, const int32_t *C,
@@ -107,21 +137,9 @@ __global__ __launch_bounds__(GFR_BLOCK) void gather_chunks(FrontierQ q, const ui
         // sum of the list open at each lane's end, back to its start or the wave's
         double open = acc;
         uint32_t any = has;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const double o = __shfl_up(open, d, 64);
-            const uint32_t oa = (uint32_t)__shfl_up((int)any, d, 64);
-            if (lane >= d && !any) {
-                open = o + open;
-                any = oa;
-            }
-        }
-        double in = __shfl_up(open, 1, 64);
-        uint32_t in_any = (uint32_t)__shfl_up((int)any, 1, 64);
-        if (lane == 0) {
-            in = 0.0;
-            in_any = 0;
-        }
+        seg_scan(open, any);
+        const double in = dpp_f64<0x138, 0xF>(open);   // wave_shr:1
+        const uint32_t in_any = dpp_u32<0x138, 0xF>(any);
         if (lane == 63) {
             s_carry[wave] = open;
             s_has[wave] = any;

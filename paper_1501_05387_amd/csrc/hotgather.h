@@ -44,43 +44,6 @@ struct HotGraph {
     uint32_t nf, mf, nch;
 };
 
-// x of another lane by DPP (no trip through LDS); 0 where there is none.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t x)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
-}
-
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_f64(double x)
-{
-    const uint64_t b = (uint64_t)__double_as_longlong(x);
-    const uint64_t lo = dpp_u32<CTRL, ROWS>((uint32_t)b), hi = dpp_u32<CTRL, ROWS>((uint32_t)(b >> 32));
-    return __longlong_as_double((long long)(hi << 32 | lo));
-}
-
-template <int CTRL, int ROWS>
-__device__ __forceinline__ void seg_scan_step(double &open, uint32_t &any)
-{
-    const double o = dpp_f64<CTRL, ROWS>(open);
-    const uint32_t oa = dpp_u32<CTRL, ROWS>(any);
-    open = any ? open : o + open;
-    any |= oa;
-}
-
-// open: sum of what each lane holds of the list open at its end; any: a list
-// starts in the lane.  Afterwards open reaches back to the list's start or the
-// wave's, and any says which.
-__device__ __forceinline__ void seg_scan(double &open, uint32_t &any)
-{
-    seg_scan_step<0x111, 0xF>(open, any);   // row_shr:1, :2, :4, :8
-    seg_scan_step<0x112, 0xF>(open, any);
-    seg_scan_step<0x114, 0xF>(open, any);
-    seg_scan_step<0x118, 0xF>(open, any);
-    seg_scan_step<0x142, 0xA>(open, any);   // row_bcast:15 into rows 1 and 3
-    seg_scan_step<0x143, 0xC>(open, any);   // row_bcast:31 into rows 2 and 3
-}
-
 template <class T>
 __global__ __launch_bounds__(HG_BLOCK) void gather_hot(HotGraph g, const T *table, double *sum, GatherScratch gs,
                                                        const uint32_t *stop)

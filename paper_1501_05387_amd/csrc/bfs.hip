@@ -861,7 +861,9 @@ __global__ __launch_bounds__(BS_BLOCK) void bfs_small(BsmArgs a, int32_t src)
 // Where one work-group is faster than the chip.  Per call, R-MAT with 4 or 16
 // edges drawn per vertex: 8,192 vertices and 57 K entries 103 us (125 by level
 // launches), 4,096 and 110 K 97 (118); beyond the line, 16,384 and 116 K 171
-// (128), 8,192 and 220 K 166 (120).  Rows of at most 16 entries (lattices) take
+// (128), 8,192 and 220 K 166 (120).  With the waits and compactions of today
+// 8,192 and 59 K 93 (103), 4,096 and 97 K 85 (89), and the level launches 114
+// and 100 beyond the line.  Rows of at most 16 entries (lattices) take
 // a thread each, and any number of them that fits the list: 33^2, 100^2 and
 // 181^2 81, 130 and 248 us (303, 441 and 656 before).
 static bool bfs_small_fits(const Ctx &c, const Graph &g)

@@ -103,20 +103,12 @@ void fill_u32(void *p, uint32_t value, size_t count, hipStream_t s)
     GFR_LAUNCH_CHECK();
 }
 
-__global__ void k_fill_many(Fills f)
-{
-    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
-    for (int k = 0; k < f.n; ++k)
-        for (size_t i = i0; i < f.count[k]; i += stride) f.p[k][i] = f.value[k];
-}
+__global__ void k_fill_many(Fills f) { f.write(); }
 
 void Fills::run(hipStream_t s) const
 {
-    size_t most = 0;
-    for (int k = 0; k < n; ++k) most = std::max(most, count[k]);
-    if (most == 0) return;
-    const size_t blocks = std::min<size_t>((most + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_fill_many, dim3((unsigned)blocks), dim3(256), 0, s, *this);
+    if (blocks() == 0) return;
+    hipLaunchKernelGGL(k_fill_many, dim3(blocks()), dim3(256), 0, s, *this);
     GFR_LAUNCH_CHECK();
 }
 

@@ -435,36 +435,40 @@ struct BfsMarks {
     }
 };
 
-__global__ void bfs_init(BfsArgs a, int32_t src, uint32_t chunk, uint32_t force, uint32_t dedup, float alpha,
-                         float beta, unsigned long long m)
-{
-    const int32_t rs = a.R[src], deg = a.R[src + 1] - rs;
-    if (threadIdx.x == 0) {
-        BfsCtl *ctl = a.ctl;
-        a.depth[src] = 0;
-        a.vis[src >> 5] = 1u << (src & 31);
-        a.fb[src >> 5] = 1u << (src & 31);
-        a.q.v[0] = src;
-        a.q.off[0] = 0;
-        a.q.row[0] = rs;
-        ctl->mu = m - (unsigned long long)deg;
-        ctl->nf = 1;
-        ctl->mf = (uint32_t)deg;
-        ctl->level = 0;
-        ctl->nu = (uint32_t)a.n - 1u;
-        ctl->force = force;
-        ctl->dedup = dedup;
-        ctl->alpha = alpha;
-        ctl->beta = beta;
-        ctl->parity = 0;
-        ctl->err = 0;
-        ctl->push_levels = ctl->pull_levels = 0;
-        ctl->push_entries = ctl->push_edges = ctl->push_new = 0ull;
-        ctl->pull_unvisited = ctl->pull_inspected = ctl->pull_new = 0ull;
-        ctl->dir = deg == 0 ? DIR_DONE : (force == 2 ? DIR_PULL : DIR_PUSH);
+// the queue of the source alone, and the control block (one work-group)
+struct BfsFirst {
+    BfsArgs a;
+    int32_t src;
+    uint32_t chunk, force, dedup;
+    float alpha, beta;
+    unsigned long long m;
+    __device__ void operator()() const
+    {
+        const int32_t rs = a.R[src], deg = a.R[src + 1] - rs;
+        if (threadIdx.x == 0) {
+            BfsCtl *ctl = a.ctl;
+            a.q.v[0] = src;
+            a.q.off[0] = 0;
+            a.q.row[0] = rs;
+            ctl->mu = m - (unsigned long long)deg;
+            ctl->nf = 1;
+            ctl->mf = (uint32_t)deg;
+            ctl->level = 0;
+            ctl->nu = (uint32_t)a.n - 1u;
+            ctl->force = force;
+            ctl->dedup = dedup;
+            ctl->alpha = alpha;
+            ctl->beta = beta;
+            ctl->parity = 0;
+            ctl->err = 0;
+            ctl->push_levels = ctl->pull_levels = 0;
+            ctl->push_entries = ctl->push_edges = ctl->push_new = 0ull;
+            ctl->pull_unvisited = ctl->pull_inspected = ctl->pull_new = 0ull;
+            ctl->dir = deg == 0 ? DIR_DONE : (force == 2 ? DIR_PULL : DIR_PUSH);
+        }
+        for (uint32_t c = threadIdx.x; (uint64_t)c * chunk < (uint64_t)deg; c += blockDim.x) a.q.part[c] = 0;
     }
-    for (uint32_t c = threadIdx.x; (uint64_t)c * chunk < (uint64_t)deg; c += blockDim.x) a.q.part[c] = 0;
-}
+};
 
 // ------------------------------------------------------------ mark-byte levels
 // What bounds a level is its chain of dependent memory round trips (marks, row
@@ -943,17 +947,16 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena
     unsigned long long *status = ar.take<unsigned long long>(2ull * cg.blocks);
     a.ctl = ar.take<BfsCtl>(1);
 
-    Fills()
-        .add(depth, 0xFFFFFFFFu, (size_t)n)
-        .add(a.vis, 0u, nwords)
-        .add(a.fb, 0u, nwords)
-        .add(a.mark, 0u, 8ull * nwords)
-        .add(status, 0u, 4ull * cg.blocks)
-        .run(s);
-    hipLaunchKernelGGL(bfs_init, dim3(1), dim3(GFR_BLOCK), 0, s, a, src, chunk, (uint32_t)c.opt.bfs_direction,
-                       (uint32_t)c.opt.bfs_dedup, (float)c.opt.bfs_alpha, (float)c.opt.bfs_beta,
-                       (unsigned long long)g.m);
-    GFR_LAUNCH_CHECK();
+    const uint32_t bit = 1u << (src & 31);
+    fill_first(Fills()
+                   .add(depth, 0xFFFFFFFFu, (size_t)n).but((size_t)src, 0u)
+                   .add(a.vis, 0u, nwords).but((size_t)src >> 5, bit)
+                   .add(a.fb, 0u, nwords).but((size_t)src >> 5, bit)
+                   .add(a.mark, 0u, 8ull * nwords)
+                   .add(status, 0u, 4ull * cg.blocks),
+               BfsFirst{a, src, chunk, (uint32_t)c.opt.bfs_direction, (uint32_t)c.opt.bfs_dedup,
+                        (float)c.opt.bfs_alpha, (float)c.opt.bfs_beta, (unsigned long long)g.m},
+               s);
 
     BfsMarks marks{a, (uint32_t)G};
     auto launch = [&]() {

@@ -393,39 +393,45 @@ struct SsspMarks {
     }
 };
 
-__global__ void sssp_init(SsspArgs a, int32_t src, uint32_t chunk, uint32_t delta, float pull_alpha)
-{
-    const int32_t rs = a.R[src], deg = a.R[src + 1] - rs;
-    if (threadIdx.x == 0) {
-        SsspCtl *ctl = a.ctl;
-        a.dist[src] = 0u;
-        a.q.v[0] = src;
-        a.q.off[0] = 0;
-        a.q.row[0] = rs;
-        ctl->nf = 1;
-        ctl->mf = (uint32_t)deg;
-        ctl->iter = 0;
-        ctl->lo = 0;
-        ctl->hi = delta;
-        ctl->delta = delta;
-        ctl->far_any = 0;
-        ctl->split_kept = 0;
-        ctl->split_seen = 0;
-        ctl->split_min = 0xFFFFFFFFu;
-        ctl->unfit = 0;
-        ctl->parity = 0;
-        ctl->err = 0;
-        ctl->splits = 0;
-        ctl->near_entries = ctl->relaxed = ctl->improvements = ctl->far_entries = 0ull;
-        ctl->dir = SS_PUSH;
-        ctl->pull_alpha = pull_alpha;
-        ctl->m = (unsigned long long)a.R[a.n];
-        ctl->pull_iters = 0;
-        ctl->mode = deg == 0 ? SS_DONE : SS_RELAX;
+// the near queue of the source alone, and the control block (one work-group)
+struct SsspFirst {
+    SsspArgs a;
+    int32_t src;
+    uint32_t chunk, delta;
+    float pull_alpha;
+    __device__ void operator()() const
+    {
+        const int32_t rs = a.R[src], deg = a.R[src + 1] - rs;
+        if (threadIdx.x == 0) {
+            SsspCtl *ctl = a.ctl;
+            a.q.v[0] = src;
+            a.q.off[0] = 0;
+            a.q.row[0] = rs;
+            ctl->nf = 1;
+            ctl->mf = (uint32_t)deg;
+            ctl->iter = 0;
+            ctl->lo = 0;
+            ctl->hi = delta;
+            ctl->delta = delta;
+            ctl->far_any = 0;
+            ctl->split_kept = 0;
+            ctl->split_seen = 0;
+            ctl->split_min = 0xFFFFFFFFu;
+            ctl->unfit = 0;
+            ctl->parity = 0;
+            ctl->err = 0;
+            ctl->splits = 0;
+            ctl->near_entries = ctl->relaxed = ctl->improvements = ctl->far_entries = 0ull;
+            ctl->dir = SS_PUSH;
+            ctl->pull_alpha = pull_alpha;
+            ctl->m = (unsigned long long)a.R[a.n];
+            ctl->pull_iters = 0;
+            ctl->mode = deg == 0 ? SS_DONE : SS_RELAX;
+        }
+        // (the first iteration pushes; every compaction writes the near-queue bitmap a pull reads)
+        for (uint32_t c = threadIdx.x; (uint64_t)c * chunk < (uint64_t)deg; c += blockDim.x) a.q.part[c] = 0;
     }
-    // (the first iteration pushes; every compaction writes the near-queue bitmap a pull reads)
-    for (uint32_t c = threadIdx.x; (uint64_t)c * chunk < (uint64_t)deg; c += blockDim.x) a.q.part[c] = 0;
-}
+};
 
 uint32_t sssp_auto_delta(const Graph &g, double factor)
 {
@@ -957,14 +963,12 @@ void run_sssp(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStream_t s)
     a.ctl = c.arena.take<SsspCtl>(1);
     uint32_t *unfit_flag = c.arena.take<uint32_t>(1);
 
-    Fills()
-        .add(dist, 0xFFFFFFFFu, (size_t)n)
-        .add(a.near, 0u, 8ull * nwords)
-        .add(a.far, 0u, 8ull * nwords)
-        .add(status, 0u, 4ull * cg.blocks)
-        .run(s);
-    hipLaunchKernelGGL(sssp_init, dim3(1), dim3(GFR_BLOCK), 0, s, a, src, chunk, delta, (float)c.opt.sssp_pull_alpha);
-    GFR_LAUNCH_CHECK();
+    fill_first(Fills()
+                   .add(dist, 0xFFFFFFFFu, (size_t)n).but((size_t)src, 0u)
+                   .add(a.near, 0u, 8ull * nwords)
+                   .add(a.far, 0u, 8ull * nwords)
+                   .add(status, 0u, 4ull * cg.blocks),
+               SsspFirst{a, src, chunk, delta, (float)c.opt.sssp_pull_alpha}, s);
 
     SsspMarks marks{a, (uint32_t)G};
     const bool pull = c.opt.sssp_pull_alpha > 0;   // direction-optimizing iterations

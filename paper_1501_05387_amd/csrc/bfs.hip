@@ -906,15 +906,8 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s)
 
 void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena &ar)
 {
-    // mark-byte levels on mesh-like graphs (bfs.frontier 0 auto, 1 queue, 2 mark bytes); a forced pull
-    // direction needs the queue path's frontier bitmap
-    const int fr = c.opt.bfs_frontier;
     if (bfs_small_fits(c, g)) {
         run_bfs_small(c, g, src, depth, s);
-        return;
-    }
-    if (c.opt.bfs_direction != 2 && (fr == 2 || (fr == 0 && g.cls == GRAPH_MESH))) {
-        run_bfs_bitmap(c, g, src, depth, s, ar);
         return;
     }
     const int32_t n = g.n;
@@ -925,6 +918,19 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena
     const CompactGeom cg = compact_geom(nwords, c.num_cu);
     size_t need = 2 * al256(nwords * 4ull) + al256(nwords * 32ull) + 3 * al256(4ull * n) + al256(4 * nparts) +
                   al256(4ull * G) + al256(16ull * cg.blocks) + al256(sizeof(BfsCtl));
+    // Mark-byte levels (bfs.frontier 0 auto, 1 queue, 2 mark bytes) on mesh-like
+    // graphs whose rows one thread takes in a turn or two, and where a fixed
+    // scratch is too small for the queue; a forced pull direction needs the
+    // queue's frontier bitmap.  Random regular graphs of 1 M vertices with 8, 10,
+    // 12, 16, 20 and 32 entries each, marks / queue: 187 / 241, 257 / 242, 222 /
+    // 212, 259 / 237, 325 / 211 and 549 / 234 us; of 40,000 with 8 and 12 entries
+    // 120 / 140 and 151 / 134 us.
+    const int fr = c.opt.bfs_frontier;
+    const bool thin = g.m <= 9ll * n, fits = !ar.fixed || need <= ar.fixed_bytes;
+    if (c.opt.bfs_direction != 2 && (fr == 2 || (fr == 0 && g.cls == GRAPH_MESH && (thin || !fits)))) {
+        run_bfs_bitmap(c, g, src, depth, s, ar);
+        return;
+    }
     ar.reserve(need);
     BfsArgs a;
     memset(&a, 0, sizeof a);   // padding too: the bytes key the captured steps

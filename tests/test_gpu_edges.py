@@ -497,3 +497,18 @@ def test_outputs_queued_before_the_end_is_known(ctx):
                 assert np.array_equal(b[i], oracle.bfs(row, col, int(src[i])))
                 assert np.array_equal(d[i], oracle.sssp(row, col, w, int(src[i])))
     g.free()
+
+
+@pytest.mark.parametrize("degree", [8, 10, 34])
+def test_regular_graph_bfs_around_the_mark_byte_line(ctx, degree):
+    n, rng = 40009, np.random.default_rng(degree)
+    rings = [rng.permutation(n) for _ in range(degree // 2)]
+    row, col = graphgen.from_edges(n, np.concatenate(rings).astype(np.int32),
+                                   np.concatenate([np.roll(p, 1) for p in rings]).astype(np.int32))
+    g = ctx.graph_load_csr(row, col)
+    for src in (0, n - 1):
+        want = oracle.bfs(row, col, src)
+        d = ctx.bfs(g, src)
+        assert np.array_equal(_host(d), want)
+        assert np.array_equal(_host(ctx.bfs_noalloc(g, src, d)), want)
+    g.free()

@@ -37,7 +37,7 @@ constexpr int HG_HOT_BYTES = 152 * 1024;
 
 // What the kernels read of a graph with ranked columns.
 struct HotGraph {
-    const int32_t *C;          // position in the table of each edge's target, padded to whole chunks
+    const int32_t *C;          // position in the table (nf + 1 values) of each edge's target, padded to whole chunks
     const uint32_t *starts;    // bit e: a list starts at edge e (one chunk of padding)
     const int32_t *entry;      // [nch + 1] entry of the whole-graph queue that holds edge c * HG_CH
     const uint32_t *off;       // first edge of each entry
@@ -51,7 +51,7 @@ __global__ __launch_bounds__(HG_BLOCK) void gather_hot(HotGraph g, const T *tabl
     constexpr uint32_t H = HG_HOT_BYTES / sizeof(T);
     __shared__ T s_hot[H];
     if (*stop) return;
-    for (uint32_t i = threadIdx.x; i < min(H, g.nf); i += HG_BLOCK) s_hot[i] = table[i];
+    for (uint32_t i = threadIdx.x; i < min(H, g.nf + 1u); i += HG_BLOCK) s_hot[i] = table[i];
     __syncthreads();
     typedef int vec4 __attribute__((ext_vector_type(4)));
     struct Chunk {

@@ -79,8 +79,8 @@ __global__ __launch_bounds__(GFR_BLOCK) void pr_init(const int32_t *R, int32_t n
     for (int32_t v = blockIdx.x * GFR_BLOCK + threadIdx.x; v < n; v += gridDim.x * GFR_BLOCK) {
         const int32_t deg = R[v + 1] - R[v];
         x0[v] = xv;
-        if (deg > 0) contrib[v] = xv / (float)deg;
-        else dang += (double)xv;
+        contrib[v] = deg > 0 ? xv / (float)deg : 0.0f;   // (an asymmetric graph may name a vertex without edges)
+        if (deg == 0) dang += (double)xv;
     }
     block_sum2(dang, zero);
     if (threadIdx.x == 0) {
@@ -162,6 +162,7 @@ __global__ __launch_bounds__(GFR_BLOCK) void prk_init(const uint32_t *off, uint3
         contrib[pos[i]] = xv / (float)(int32_t)deg;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+        contrib[nf] = 0.0f;   // of targets without edges
         ctl->iso = xv;
         ctl->pr.D = (double)ctl->n_iso * (double)xv;
     }
@@ -240,11 +241,11 @@ static void run_pagerank_ranked(Ctx &c, Graph &g, const RankedCols &rk, float da
     const uint32_t nf = (uint32_t)g.full_nf, mf = (uint32_t)g.m;
     const int G = grid_blocks(c, 8);
     const size_t nch = rk.nch;
-    c.arena.reserve(3 * al256(4ull * nf) + al256(8ull * nf) + 2 * al256(8 * nch) + al256(8ull * G) +
-                    al256(sizeof(PrkCtl)));
+    c.arena.reserve(2 * al256(4ull * nf) + al256(4ull * nf + 4) + al256(8ull * nf) + 2 * al256(8 * nch) +
+                    al256(8ull * G) + al256(sizeof(PrkCtl)));
     float *xa = c.arena.take<float>(nf);
     float *xb = c.arena.take<float>(nf);
-    float *contrib = c.arena.take<float>(nf);
+    float *contrib = c.arena.take<float>((size_t)nf + 1);
     double *sum = c.arena.take<double>(nf);
     GatherScratch gs{c.arena.take<double>(nch), c.arena.take<double>(nch)};
     double *part = c.arena.take<double>(G);

@@ -22,7 +22,7 @@ struct RankArgs {
     const int32_t *v;
     uint32_t nf, mf;
     uint32_t *cursor;       // [256] class sizes, then next free places
-    int32_t *pos;           // [n] place of each vertex with edges
+    int32_t *pos;           // [n] place of each vertex with edges; nf of the others
     int32_t *epos;          // [nf] the same by entry
 };
 
@@ -135,6 +135,9 @@ const RankedCols *ranked_cols(Ctx &c, Graph &g, hipStream_t s)
     const dim3 grid(grid_blocks(c, 8)), block(256);
     fill_u32(cursor, 0u, 256, s);
     fill_u32(r.starts, 0u, b_s / 4, s);
+    // In a symmetric graph every target has edges.  The load does not ask for symmetry unless it is told to
+    // validate, so a target without edges gets the table's last place, which holds 0.
+    fill_u32(pos, nf, (size_t)g.n, s);
     const RankArgs a{g.full.off, g.full.v, nf, m, cursor, pos, r.pos};
     hipLaunchKernelGGL(rank_pass<0>, dim3(RANK_GROUPS), block, 0, s, a);
     hipLaunchKernelGGL(rank_scan, dim3(1), block, 0, s, cursor);

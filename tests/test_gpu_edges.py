@@ -267,6 +267,41 @@ def test_ranked_columns(ctx, name):
     g.free()
 
 
+def _without_rows(row, col, drop):
+    """The graph without the rows of the vertices in `drop`; entries that name them stay."""
+    deg = np.diff(row)
+    keep = ~np.repeat(drop, deg)
+    return np.concatenate([[0], np.cumsum(np.where(drop, 0, deg))]).astype(np.int32), col[keep]
+
+
+def _pagerank(row, col, damping, iters):
+    """Power iteration in float64; a vertex without edges gives its rank to all, and nothing to those that name it."""
+    n, deg = row.size - 1, np.diff(row)
+    rows, x = np.repeat(np.arange(n), deg), np.full(n, 1.0 / n)
+    for _ in range(iters):
+        y = np.where(deg > 0, x / np.maximum(deg, 1), 0.0)
+        total = np.bincount(rows, weights=y[col], minlength=n)
+        x = (1 - damping) / n + damping * (total + x[deg == 0].sum() / n)
+    return x
+
+
+@pytest.mark.parametrize("share", [0.1, 0.97])   # (0.97: every value of the table fits LDS)
+def test_pagerank_of_targets_without_edges(ctx, share):
+    """An asymmetric graph is accepted when no validation is asked for: its columns name vertices without a row."""
+    row, col = graphgen.rmat(18, 32)
+    deg = np.diff(row)
+    drop = np.random.default_rng(8).random(row.size - 1) < share
+    drop[np.argsort(deg)[-3000:]] = False   # the hubs keep the entries over the ranked columns' line
+    row, col = _without_rows(row, col, drop)
+    assert np.any(np.diff(row)[col] == 0) and col.size > 1 << 21
+    g = ctx.graph_load_csr(row, col)
+    for iters in (3, 9, 9):   # over the CSR, then over the ranked columns
+        x = _host(ctx.pagerank(g, 0.85, 0.0, iters)[0]).astype(np.float64)
+        want = _pagerank(row, col, 0.85, iters)
+        assert np.abs(x - want).sum() <= 1e-6 and np.all(np.abs(x - want) <= 1e-5 * want)
+    g.free()
+
+
 SMALL = {   # name: (graph, source): around the rules of the one-work-group traversal, both lane counts
     "one vertex": (lambda: (np.zeros(2, np.int32), np.zeros(0, np.int32)), 0),
     "no edges at the source": (lambda: _union((np.zeros(6, np.int32), np.zeros(0, np.int32)), graphgen.rmat(9)), 2),

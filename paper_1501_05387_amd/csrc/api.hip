@@ -343,7 +343,7 @@ static gfr_status guard(gfr_ctx *ctx, F f)
     try {
         c.err.clear();
         GFR_HIP(hipSetDevice(c.device));
-        f(c);
+        with_room([&]() { f(c); }, [&]() { return give_back_spares(c); });
         return GFR_OK;
     } catch (const Error &e) {
         c.err = e.msg;

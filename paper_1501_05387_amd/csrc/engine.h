@@ -17,15 +17,10 @@
 
 #include "../../include/gfr.h"
 #include "device.h"
+#include "error.h"
+#include "spare.h"
 
 namespace gfr {
-
-struct Error {
-    gfr_status code;
-    std::string msg;
-};
-
-[[noreturn]] void fail(gfr_status code, const std::string &msg);
 
 #define GFR_HIP(x)                                                                          \
     do {                                                                                    \
@@ -107,10 +102,11 @@ extern const char *const kClassNames[kNumGraphClasses];
 int classify_graph(int32_t n, int64_t m, int32_t max_deg);
 
 // Columns renumbered by degree, for the gathers of hotgather.h (made on first
-// use, under the context's lock; freed with the graph).
+// use, under the context's lock; freed with the graph, or when a call on the
+// context runs out of device memory: it then runs again without them).
 struct RankedCols {
-    DevMem mem;              // empty: not made, or it did not fit
-    bool tried = false;
+    DevMem mem;
+    Spare have;
     int32_t *C = nullptr;    // [m padded] position of each edge's target in degree order
     int32_t *pos = nullptr;  // [nf] position of each entry of the whole-graph queue
     uint32_t *starts = nullptr;
@@ -397,6 +393,10 @@ int grid_blocks(const Ctx &c, int per_cu = 4);
 // or (per_cu = 0) as many as are resident at once on every CU, so that no
 // work-group of a statically divided grid starts after the others finish.
 int resident_grid(const Ctx &c, const void *kernel, int per_cu);
+
+// Free what the context's graphs hold only to be faster (under the context's
+// lock, with no call's work in flight); false if there was nothing.
+bool give_back_spares(Ctx &c);
 
 // Solvers (outputs are device pointers on the context's device).
 void likely_neighbours(Ctx &c, Graph &g, hipStream_t s);

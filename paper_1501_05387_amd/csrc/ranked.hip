@@ -108,47 +108,60 @@ __global__ __launch_bounds__(256) void rank_entries(FrontierQ full, uint32_t nf,
 const RankedCols *ranked_cols(Ctx &c, Graph &g, hipStream_t s)
 {
     RankedCols &r = g.ranked;
-    if (r.tried) return r.mem.p ? &r : nullptr;
-    const uint32_t m = (uint32_t)g.m;
-    const uint32_t nch = (m + HG_CH - 1) / HG_CH;
-    const size_t padded = (size_t)nch * HG_CH;
-    const uint32_t nf = (uint32_t)g.full_nf;
-    const size_t b_c = al256(4 * padded), b_p = al256(4ull * nf), b_s = al256(padded / 8 + HG_CH / 8),
-                 b_e = al256(4ull * (nch + 1));
-    r.tried = true;
-    try {
+    const auto make = [&]() {
+        const uint32_t m = (uint32_t)g.m;
+        const uint32_t nch = (m + HG_CH - 1) / HG_CH;
+        const size_t padded = (size_t)nch * HG_CH;
+        const uint32_t nf = (uint32_t)g.full_nf;
+        const size_t b_c = al256(4 * padded), b_p = al256(4ull * nf), b_s = al256(padded / 8 + HG_CH / 8),
+                     b_e = al256(4ull * (nch + 1));
+        c.arena.reserve(al256(4ull * g.n));
+        int32_t *pos = c.arena.take<int32_t>(g.n);   // by vertex: only the columns need it
         r.mem.alloc(b_c + b_p + b_s + b_e + 1024);
-    } catch (const Error &e) {
-        if (e.code != GFR_E_OOM) throw;
+        char *base = (char *)r.mem.p;
+        r.C = (int32_t *)base;
+        r.pos = (int32_t *)(base + b_c);
+        r.starts = (uint32_t *)(base + b_c + b_p);
+        r.entry = (int32_t *)(base + b_c + b_p + b_s);
+        uint32_t *cursor = (uint32_t *)(base + b_c + b_p + b_s + b_e);
+        r.nch = nch;
+        const dim3 grid(grid_blocks(c, 8)), block(256);
+        fill_u32(cursor, 0u, 256, s);
+        fill_u32(r.starts, 0u, b_s / 4, s);
+        // In a symmetric graph every target has edges.  The load does not ask for symmetry unless it is told to
+        // validate, so a target without edges gets the table's last place, which holds 0.
+        fill_u32(pos, nf, (size_t)g.n, s);
+        const RankArgs a{g.full.off, g.full.v, nf, m, cursor, pos, r.pos};
+        hipLaunchKernelGGL(rank_pass<0>, dim3(RANK_GROUPS), block, 0, s, a);
+        hipLaunchKernelGGL(rank_scan, dim3(1), block, 0, s, cursor);
+        hipLaunchKernelGGL(rank_pass<1>, dim3(RANK_GROUPS), block, 0, s, a);
+        hipLaunchKernelGGL(rank_columns, grid, block, 0, s, g.C.as<int32_t>(), pos, m, (uint32_t)padded, r.C);
+        hipLaunchKernelGGL(rank_starts, grid, block, 0, s, g.full.off, nf, r.starts);
+        hipLaunchKernelGGL(rank_entries, grid, block, 0, s, g.full, nf, m, nch, r.entry);
+        GFR_LAUNCH_CHECK();
+        GFR_HIP(hipStreamSynchronize(s));   // later calls may come on other streams
+        g.bytes += r.mem.bytes;
+    };
+    const bool made = r.have.get(make, [&]() {
         (void)hipGetLastError();
-        return nullptr;
+        r.mem.release();
+    });
+    return made ? &r : nullptr;
+}
+
+bool give_back_spares(Ctx &c)
+{
+    bool any = false;
+    for (auto &kv : c.graphs) {
+        Graph &g = *kv.second;
+        if (g.ranked.have.state != Spare::MADE) continue;
+        g.bytes -= g.ranked.mem.bytes;
+        g.ranked.mem.release();
+        g.ranked.have.state = Spare::NO_ROOM;
+        any = true;
     }
-    char *base = (char *)r.mem.p;
-    r.C = (int32_t *)base;
-    r.pos = (int32_t *)(base + b_c);
-    r.starts = (uint32_t *)(base + b_c + b_p);
-    r.entry = (int32_t *)(base + b_c + b_p + b_s);
-    uint32_t *cursor = (uint32_t *)(base + b_c + b_p + b_s + b_e);
-    r.nch = nch;
-    c.arena.reserve(al256(4ull * g.n));
-    int32_t *pos = c.arena.take<int32_t>(g.n);   // by vertex: only the columns need it
-    const dim3 grid(grid_blocks(c, 8)), block(256);
-    fill_u32(cursor, 0u, 256, s);
-    fill_u32(r.starts, 0u, b_s / 4, s);
-    // In a symmetric graph every target has edges.  The load does not ask for symmetry unless it is told to
-    // validate, so a target without edges gets the table's last place, which holds 0.
-    fill_u32(pos, nf, (size_t)g.n, s);
-    const RankArgs a{g.full.off, g.full.v, nf, m, cursor, pos, r.pos};
-    hipLaunchKernelGGL(rank_pass<0>, dim3(RANK_GROUPS), block, 0, s, a);
-    hipLaunchKernelGGL(rank_scan, dim3(1), block, 0, s, cursor);
-    hipLaunchKernelGGL(rank_pass<1>, dim3(RANK_GROUPS), block, 0, s, a);
-    hipLaunchKernelGGL(rank_columns, grid, block, 0, s, g.C.as<int32_t>(), pos, m, (uint32_t)padded, r.C);
-    hipLaunchKernelGGL(rank_starts, grid, block, 0, s, g.full.off, nf, r.starts);
-    hipLaunchKernelGGL(rank_entries, grid, block, 0, s, g.full, nf, m, nch, r.entry);
-    GFR_LAUNCH_CHECK();
-    GFR_HIP(hipStreamSynchronize(s));   // later calls may come on other streams
-    g.bytes += r.mem.bytes;
-    return &r;
+    if (any) (void)hipGetLastError();   // of the allocation that failed: the call is made again
+    return any;
 }
 
 HotGraph hot_graph(const Graph &g, const RankedCols &r)

@@ -114,16 +114,16 @@ __device__ __forceinline__ void bc_pull_discover(const BcArgs &a, int32_t n, con
         const uint32_t visw = a.vis[grp * 2u + (uint32_t)(lane >> 5)];
         bool found = false;
         if (v < n && !(visw & (1u << (v & 31)))) {
-            int32_t e = a.R[v];
-            const int32_t re = a.R[v + 1];
+            uint32_t e = (uint32_t)a.R[v];
+            const uint32_t re = (uint32_t)a.R[v + 1];
             while (e < re) {
-                const int32_t k = min(4, re - e);
+                const uint32_t k = min(4u, re - e);
                 int32_t u[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) u[j] = a.C[j < k ? e + j : e];
+                for (uint32_t j = 0; j < 4; ++j) u[j] = a.C[j < k ? e + j : e];
                 uint32_t hit = 0;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) hit |= (j < k) ? (fb[u[j] >> 5] >> (u[j] & 31)) & 1u : 0u;
+                for (uint32_t j = 0; j < 4; ++j) hit |= (j < k) ? (fb[u[j] >> 5] >> (u[j] & 31)) & 1u : 0u;
                 if (hit) {
                     found = true;
                     break;

@@ -188,9 +188,9 @@ __global__ __launch_bounds__(GFR_BLOCK) void likely_kernel(const int32_t *R, con
     const int32_t lane = (int32_t)(threadIdx.x % LK_LANES);
     const uint32_t groups = gridDim.x * (GFR_BLOCK / LK_LANES);
     for (uint32_t v = (blockIdx.x * GFR_BLOCK + threadIdx.x) / LK_LANES; v < (uint32_t)n; v += groups) {
-        const int32_t r0 = R[v], r1 = min(R[v + 1], r0 + LK_MAX);
+        const uint32_t r0 = (uint32_t)R[v], r1 = head_end(r0, (uint32_t)R[v + 1], LK_MAX);
         int32_t deg = 0, best = -1;
-        for (int32_t e = r0 + lane; e < r1; e += LK_LANES) {
+        for (uint32_t e = r0 + (uint32_t)lane; e < r1; e += LK_LANES) {
             const int32_t u = C[e], d = R[u + 1] - R[u];
             if (d > deg) {
                 deg = d;
@@ -298,21 +298,22 @@ __global__ __launch_bounds__(GFR_BLOCK) void bfs_level(BfsArgs a)
         const uint32_t end = ((uint32_t)a.n + 63u) / 64u;
         uint32_t grp = blockIdx.x * GFR_WAVES + threadIdx.x / 64;
         uint32_t visw_n = 0;
-        int32_t u_n = 0, e_n = 0, re_n = 0;
+        int32_t u_n = 0;
+        uint32_t e_n = 0, re_n = 0;
         const auto fetch = [&](uint32_t gr) {
             if (gr >= end) return;
             const uint32_t x = min(gr * 64u + (uint32_t)lane, (uint32_t)a.n - 1u);
             visw_n = a.vis[gr * 2u + (uint32_t)(lane >> 5)];
             u_n = a.likely ? a.likely[x] : 0;
-            e_n = a.R[x];
-            re_n = a.R[x + 1u];
+            e_n = (uint32_t)a.R[x];
+            re_n = (uint32_t)a.R[x + 1u];
         };
         fetch(grp);
         for (; grp < end; grp += waves) {
             const int32_t v = (int32_t)(grp * 64u) + lane;
             const bool open = v < a.n && !(visw_n & (1u << (v & 31)));
             const int32_t u = u_n;
-            int32_t e = open ? e_n : 0, re = open ? re_n : 0;
+            uint32_t e = open ? e_n : 0u, re = open ? re_n : 0u;
             fetch(grp + waves);
             bool found = false;
             if (a.likely && e < re) {
@@ -321,14 +322,14 @@ __global__ __launch_bounds__(GFR_BLOCK) void bfs_level(BfsArgs a)
             }
             // a lane's first entries, four independent probes per step
             for (int step = 0; step < PULL_STEPS && e < re && !found; ++step) {
-                const int32_t k = min(4, re - e);
+                const uint32_t k = min(4u, re - e);
                 int32_t u[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) u[j] = a.C[j < k ? e + j : e];
+                for (uint32_t j = 0; j < 4; ++j) u[j] = a.C[j < k ? e + j : e];
                 uint32_t hit = 0;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) hit |= (j < k) ? (a.fb[u[j] >> 5] >> (u[j] & 31)) & 1u : 0u;
-                insp += (uint32_t)k;
+                for (uint32_t j = 0; j < 4; ++j) hit |= (j < k) ? (a.fb[u[j] >> 5] >> (u[j] & 31)) & 1u : 0u;
+                insp += k;
                 found = hit != 0;
                 e += 4;
             }
@@ -338,15 +339,15 @@ __global__ __launch_bounds__(GFR_BLOCK) void bfs_level(BfsArgs a)
                 uint64_t mine = todo;
                 for (int j = 0; j < lane / 16; ++j) mine &= mine - 1;
                 const int owner = mine ? __ffsll((unsigned long long)mine) - 1 : 0;
-                int32_t p = __shfl(e, owner, 64), end = __shfl(re, owner, 64);   // (the owner may sit in any quarter)
+                uint32_t p = shfl_u32(e, owner), end = shfl_u32(re, owner);   // (the owner may sit in any quarter)
                 if (!mine) end = p;
                 bool hit = false;
                 while (p < end && !hit) {
-                    const int32_t i0 = p + lane % 16, i1 = i0 + 16;
-                    const int32_t u0 = a.C[min(i0, end - 1)], u1 = a.C[min(i1, end - 1)];
+                    const uint32_t i = (uint32_t)lane % 16u;
+                    const int32_t u0 = a.C[entry_or_last(p, i, end)], u1 = a.C[entry_or_last(p, i + 16u, end)];
                     const uint32_t f0 = a.fb[u0 >> 5] >> (u0 & 31), f1 = a.fb[u1 >> 5] >> (u1 & 31);
                     hit = ((ballot((f0 | f1) & 1u) >> (lane & 48)) & 0xFFFFull) != 0;
-                    if (lane % 16 == 0) insp += (uint32_t)min(32, end - p);
+                    if (lane % 16 == 0) insp += min(32u, end - p);
                     p += 32;
                 }
                 const uint64_t hits = ballot(hit);
@@ -527,12 +528,12 @@ __global__ __launch_bounds__(BM_SOLO_BLOCK) void bfs_bitmap_head(BmArgs a, int32
     for (;;) {
         if (threadIdx.x < cnt) {
             const int32_t v = s_cur[threadIdx.x];
-            const int32_t e1 = a.R[v + 1];
-            for (int32_t e = a.R[v]; e < e1; e += 8) {
+            const uint32_t e1 = (uint32_t)a.R[v + 1];
+            for (uint32_t e = (uint32_t)a.R[v]; e < e1; e += 8) {
                 int32_t u[8];
                 uint32_t old[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) u[k] = a.C[min(e + k, e1 - 1)];
+                for (int k = 0; k < 8; ++k) u[k] = a.C[entry_or_last(e, k, e1)];
 #pragma unroll
                 for (int k = 0; k < 8; ++k)
                     if (e + k < e1) old[k] = atomicOr(a.vis + (u[k] >> 5), 1u << (u[k] & 31));
@@ -658,8 +659,8 @@ __global__ __launch_bounds__(BM_BLOCK) void bfs_bitmap_level(BmArgs a, int32_t l
         const uint32_t cnt = s_cnt;   // at most SPAN
         for (uint32_t i = threadIdx.x; i < cnt; i += BM_BLOCK) {
             const int32_t v = v0 + s_v[i];   // only vertices < n are ever marked
-            int32_t e = a.R[v];
-            const int32_t e1 = a.R[v + 1];
+            uint32_t e = (uint32_t)a.R[v];
+            const uint32_t e1 = (uint32_t)a.R[v + 1];
             if (!VIS && a.depth[v] >= 0) continue;
             a.depth[v] = L;
             found = 1;
@@ -667,7 +668,7 @@ __global__ __launch_bounds__(BM_BLOCK) void bfs_bitmap_level(BmArgs a, int32_t l
                 int32_t u[8];
                 uint32_t d[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) u[k] = a.C[min(e + k, e1 - 1)];
+                for (int k = 0; k < 8; ++k) u[k] = a.C[entry_or_last(e, k, e1)];
 #pragma unroll
                 for (int k = 0; k < 8; ++k) d[k] = VIS ? a.vis[u[k] >> 5] >> (u[k] & 31) & 1u : (uint32_t)(a.depth[u[k]] >= 0);
 #pragma unroll

@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "entries.h"
+
 #define GFR_BLOCK 256                 // work-group size used by every traversal kernel
 #define GFR_WAVES (GFR_BLOCK / 64)
 

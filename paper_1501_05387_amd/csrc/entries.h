@@ -1,0 +1,21 @@
+// entries.h -- steps along a row of the column array (host and device).
+//
+// Entry indices reach 2^31 - 2, so a step past a row's end may leave the range
+// of int32_t.  Kernels that take several entries of a row at a time count them
+// in uint32_t, where such a step stays past the end, and clamp with these.
+#pragma once
+
+#include <stdint.h>
+
+namespace gfr {
+
+// Entry e + k of the row that ends at `end`, or the row's last one (not for empty rows).
+constexpr uint32_t entry_or_last(uint32_t e, uint32_t k, uint32_t end) { return e + k < end ? e + k : end - 1u; }
+
+// End of the first `most` entries of the row [begin, end).
+constexpr uint32_t head_end(uint32_t begin, uint32_t end, uint32_t most)
+{
+    return end - begin < most ? end : begin + most;
+}
+
+}  // namespace gfr

@@ -111,18 +111,19 @@ __global__ __launch_bounds__(GFR_BLOCK) void pred_kernel(const int32_t *R, const
             if (v == src) {
                 p = src;
             } else {
-                const int32_t rb = R[v], re = R[v + 1];
-                if (re - rb > PRED_LANE_ROW) {
+                const uint32_t rb = (uint32_t)R[v], re = (uint32_t)R[v + 1];
+                if (re - rb > (uint32_t)PRED_LANE_ROW) {
                     s_v[atomicAdd(&s_n, 1u)] = v;   // at most GFR_BLOCK a turn: room was made below
                 } else {
-                    for (int32_t e = rb; e < re; e += 4) {
-                        const int32_t k = min(4, re - e);
+                    for (uint32_t e = rb; e < re; e += 4) {
+                        const uint32_t k = min(4u, re - e);
                         int32_t u[4];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) u[j] = C[j < k ? e + j : e];
+                        for (uint32_t j = 0; j < 4; ++j) u[j] = C[j < k ? e + j : e];
                         bool hit[4];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) hit[j] = (j < k) & t.closer(kv, j < k ? e + j : e, u[j]);
+                        for (uint32_t j = 0; j < 4; ++j)
+                            hit[j] = (j < k) & t.closer(kv, (int32_t)(j < k ? e + j : e), u[j]);
                         int32_t f = -1;
 #pragma unroll
                         for (int j = 3; j >= 0; --j) f = hit[j] ? u[j] : f;

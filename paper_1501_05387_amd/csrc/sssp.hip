@@ -741,13 +741,13 @@ __global__ __launch_bounds__(SM_BLOCK) void sssp_mark_level(SmArgs a, int32_t L,
                 } else {
                     du = a.dist[v];
                 }
-                const int32_t e1 = a.R[v + 1];
-                for (int32_t e = a.R[v]; e < e1; e += 8) {
+                const uint32_t e1 = (uint32_t)a.R[v + 1];
+                for (uint32_t e = (uint32_t)a.R[v]; e < e1; e += 8) {
                     int32_t u[8];
                     uint32_t wt[8], d[8];
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
-                        const int32_t ek = min(e + k, e1 - 1);
+                        const uint32_t ek = entry_or_last(e, k, e1);
                         u[k] = a.C[ek];
                         wt[k] = a.W[ek];
                     }

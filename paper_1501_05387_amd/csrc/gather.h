@@ -110,8 +110,8 @@ __global__ __launch_bounds__(GFR_BLOCK) void gather_chunks(FrontierQ q, const ui
 #pragma unroll
         for (int j = 0; j < EPL; ++j) {
             ent[j] = (int)(before + __popc(starts & ((2u << j) - 1u)));
-            const uint32_t e = min(e0 + k + j, e1 - 1u);   // past the end: the last edge again, not added
-            u[j] = C[(int32_t)e + s_delta[e0 + k + j < e1 ? ent[j] : 0]];
+            const uint32_t e = min(e0 + k + j, e1 - 1u);   // past the end: the last edge again (and its entry), not added
+            u[j] = C[(int32_t)e + s_delta[ent[j]]];
         }
         double val[EPL];
 #pragma unroll

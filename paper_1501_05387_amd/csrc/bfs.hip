@@ -888,13 +888,15 @@ static void run_bfs_small(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStre
     GFR_LAUNCH_CHECK();
     await_arrival(c, s);
     const volatile uint32_t *h = c.pinned;
-    c.stats.v["levels"] += h[0];
-    c.stats.v["push_levels"] += h[0];
-    c.stats.v["pull_levels"] += 0.0;
+    // (queue levels, which scale-free graphs take otherwise, count none from a source without edges)
+    const double levels = g.cls == GRAPH_SCALEFREE && h[2] == 0 ? 0.0 : (double)h[0];
+    c.stats.v["levels"] += levels;
+    c.stats.v["push_levels"] += levels;
     c.stats.v["edges_inspected"] += h[2];
     c.stats.v["push_entries"] += h[1];
     c.stats.v["push_edges"] += h[2];
     c.stats.v["push_new"] += h[3];
+    for (const char *k : {"pull_levels", "pull_unvisited", "pull_inspected", "pull_new"}) c.stats.v[k] += 0.0;
     c.stats.v["launches"] += 1.0;
     c.stats.v["solves"] += 1.0;
 }

@@ -907,6 +907,7 @@ static void run_sssp_marks(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStr
     c.stats.v["near_entries"] += (double)h.near_entries;
     c.stats.v["improvements"] += (double)h.improvements;
     c.stats.v["far_entries"] += (double)h.far_entries;
+    c.stats.v["pull_iterations"] += 0.0;
     c.stats.v["delta"] = delta;
     c.stats.v["launches"] += launched;
     c.stats.v["solves"] += 1.0;

@@ -335,6 +335,45 @@ def test_small_graph_bfs(ctx, name):
     g.free()
 
 
+# what the queue levels and iterations report, and so every path that is taken in their place
+BFS_STATS = ["levels", "push_levels", "pull_levels", "edges_inspected", "push_entries", "push_edges", "push_new",
+             "pull_unvisited", "pull_inspected", "pull_new", "launches", "solves", "kernel_ms"]
+SSSP_STATS = ["iterations", "relaxations", "edges_inspected", "splits", "near_entries", "improvements",
+              "far_entries", "pull_iterations", "delta", "launches", "solves", "kernel_ms"]
+
+
+def test_statistics_of_the_paths_without_a_queue(ctx):
+    row, col = _union((np.zeros(6, np.int32), np.zeros(0, np.int32)), graphgen.rmat(11))
+    g = ctx.graph_load_csr(row, col)
+    src = int(np.argmax(np.diff(row)))
+    got = []
+    for frontier in (1, 0):   # queue levels; one work-group
+        ctx.set_option("bfs.frontier", frontier)
+        ctx.set_option("bfs.direction", 1)
+        try:
+            ctx.bfs(g, src)
+            got.append({k: ctx.stat(k) for k in BFS_STATS})
+            ctx.bfs(g, 2)     # no edges at the source
+            got[-1]["levels without edges"] = ctx.stat("levels")
+        finally:
+            ctx.set_option("bfs.frontier", 0)
+            ctx.set_option("bfs.direction", 0)
+    for s in got:
+        del s["kernel_ms"], s["launches"]
+    assert got[0] == got[1]
+    g.free()
+    row, col = graphgen.grid(60)
+    g = ctx.graph_load_csr(row, col, graphgen.weights(row, col, 64))
+    for frontier in (1, 2):
+        ctx.set_option("sssp.frontier", frontier)
+        try:
+            ctx.sssp(g, 7)
+            assert all(ctx.stat(k) >= 0 for k in SSSP_STATS) and ctx.stat("pull_iterations") == 0
+        finally:
+            ctx.set_option("sssp.frontier", 0)
+    g.free()
+
+
 @pytest.mark.parametrize("k", [2, 24, 31, 32, 33, 64, 65, 97])
 @pytest.mark.parametrize("name", ["rmat", "hub rows", "lattice", "no edges at a source"])
 def test_batches_part_filled(ctx, name, k):

@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "../../include/gfr.h"
+#include "batches.h"
 #include "device.h"
 #include "error.h"
 #include "spare.h"
@@ -607,7 +608,8 @@ struct NoOutput {
 template <class LaunchFn, class OutputFn = NoOutput>
 int32_t run_until_done(Ctx &c, const uint32_t *flag_dev, uint32_t done_value, int32_t first_batch,
                        int64_t max_launches, hipStream_t s, LaunchFn launch, size_t bytes,
-                       const StepKey *key = nullptr, OutputFn output = OutputFn())
+                       const StepKey *key = nullptr, OutputFn output = OutputFn(),
+                       int32_t (*next)(int64_t) = next_batch)
 {
     int64_t launched = 0;
     int32_t batch = first_batch < 1 ? 1 : first_batch;
@@ -642,10 +644,7 @@ int32_t run_until_done(Ctx &c, const uint32_t *flag_dev, uint32_t done_value, in
         read_back(c, flag_dev, bytes, s);
         if (*(volatile uint32_t *)c.pinned == done_value) break;
         if (launched > max_launches) fail(GFR_E_DEVICE, "iteration watchdog: solve did not converge");
-        // double while little is known; later a quarter more at a time, as a
-        // traversal a few levels longer than the last one would otherwise
-        // queue its whole length again in launches that return at once
-        batch = launched < 32 ? (int32_t)launched : (int32_t)std::min<int64_t>(std::max<int64_t>(8, launched / 4), 256);
+        batch = next(launched);
     }
     return (int32_t)launched;
 }

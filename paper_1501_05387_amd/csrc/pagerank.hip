@@ -274,7 +274,8 @@ static void run_pagerank_ranked(Ctx &c, Graph &g, const RankedCols &rk, float da
     const auto output = [&]() {
         hipLaunchKernelGGL(prk_output, grid, block, 0, s, g.full, nf, g.R.as<int32_t>(), g.n, xa, xb, ctl, rank);
     };
-    run_until_done(c, done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h, nullptr, output);
+    run_until_done(c, done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h, nullptr, output,
+                   next_batch_unknown);
     c.waited = true;
     memcpy(&h, c.pinned, sizeof h);
     *iters = (int32_t)h.pr.iters;
@@ -327,7 +328,8 @@ void run_pagerank(Ctx &c, Graph &g, float damping, double tol, int32_t max_iter,
         hipLaunchKernelGGL(pr_reduce, dim3(1), dim3(GFR_BLOCK), 0, s, part, (uint32_t)G, ctl, 0u);
     };
     const int32_t first = max_iter < 8 ? max_iter : 8;
-    run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h);
+    run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h, nullptr, NoOutput(),
+                   next_batch_unknown);
     memcpy(&h, c.pinned, sizeof h);
     const float *xf = (h.iters & 1) ? xb : xa;
     GFR_HIP(hipMemcpyAsync(rank, xf, 4ull * n, hipMemcpyDeviceToDevice, s));
@@ -531,7 +533,8 @@ const uint8_t *run_pagerank_filtered(Ctx &c, Graph &g, double damping, double ve
                            q, (uint32_t)GATHER_CH, status, &ctl->parity, &ctl->err);
     };
     const int32_t first = max_iter < 8 ? max_iter : 8;
-    run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h);
+    run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h, nullptr, NoOutput(),
+                   next_batch_unknown);
     hipLaunchKernelGGL(pf_output, dim3(G), dim3(GFR_BLOCK), 0, s, R, n, x, keep, ctl, rank, active);
     GFR_LAUNCH_CHECK();
     memcpy(&h, c.pinned, sizeof h);
@@ -648,7 +651,8 @@ void run_ppr(Ctx &c, Graph &g, const int32_t *seeds, int32_t k, double damping, 
         hipLaunchKernelGGL(pr_reduce, dim3(1), dim3(GFR_BLOCK), 0, s, part, (uint32_t)G, ctl, 0u);
     };
     const int32_t first = max_iter < 8 ? max_iter : 8;
-    run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h);
+    run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h, nullptr, NoOutput(),
+                   next_batch_unknown);
     memcpy(&h, c.pinned, sizeof h);
     const double *xf = (h.iters & 1) ? xb : xa;
     GFR_HIP(hipMemcpyAsync(rank, xf, 8ull * n, hipMemcpyDeviceToDevice, s));

@@ -287,9 +287,12 @@ gfr_status gfr_cc(gfr_ctx *ctx, gfr_graph g, int32_t *label_out, int32_t *num_co
  * both cases; compare *iters_out with max_iter).  Ranks are FP32, global sums
  * FP64.  rank_out: n floats; iters_out / final_l1_out: host pointers, may be
  * NULL.  GFR_E_INVALID if damping is not in (0,1) or max_iter < 1.
- * The first call with max_iter >= 4 on a scale-free graph of 2^21 entries or
- * more adds a copy of the columns, renumbered by degree (about 4.2 bytes per
- * entry), to the graph's device memory; without room for it the CSR is used.
+ * On a scale-free graph of 2^21 entries or more, calls with max_iter >= 4 use a
+ * copy of the columns, renumbered by degree (about 4.2 bytes per entry of device
+ * memory).  The second call on the graph makes it, or the first one where that
+ * already pays (max_iter >= 8, l1_tol <= 1e-3 and 10 * 2^20 entries, or l1_tol <= 1e-2
+ * and 2^25 entries).  Without room for it the CSR is used, and it is given back
+ * when another call on the context runs out of device memory.
  */
 gfr_status gfr_pagerank(gfr_ctx *ctx, gfr_graph g, float damping, double l1_tol,
                         int32_t max_iter, float *rank_out, int32_t *iters_out,

@@ -132,6 +132,7 @@ struct Graph {
     int32_t full_nf = 0;
     int32_t n_isolated = 0;
     RankedCols ranked;
+    int32_t rankings = 0;    // PageRank calls so far
     DevMem likely;   // [n] each vertex's neighbour a pull level probes first (likely_neighbours), or none
     int32_t bip_checked_nl = -1;   // last side split verified for the bipartite rankings
     // hints for the speculative level loops (the size of the first batch of

@@ -224,15 +224,27 @@ __global__ __launch_bounds__(GFR_BLOCK) void prk_output(FrontierQ full, uint32_t
             if (R[v] == R[v + 1]) rank[v] = iso;
 }
 
-// Ranked columns pay on scale-free graphs and for at least four iterations:
-// making them costs one to two sweeps of the CSR, and each iteration saves half
-// of one.  A call to L1 < 1e-6 on R-MAT graphs (16 edges drawn per vertex) of
-// 60 K, 120 K, 500 K and 2 M vertices takes 583, 637, 1,073 and 3,494 us with
-// them (848, 985, 1,910 and 4,922 the first time) and 543, 712, 1,879 and 7,555
-// without: from 2 M entries on.
-static bool pays_ranked(const Graph &g, int32_t max_iter)
+// Ranked columns pay on scale-free graphs and for at least four iterations,
+// once they are there.  Making them costs one to two sweeps of the CSR, so the
+// call that does so is only faster where it saves more than that.  R-MAT, 16
+// edges drawn per vertex, over the CSR / with the columns made in the call / with
+// columns made before, us:
+//   entries             2.3 M              3.7 M              5.1 M              7.6 M
+//   to 1e-6     519 / 727 / 623    626 / 787 / 660    790 / 830 / 682    885 / 946 / 689
+//   8 iterations 252 / 392 / 284   300 / 425 / 302    358 / 458 / 321    502 / 612 / 369
+//   4 iterations 163 / 283 / 174   187 / 300 / 182    222 / 328 / 191    320 / 463 / 217
+//   entries            10.4 M             15.5 M             31.4 M
+//   to 1e-6   1,240 / 1,123 / 895  1,480 / 1,280 / 1,000  2,787 / 2,148 / 1,745
+//   8 iterations 635 / 650 / 425   807 / 797 / 530    1,466 / 1,296 / 901
+//   4 iterations 366 / 465 / 242   475 / 561 / 294    817 / 860 / 487
+// (five iterations reach 1e-2, nine 1e-4, 16 to 19 1e-6).  A graph that is ranked
+// a second time is taken to be ranked again after that.
+static bool pays_ranked(const Graph &g, double tol, int32_t max_iter, int32_t earlier)
 {
-    return g.cls == GRAPH_SCALEFREE && g.full_nf > 0 && max_iter >= 4 && g.m >= (1 << 21);
+    if (g.cls != GRAPH_SCALEFREE || g.full_nf == 0 || max_iter < 4 || g.m < (1 << 21)) return false;
+    if (earlier > 0 || g.ranked.have.state == Spare::MADE) return true;
+    if (max_iter >= 8 && tol <= 1e-3) return g.m >= 10 << 20;
+    return g.m >= 1 << 25 && tol <= 1e-2;
 }
 
 static void run_pagerank_ranked(Ctx &c, Graph &g, const RankedCols &rk, float damping, double tol, int32_t max_iter,
@@ -297,7 +309,7 @@ static int sweep_grid(const Ctx &c, const Graph &g)
 void run_pagerank(Ctx &c, Graph &g, float damping, double tol, int32_t max_iter, float *rank,
                   int32_t *iters, double *l1, hipStream_t s)
 {
-    if (pays_ranked(g, max_iter)) {
+    if (pays_ranked(g, tol, max_iter, g.rankings++)) {
         if (const RankedCols *rk = ranked_cols(c, g, s)) {
             run_pagerank_ranked(c, g, *rk, damping, tol, max_iter, rank, iters, l1, s);
             return;

@@ -267,6 +267,32 @@ def test_ranked_columns(ctx, name):
     g.free()
 
 
+# scale, edge factor, (iterations, tolerance) of the calls, which of them hold the ranked columns afterwards
+RANKED_CALLS = {
+    "small": (17, 16, [(1000, 1e-6), (3, 0.0), (4, 0.0)], [False, False, True]),
+    "first call": (18, 32, [(8, 0.0)], [True]),
+    "few iterations": (18, 32, [(7, 0.0), (4, 0.0)], [False, True]),
+    "loose": (18, 32, [(1000, 1e-2), (1000, 0.5)], [False, True]),
+}
+
+
+@pytest.mark.parametrize("name", list(RANKED_CALLS))
+def test_the_call_that_makes_ranked_columns(ctx, name):
+    """Only where the call itself is faster with them, or when the graph is ranked again."""
+    scale, factor, calls, want = RANKED_CALLS[name]
+    row, col = graphgen.rmat(scale, factor)
+    assert (1 << 21 if name == "small" else 10 << 20) < col.size < (10 << 20 if name == "small" else 1 << 25)
+    g = ctx.graph_load_csr(row, col)
+    held = ctx.graph_info(g)[2]
+    got = []
+    for iters, tol in calls:
+        _, it, _ = ctx.pagerank(g, 0.85, tol, iters)
+        got.append(ctx.graph_info(g)[2] > held)
+        assert it <= iters
+    assert got == want
+    g.free()
+
+
 def _without_rows(row, col, drop):
     """The graph without the rows of the vertices in `drop`; entries that name them stay."""
     deg = np.diff(row)

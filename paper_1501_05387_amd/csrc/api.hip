@@ -778,6 +778,7 @@ gfr_status gfr_graph_load_csr(gfr_ctx *ctx, int32_t n, int64_t m, const int32_t 
         for (int32_t i = 0; i < n; ++i) md = std::max(md, R[i + 1] - R[i]);
         g->max_deg = md;
         g->cls = classify_graph(n, m, md);
+        if (g->cls == GRAPH_MESH) g->near = near_share(n, m, R, C);
         build_full_queue(c, *g, R);
         likely_neighbours(c, *g, c.stream);
         GFR_HIP(hipStreamSynchronize(c.stream));

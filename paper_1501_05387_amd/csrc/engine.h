@@ -19,6 +19,7 @@
 #include "batches.h"
 #include "device.h"
 #include "error.h"
+#include "nearness.h"
 #include "spare.h"
 
 namespace gfr {
@@ -123,6 +124,7 @@ struct Graph {
     bool weighted = false;
     int32_t max_deg = 0;
     double mean_w = 0.0;
+    double near = 0.0;       // near_share of a mesh-class graph
     uint64_t bytes = 0;
     // the whole vertex set as a frontier queue (non-isolated vertices in id
     // order, offsets = row offsets), chunked for the gather kernels

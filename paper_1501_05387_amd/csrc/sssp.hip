@@ -492,8 +492,8 @@ static void sssp_check_unfit(Ctx &c, Graph &g, const uint32_t *dist, uint32_t *f
 
 enum : uint32_t { SM_RELAX = 0, SM_SPLIT = 1, SM_DONE = 2 };
 
-constexpr int SM_BLOCK = 512;
-constexpr int SM_WAVES = SM_BLOCK / 64;
+constexpr int SM_BLOCK = 512;   // largest work-group
+static_assert(NEAR_RUN == SM_BLOCK * 16, "near_share counts in the spans that rounds run in");
 constexpr int32_t SM_ROUNDS = 8;
 
 struct SmState {
@@ -571,15 +571,15 @@ __device__ __forceinline__ uint32_t owner_mask(const uint4 (&w)[VPT / 16])
 // improvement, and relaxing with a value that only looks smaller could go round
 // in circles.  A vertex is in the list at most once (a bit in LDS), so SPAN
 // entries are enough.
-template <int VPT, bool LOCAL>
-__global__ __launch_bounds__(SM_BLOCK) void sssp_mark_level(SmArgs a, int32_t L, int32_t rounds)
+template <int BLOCK, int VPT, bool LOCAL>
+__global__ __launch_bounds__(BLOCK) void sssp_mark_level(SmArgs a, int32_t L, int32_t rounds)
 {
-    static_assert((VPT == 16 || VPT == 32) && SM_BLOCK * VPT <= 65536, "16-bit offsets in a span");
-    constexpr int VEC = VPT / 16;
-    constexpr int SPAN = SM_BLOCK * VPT;
+    static_assert((VPT == 16 || VPT == 32) && BLOCK * VPT <= 65536, "16-bit offsets in a span");
+    constexpr int VEC = VPT / 16, WAVES = BLOCK / 64;
+    constexpr int SPAN = BLOCK * VPT;
     const uint32_t G = gridDim.x;
     const int lane = lane_id(), wave = threadIdx.x / 64;
-    __shared__ uint32_t s_bits[SM_WAVES], s_min[SM_WAVES];
+    __shared__ uint32_t s_bits[WAVES], s_min[WAVES];
     __shared__ SmState s_st;
     __shared__ uint16_t s_v[SPAN];                      // circular list of vertices to relax
     __shared__ uint32_t s_best[LOCAL ? SPAN : 1];       // smallest distance known here
@@ -594,13 +594,13 @@ __global__ __launch_bounds__(SM_BLOCK) void sssp_mark_level(SmArgs a, int32_t L,
         for (int j = 0; j < VEC; ++j)
             w[j] = own < nown ? *(const uint4 *)(p + own * VPT + 16 * j) : make_uint4(0u, 0u, 0u, 0u);
     };
-    load_marks(near, (size_t)blockIdx.x * SM_BLOCK + threadIdx.x);
+    load_marks(near, (size_t)blockIdx.x * BLOCK + threadIdx.x);
     const SmState p = a.st[(L & 1) ^ 1];
     // this launch's mode and bucket from the previous launch's words
     {
         const unsigned long long *pf = a.flags + (size_t)((L & 1) ^ 1) * G;
         uint32_t bits = 0, mn = 0xFFFFFFFFu;
-        for (uint32_t i = threadIdx.x; i < G; i += SM_BLOCK) {
+        for (uint32_t i = threadIdx.x; i < G; i += BLOCK) {
             const unsigned long long f = pf[i];
             bits |= (uint32_t)f;
             mn = min(mn, (uint32_t)(f >> 32));
@@ -613,7 +613,7 @@ __global__ __launch_bounds__(SM_BLOCK) void sssp_mark_level(SmArgs a, int32_t L,
         }
         __syncthreads();
         if (threadIdx.x == 0) {
-            for (int i = 1; i < SM_WAVES; ++i) {
+            for (int i = 1; i < WAVES; ++i) {
                 bits |= s_bits[i];
                 mn = min(mn, s_min[i]);
             }
@@ -658,13 +658,13 @@ __global__ __launch_bounds__(SM_BLOCK) void sssp_mark_level(SmArgs a, int32_t L,
     uint32_t bits = 0, fmin = 0xFFFFFFFFu;
     uint32_t nent = 0, nrel = 0, nimp = 0, nfar = 0;
     bool ovf = false;
-    for (size_t span = blockIdx.x; span * SM_BLOCK < nown; span += G) {
-        const size_t own = span * SM_BLOCK + threadIdx.x;
+    for (size_t span = blockIdx.x; span * BLOCK < nown; span += G) {
+        const size_t own = span * BLOCK + threadIdx.x;
         if (split || span != blockIdx.x) load_marks(split ? a.far : near, own);
         const uint32_t mine = owner_mask<VPT>(w);
         if (!__syncthreads_or((int)mine)) continue;
         if (LOCAL) {
-            for (uint32_t i = threadIdx.x; i < SPAN; i += SM_BLOCK) s_best[i] = 0xFFFFFFFFu;
+            for (uint32_t i = threadIdx.x; i < SPAN; i += BLOCK) s_best[i] = 0xFFFFFFFFu;
             if (threadIdx.x < SPAN / 32) s_in[threadIdx.x] = 0;
         }
         if (threadIdx.x == 0) s_tail = 0;
@@ -724,11 +724,11 @@ __global__ __launch_bounds__(SM_BLOCK) void sssp_mark_level(SmArgs a, int32_t L,
             }
             lim = head + SPAN;   // entries from head on are still being read in this round
             if (round == rounds) {   // the rest goes to the next launch
-                for (uint32_t i = head + threadIdx.x; i < tail; i += SM_BLOCK) nxt[v0 + s_v[i % SPAN]] = 1;
+                for (uint32_t i = head + threadIdx.x; i < tail; i += BLOCK) nxt[v0 + s_v[i % SPAN]] = 1;
                 bits |= SMF_NEAR;
                 break;
             }
-            for (uint32_t i = head + threadIdx.x; i < tail; i += SM_BLOCK) {
+            for (uint32_t i = head + threadIdx.x; i < tail; i += BLOCK) {
                 const uint32_t off = s_v[i % SPAN];
                 const int32_t v = (int32_t)(v0 + off);   // only vertices < n are ever marked
                 ++nent;
@@ -809,7 +809,7 @@ __global__ __launch_bounds__(SM_BLOCK) void sssp_mark_level(SmArgs a, int32_t L,
     nrel = wave_sum_u32(nrel);
     nimp = wave_sum_u32(nimp);
     nfar = wave_sum_u32(nfar);
-    __shared__ uint32_t s_c[4][SM_WAVES];
+    __shared__ uint32_t s_c[4][WAVES];
     if (lane == 0) {
         s_bits[wave] = bits;
         s_min[wave] = fmin;
@@ -820,7 +820,7 @@ __global__ __launch_bounds__(SM_BLOCK) void sssp_mark_level(SmArgs a, int32_t L,
     }
     ovf = __syncthreads_or((int)ovf) != 0;
     if (threadIdx.x == 0) {
-        for (int i = 1; i < SM_WAVES; ++i) {
+        for (int i = 1; i < WAVES; ++i) {
             bits |= s_bits[i];
             fmin = min(fmin, s_min[i]);
         }
@@ -829,7 +829,7 @@ __global__ __launch_bounds__(SM_BLOCK) void sssp_mark_level(SmArgs a, int32_t L,
     }
     if (threadIdx.x < 4) {
         uint32_t t = 0;
-        for (int i = 0; i < SM_WAVES; ++i) t += s_c[threadIdx.x][i];
+        for (int i = 0; i < WAVES; ++i) t += s_c[threadIdx.x][i];
         if (t) a.count[blockIdx.x].v[threadIdx.x] += t;   // this work-group's own
     }
 }
@@ -848,17 +848,30 @@ static void run_sssp_marks(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStr
 {
     const int32_t n = g.n;
     const size_t nb = ((size_t)n + 31) / 32 * 32;
-    // Rounds inside a launch where all spans are resident with the 49 KB of
-    // LDS they take (three groups per CU).  Lattices of 100^2, 300^2, 1000^2
+    // Rounds inside a launch pay where edges stay inside a span (lattices and
+    // other graphs numbered along their rows; near_share) and all spans are
+    // resident with the 49 KB of LDS they take (three groups per CU).  Lattices of 100^2, 300^2, 1000^2
     // and 1999^2 at the packaged bucket width: 0.55, 0.97, 1.41 and 2.08 ms with
     // rounds, 0.85, 1.27, 1.59 and 2.39 without; 4096^2, where groups wait for
     // LDS, 7.2 against 6.6.  One, three, eight and 32 rounds on 1999^2: 2.91,
     // 2.12, 2.08 and 3.06 ms (too many carry distances far that are improved later).
-    // Beyond that, 32 vertices per thread where 16 would leave more spans than
-    // are resident (four groups per CU).
+    // A cube of 46^3, 67^3 and 100^3 vertices (91, 82 and 66 % of its entries inside a
+    // span): 1,575, 2,684 and 5,320 us with rounds, 1,548, 2,041 and 3,008 without.
+    //
+    // Without rounds a large span has nothing to offer, and spans of 8,192
+    // vertices leave most of the chip idle while the near set is fat: 2,048
+    // vertices each, or 4,096 where those fill the chip.  Random regular graphs
+    // with 6 entries per vertex of 30,000, 100,000, 300,000 and 1 M vertices, with
+    // rounds / 8,192 / 4,096 / 2,048: 1,083 / 664 / 459 / 406, 975 / 726 / 503 / 428, 923 /
+    // 761 / 531 / 468 and 1,184 / 1,019 / 802 / 845 us (the queue form 438, 501, 612,
+    // 1,079).  Spans of 1,024 are faster still below 100,000 vertices and slower above
+    // 300,000.
+    // Beyond what is resident (four groups per CU), 32 vertices per thread.
     const size_t cu_span = (size_t)c.num_cu * SM_BLOCK * 16;
-    const bool local = (size_t)n <= 3 * cu_span, wide = (size_t)n > 4 * cu_span;
-    const size_t span = (size_t)SM_BLOCK * (wide ? 32 : 16);
+    const bool near = g.near >= NEAR_SHARE, wide = (size_t)n > 4 * cu_span;
+    const bool local = near && g.m <= 16ll * n && (size_t)n <= 3 * cu_span;
+    const int threads = near || wide ? SM_BLOCK : (size_t)n >= 4096ull * c.num_cu ? 256 : 128;
+    const size_t span = (size_t)threads * (wide ? 32 : 16);
     const int G = (int)std::min(((size_t)n + span - 1) / span, (size_t)grid_blocks(c, 4));
     // a graph of one span has nothing to wait for: its bucket is finished in one launch
     const int32_t rounds = G == 1 ? INT32_MAX : SM_ROUNDS;
@@ -886,10 +899,13 @@ static void run_sssp_marks(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStr
     int32_t level = 0;
     auto launch = [&]() {
         c.ktimer.run("sssp_mark_level", s, [&]() {
-            const dim3 grid(G), block(SM_BLOCK);
-            if (local) hipLaunchKernelGGL((sssp_mark_level<16, true>), grid, block, 0, s, a, level, rounds);
-            else if (wide) hipLaunchKernelGGL((sssp_mark_level<32, false>), grid, block, 0, s, a, level, rounds);
-            else hipLaunchKernelGGL((sssp_mark_level<16, false>), grid, block, 0, s, a, level, rounds);
+            const dim3 grid(G), block(threads);
+            if (local) hipLaunchKernelGGL((sssp_mark_level<512, 16, true>), grid, block, 0, s, a, level, rounds);
+            else if (wide) hipLaunchKernelGGL((sssp_mark_level<512, 32, false>), grid, block, 0, s, a, level, rounds);
+            else if (near) hipLaunchKernelGGL((sssp_mark_level<512, 16, false>), grid, block, 0, s, a, level, rounds);
+            else if (threads == 256)
+                hipLaunchKernelGGL((sssp_mark_level<256, 16, false>), grid, block, 0, s, a, level, rounds);
+            else hipLaunchKernelGGL((sssp_mark_level<128, 16, false>), grid, block, 0, s, a, level, rounds);
         });
         ++level;
     };

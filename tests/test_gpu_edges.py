@@ -193,6 +193,43 @@ def test_mark_byte_iterations(ctx, name):
         g.free()
 
 
+def _shuffled(row, col, seed):
+    return _renumbered(row, col, np.random.default_rng(seed).permutation(row.size - 1))
+
+
+# graphs whose edges leave the spans: 2,048 vertices to a work-group, 4,096 from 4,096 vertices per CU on
+SSSP_FAR = {   # name: (graph, source, largest weight, bucket width or 0 for the default)
+    "span -1": (lambda: _shuffled(*graphgen.from_edges(10239, np.arange(10238), np.arange(1, 10239)), 1), 5, 64, 0),
+    "span": (lambda: _shuffled(*graphgen.from_edges(10240, np.arange(10239), np.arange(1, 10240)), 2), 10239, 64, 0),
+    "span +1": (lambda: _shuffled(*graphgen.from_edges(10241, np.arange(10240), np.arange(1, 10241)), 3), 0, 64, 100),
+    "lattice": (lambda: _shuffled(*graphgen.grid(217), 4), 1234, 1000, 0),
+    "narrow buckets": (lambda: _shuffled(*graphgen.grid(120), 5), 77, 1000, 40),
+    "wide buckets": (lambda: _random_regular(100003, 6, 6), 9, 1000, 16000),
+    "long rows": (lambda: _random_regular(30011, 40, 7), 9, 64, 0),
+    "larger spans -1": (lambda: _random_regular(1048575, 4, 8), 17, 64, 0),
+    "larger spans": (lambda: _random_regular(1048576, 4, 9), 1048575, 64, 200),
+    "larger spans +1": (lambda: _random_regular(1048577, 4, 10), 0, 1000, 0),
+}
+
+
+@pytest.mark.parametrize("name", list(SSSP_FAR))
+def test_mark_byte_iterations_across_spans(ctx, name):
+    make, src, maxw, delta = SSSP_FAR[name]
+    row, col = make()
+    w = graphgen.weights(row, col, maxw)
+    g = ctx.graph_load_csr(row, col, w)
+    ctx.set_option("sssp.delta", delta)
+    ctx.set_option("sssp.frontier", 2)
+    try:
+        want = oracle.sssp(row, col, w, src)
+        for _ in range(2):
+            assert np.array_equal(_host(ctx.sssp(g, src)).view(np.uint32), want)
+    finally:
+        ctx.set_option("sssp.delta", 0)
+        ctx.set_option("sssp.frontier", 0)
+        g.free()
+
+
 def _rows(degrees, seed):
     """Symmetric simple graph whose first vertices have the given numbers of neighbours (leaves of their own)."""
     eu, ev, leaf = [], [], len(degrees)

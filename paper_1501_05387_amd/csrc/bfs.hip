@@ -600,12 +600,12 @@ __global__ void bfs_bitmap_init(BmArgs a, int32_t src)
 // of 2^24 vertices is 2 MB and stays in L2; depth[] is 64 MB) and stores one
 // mark.  A probe that misses the bit of a vertex of the same level, which its
 // owner is just setting, leaves a mark that the owner drops in the next launch.
-template <int VPT, bool VIS>
-__global__ __launch_bounds__(BM_BLOCK) void bfs_bitmap_level(BmArgs a, int32_t launch)
+template <int BLOCK, int VPT, bool VIS>
+__global__ __launch_bounds__(BLOCK) void bfs_bitmap_level(BmArgs a, int32_t launch)
 {
-    static_assert((VPT == 16 || VPT == 32) && BM_BLOCK * VPT <= 65536, "16-bit offsets in a span");
+    static_assert((VPT == 16 || VPT == 32) && BLOCK * VPT <= 65536, "16-bit offsets in a span");
     constexpr int VEC = VPT / 16;
-    constexpr int SPAN = BM_BLOCK * VPT;
+    constexpr int SPAN = BLOCK * VPT;
     __shared__ uint16_t s_v[SPAN];
     __shared__ uint32_t s_cnt;
     BfsCtl *ctl = a.ctl;
@@ -616,10 +616,10 @@ __global__ __launch_bounds__(BM_BLOCK) void bfs_bitmap_level(BmArgs a, int32_t l
     uint8_t *nxt = a.mk[(L & 1) ^ 1];
     int found = 0;
     const size_t nown = ((size_t)a.n + VPT - 1) / VPT;   // owners (the mark bytes are padded to whole ones)
-    for (size_t span = blockIdx.x; span * BM_BLOCK < nown; span += G) {
+    for (size_t span = blockIdx.x; span * BLOCK < nown; span += G) {
         if (threadIdx.x == 0) s_cnt = 0;
         __syncthreads();
-        const size_t own = span * BM_BLOCK + threadIdx.x;
+        const size_t own = span * BLOCK + threadIdx.x;
         uint4 w[VEC];
 #pragma unroll
         for (int j = 0; j < VEC; ++j)
@@ -657,7 +657,7 @@ __global__ __launch_bounds__(BM_BLOCK) void bfs_bitmap_level(BmArgs a, int32_t l
         }
         __syncthreads();
         const uint32_t cnt = s_cnt;   // at most SPAN
-        for (uint32_t i = threadIdx.x; i < cnt; i += BM_BLOCK) {
+        for (uint32_t i = threadIdx.x; i < cnt; i += BLOCK) {
             const int32_t v = v0 + s_v[i];   // only vertices < n are ever marked
             uint32_t e = (uint32_t)a.R[v];
             const uint32_t e1 = (uint32_t)a.R[v + 1];
@@ -683,7 +683,7 @@ __global__ __launch_bounds__(BM_BLOCK) void bfs_bitmap_level(BmArgs a, int32_t l
         // the previous level held no vertex: it was the end
         const uint32_t *fprev = a.flags + (size_t)((L & 1) ^ 1) * G;
         uint32_t any = 0;
-        for (uint32_t i = threadIdx.x; i < G; i += BM_BLOCK) any |= fprev[i];
+        for (uint32_t i = threadIdx.x; i < G; i += BLOCK) any |= fprev[i];
         if (!__syncthreads_or((int)any)) {
             if (threadIdx.x == 0) {
                 ctl->level = L - 1;
@@ -697,13 +697,22 @@ __global__ __launch_bounds__(BM_BLOCK) void bfs_bitmap_level(BmArgs a, int32_t l
     if (threadIdx.x == 0) a.flags[(size_t)(L & 1) * G + blockIdx.x] = (uint32_t)found;
 }
 
+// rows that one thread takes in a turn or two
+static bool bm_thin(const Graph &g) { return g.m <= 9ll * g.n; }
+
 static void run_bfs_bitmap(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena &ar)
 {
     const int32_t n = g.n;
     const size_t nb = ((size_t)n + 63) / 64 * 64;
-    // 32 vertices per thread where 16 would leave more spans than are resident (four groups per CU)
+    // 32 vertices per thread where 16 would leave more spans than are resident (four groups per CU).
+    // Where rows are long a level is bound by how many of the CUs expand them, and spans of 8,192 vertices
+    // leave most of them idle: 2,048 vertices each, or 4,096 where those fill the chip.  Random regular
+    // graphs of 100,000 x 16, 100,000 x 64, 300,000 x 100, 1 M x 16 and 1 M x 32 entries, spans of 8,192 /
+    // 4,096 / 2,048: 213 / 160 / 147, 632 / 384 / 295, 1,057 / 565 / 468, 284 / 217 / 216 and 404 / 288 / 283 us.
     const bool wide = (size_t)n > (size_t)grid_blocks(c, 4) * BM_BLOCK * 16;
-    const size_t span = (size_t)BM_BLOCK * (wide ? 32 : 16);
+    const bool dense = g.cls == GRAPH_MESH && !bm_thin(g);
+    const int threads = !dense || wide ? BM_BLOCK : (size_t)n >= 4096ull * c.num_cu ? 256 : 128;
+    const size_t span = (size_t)threads * (wide ? 32 : 16);
     const int G = (int)std::min(((size_t)n + span - 1) / span, (size_t)grid_blocks(c, 16));
     const size_t least = 2 * al256(nb) + al256(8ull * G) + al256(sizeof(BfsCtl));
     // a fixed scratch too small for the visited bitmap does without it
@@ -723,8 +732,9 @@ static void run_bfs_bitmap(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStr
         .add(depth, 0xFFFFFFFFu, (size_t)n)
         .add(a.mk[0], 0u, (2 * al256(nb) + (vis ? al256(nb / 8) : 0)) / 4)   // marks and bitmap (adjacent)
         .run(s);
-    // one thread per vertex: only where no vertex has a long row
-    const bool head = vis && g.cls == GRAPH_MESH;
+    // one thread per vertex: only where no vertex has a long row (64 neighbours on either side of 100,000
+    // vertices in a ring: 1,562 levels of 33 us in the head, 9 us as launches)
+    const bool head = vis && g.cls == GRAPH_MESH && !dense;
     if (head)
         hipLaunchKernelGGL(bfs_bitmap_head, dim3(1), dim3(BM_SOLO_BLOCK), 0, s, a, src);
     else
@@ -733,10 +743,12 @@ static void run_bfs_bitmap(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStr
     int32_t i = 0;
     auto launch = [&]() {
         c.ktimer.run("bfs_bitmap_level", s, [&]() {
-            const dim3 grid(G), block(BM_BLOCK);
-            if (!vis) hipLaunchKernelGGL((bfs_bitmap_level<32, false>), grid, block, 0, s, a, i);
-            else if (wide) hipLaunchKernelGGL((bfs_bitmap_level<32, true>), grid, block, 0, s, a, i);
-            else hipLaunchKernelGGL((bfs_bitmap_level<16, true>), grid, block, 0, s, a, i);
+            const dim3 grid(G), block(threads);
+            if (!vis) hipLaunchKernelGGL((bfs_bitmap_level<512, 32, false>), grid, block, 0, s, a, i);
+            else if (wide) hipLaunchKernelGGL((bfs_bitmap_level<512, 32, true>), grid, block, 0, s, a, i);
+            else if (threads == 512) hipLaunchKernelGGL((bfs_bitmap_level<512, 16, true>), grid, block, 0, s, a, i);
+            else if (threads == 256) hipLaunchKernelGGL((bfs_bitmap_level<256, 16, true>), grid, block, 0, s, a, i);
+            else hipLaunchKernelGGL((bfs_bitmap_level<128, 16, true>), grid, block, 0, s, a, i);
         });
         ++i;
     };
@@ -929,7 +941,7 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena
     // 212, 259 / 237, 325 / 211 and 549 / 234 us; of 40,000 with 8 and 12 entries
     // 120 / 140 and 151 / 134 us.
     const int fr = c.opt.bfs_frontier;
-    const bool thin = g.m <= 9ll * n, fits = !ar.fixed || need <= ar.fixed_bytes;
+    const bool thin = bm_thin(g), fits = !ar.fixed || need <= ar.fixed_bytes;
     if (c.opt.bfs_direction != 2 && (fr == 2 || (fr == 0 && g.cls == GRAPH_MESH && (thin || !fits)))) {
         run_bfs_bitmap(c, g, src, depth, s, ar);
         return;

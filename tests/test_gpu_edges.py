@@ -156,6 +156,43 @@ def _random_regular(n, deg, seed):
     return graphgen.from_edges(n, u, v)
 
 
+def _ring(n, side):
+    """Every vertex joined to `side` neighbours on either side."""
+    v = np.arange(n)
+    return graphgen.from_edges(n, np.tile(v, side), np.concatenate([(v + d) % n for d in range(1, side + 1)]))
+
+
+# rows of more than nine entries on average: work-groups of 2,048 vertices, 4,096 from 4,096 vertices per CU on
+LONG_ROWS = {   # name: (graph, source)
+    "span -1": (lambda: _random_regular(2047, 16, 1), 2046),
+    "span": (lambda: _random_regular(2048, 16, 2), 0),
+    "span +1": (lambda: _random_regular(2049, 16, 3), 2048),
+    "spans": (lambda: _random_regular(30011, 60, 4), 9),
+    "ring": (lambda: _ring(20000, 32), 777),
+    "larger spans -1": (lambda: _random_regular(1048575, 10, 5), 17),
+    "larger spans": (lambda: _random_regular(1048576, 10, 6), 1048575),
+    "larger spans +1": (lambda: _random_regular(1048577, 10, 7), 0),
+}
+
+
+@pytest.mark.parametrize("name", list(LONG_ROWS))
+def test_mark_byte_levels_over_long_rows(ctx, name):
+    make, src = LONG_ROWS[name]
+    row, col = make()
+    assert col.size > 9 * (row.size - 1)
+    g = ctx.graph_load_csr(row, col)
+    want = oracle.bfs(row, col, src)
+    ctx.set_option("bfs.frontier", 2)
+    try:
+        for _ in range(2):
+            assert np.array_equal(_host(ctx.bfs(g, src)), want)
+            assert ctx.stat("levels") == want.max() + 1
+    finally:
+        ctx.set_option("bfs.frontier", 0)
+    assert np.array_equal(_host(ctx.bfs(g, src)), want)
+    g.free()
+
+
 SSSP_MESHES = {   # name: (graph, source, largest weight, bucket width or 0 for the default)
     "span -1": (lambda: graphgen.from_edges(8191, np.arange(8190), np.arange(1, 8191)), 4000, 64, 0),
     "span": (lambda: graphgen.from_edges(8192, np.arange(8191), np.arange(1, 8192)), 8191, 64, 100),

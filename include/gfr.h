@@ -94,8 +94,7 @@ const char *gfr_last_error(const gfr_ctx *ctx);
  *   "bfs.dedup"       0 atomic claim (each vertex enqueued once), 1 idempotent (Sec. 4.5)
  *   "bfs.frontier"    0 auto, 1 queue levels (advance + compaction), 2 mark-byte levels:
  *                     the frontier is a byte per vertex, one launch per level, push
- *                     only (auto: mark bytes on mesh-class graphs of at most 9 entries per
- *                     vertex, unless pull is forced)
+ *                     only (auto: mark bytes on mesh-class graphs unless pull is forced)
  *   "sssp.pull_alpha" single-source SSSP direction (the pull advance of Sec. 4.5 applied to
  *                     SSSP): an iteration whose near queue carries more than m / alpha edges
  *                     relaxes by a pull sweep over every list (one pre-checked atomicMin per
@@ -214,8 +213,8 @@ gfr_status gfr_graph_info(gfr_ctx *ctx, gfr_graph g, int32_t *n, int64_t *m,
  * Breadth-first search (Sec. 5.1): depth_out[v] = hop distance from `source`,
  * depth_out[source] = 0, unreached vertices -1.  n int32 elements.
  * Level-synchronous advance + filter with a per-level push/pull choice; on
- * mesh-class graphs of at most 9 entries per vertex the frontier stays as mark
- * bytes, one launch per level (option "bfs.frontier").  The depths are the same either way.
+ * mesh-class graphs the frontier stays as mark bytes, one launch per level
+ * (option "bfs.frontier").  The depths are the same either way.
  * pred_out (n int32, may be NULL): a BFS tree read off the depths --
  * pred[source] = source, unreached -1, otherwise the first neighbour in v's
  * row one level up (the smallest such id when rows are sorted).

@@ -705,13 +705,19 @@ static void run_bfs_bitmap(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStr
     const int32_t n = g.n;
     const size_t nb = ((size_t)n + 63) / 64 * 64;
     // 32 vertices per thread where 16 would leave more spans than are resident (four groups per CU).
-    // Where rows are long a level is bound by how many of the CUs expand them, and spans of 8,192 vertices
-    // leave most of them idle: 2,048 vertices each, or 4,096 where those fill the chip.  Random regular
-    // graphs of 100,000 x 16, 100,000 x 64, 300,000 x 100, 1 M x 16 and 1 M x 32 entries, spans of 8,192 /
-    // 4,096 / 2,048: 213 / 160 / 147, 632 / 384 / 295, 1,057 / 565 / 468, 284 / 217 / 216 and 404 / 288 / 283 us.
+    // Where rows are long a level is bound by how many of the CUs expand them.  On graphs numbered along
+    // their edges a frontier is a few spans at any size; on others it is everywhere, and spans of 8,192
+    // vertices leave most CUs idle: 2,048 vertices each, or 4,096 where those fill the chip.  Spans of 8,192 /
+    // 4,096 / 2,048: random regular graphs of 100,000 x 16, 100,000 x 64, 300,000 x 100 and 1 M x 32 entries 213 /
+    // 160 / 147, 632 / 384 / 295, 1,057 / 565 / 468 and 404 / 288 / 283 us; squares with all neighbours within two
+    // steps of 100,000 and 1 M vertices 1,205 / 1,320 / 1,564 and 7,310 / 8,530 / 10,990 us; cubes with 26
+    // neighbours of 100,000, 300,000 and 1 M vertices (82, 62 and 31 % of the entries inside 8,192 ids) 646 / 732 /
+    // 904, 1,287 / 1,466 / 1,585 and 2,815 / 2,756 / 2,508.
     const bool wide = (size_t)n > (size_t)grid_blocks(c, 4) * BM_BLOCK * 16;
     const bool dense = g.cls == GRAPH_MESH && !bm_thin(g);
-    const int threads = !dense || wide ? BM_BLOCK : (size_t)n >= 4096ull * c.num_cu ? 256 : 128;
+    const bool near = g.near >= 0.6;
+    const int threads = !dense || wide || (near && n >= 32768) ? BM_BLOCK
+                        : near || (size_t)n >= 4096ull * c.num_cu ? 256 : 128;
     const size_t span = (size_t)threads * (wide ? 32 : 16);
     const int G = (int)std::min(((size_t)n + span - 1) / span, (size_t)grid_blocks(c, 16));
     const size_t least = 2 * al256(nb) + al256(8ull * G) + al256(sizeof(BfsCtl));
@@ -933,16 +939,15 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena
     const CompactGeom cg = compact_geom(nwords, c.num_cu);
     size_t need = 2 * al256(nwords * 4ull) + al256(nwords * 32ull) + 3 * al256(4ull * n) + al256(4 * nparts) +
                   al256(4ull * G) + al256(16ull * cg.blocks) + al256(sizeof(BfsCtl));
-    // Mark-byte levels (bfs.frontier 0 auto, 1 queue, 2 mark bytes) on mesh-like
-    // graphs whose rows one thread takes in a turn or two, and where a fixed
-    // scratch is too small for the queue; a forced pull direction needs the
-    // queue's frontier bitmap.  Random regular graphs of 1 M vertices with 8, 10,
-    // 12, 16, 20 and 32 entries each, marks / queue: 187 / 241, 257 / 242, 222 /
-    // 212, 259 / 237, 325 / 211 and 549 / 234 us; of 40,000 with 8 and 12 entries
-    // 120 / 140 and 151 / 134 us.
+    // Mark-byte levels (bfs.frontier 0 auto, 1 queue, 2 mark bytes) on mesh-like graphs; a forced pull
+    // direction needs the queue's frontier bitmap.  What decides is the number of levels, which is not
+    // known beforehand, and a queue level costs 20 us or more: cubes of 36,000, 300,000 and 3 M vertices
+    // with 26 neighbours each (31 to 128 levels) 420 / 680, 1,600 / 1,760 and 5,050 / 7,990 us (marks / queue),
+    // squares of 100,000 and 1 M vertices with 24 (106 and 334 levels) 1,205 / 3,620 and 7,310 / 20,300, random regular
+    // graphs of 1 M vertices with 10, 16 and 32 entries each (9, 8 and 6 levels) 208 / 262, 225 / 290 and
+    // 295 / 285; with 32 entries and 3 M vertices 870 / 425.
     const int fr = c.opt.bfs_frontier;
-    const bool thin = bm_thin(g), fits = !ar.fixed || need <= ar.fixed_bytes;
-    if (c.opt.bfs_direction != 2 && (fr == 2 || (fr == 0 && g.cls == GRAPH_MESH && (thin || !fits)))) {
+    if (c.opt.bfs_direction != 2 && (fr == 2 || (fr == 0 && g.cls == GRAPH_MESH))) {
         run_bfs_bitmap(c, g, src, depth, s, ar);
         return;
     }

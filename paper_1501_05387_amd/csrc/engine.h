@@ -159,7 +159,7 @@ struct Options {
     double bfs_alpha = 15.0;
     double bfs_beta = 18.0;
     int bfs_dedup = 0;          // 0 atomic, 1 idempotent
-    int bfs_frontier = 0;       // 0 auto (mark bytes on thin mesh-class graphs), 1 queue, 2 mark bytes
+    int bfs_frontier = 0;       // 0 auto (mark bytes on mesh-class graphs), 1 queue, 2 mark bytes
     int sssp_frontier = 0;      // 0 auto (mark bytes on mesh-class graphs), 1 queue, 2 mark bytes
     double sssp_pull_alpha = 0.0;   // single-source SSSP: pull sweep when the near queue's edges exceed m / alpha (0: never)
     double sssp_delta = 0.0;    // 0 -> sssp_delta_factor x mean edge weight

@@ -169,6 +169,9 @@ LONG_ROWS = {   # name: (graph, source)
     "span +1": (lambda: _random_regular(2049, 16, 3), 2048),
     "spans": (lambda: _random_regular(30011, 60, 4), 9),
     "ring": (lambda: _ring(20000, 32), 777),
+    "near, 4,096": (lambda: _ring(32767, 6), 32766),
+    "near, 8,192": (lambda: _ring(32768, 6), 8191),
+    "near, 8,192 +1": (lambda: _ring(40961, 6), 40960),
     "larger spans -1": (lambda: _random_regular(1048575, 10, 5), 17),
     "larger spans": (lambda: _random_regular(1048576, 10, 6), 1048575),
     "larger spans +1": (lambda: _random_regular(1048577, 10, 7), 0),

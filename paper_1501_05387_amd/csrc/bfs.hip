@@ -887,13 +887,19 @@ __global__ __launch_bounds__(BS_BLOCK) void bfs_small(BsmArgs a, int32_t src)
 // (128), 8,192 and 220 K 166 (120).  With the waits and compactions of today
 // 8,192 and 59 K 93 (103), 4,096 and 97 K 85 (89), and the level launches 114
 // and 100 beyond the line.  Rows of at most 16 entries (lattices) take
-// a thread each, and any number of them that fits the list: 33^2, 100^2 and
-// 181^2 81, 130 and 248 us (303, 441 and 656 before).
+// a thread each, and as many of them as fit the list while they take one turn
+// of eight entries: 33^2, 100^2 and 181^2 81, 130 and 248 us (303, 441 and 656
+// before).  Rows of two turns reach the line earlier: random regular graphs of 16,384
+// vertices with 10 and 16 entries each 143 and 147 us, of 24,576 193 and 196 (131 and
+// 139 by level launches), of 32,768 with 8 and 12 entries 165 and 242 (141 and 137).
+constexpr int64_t BS_TURNS = 49152;     // most vertices + entries / 8 with rows of two turns
 static bool bfs_small_fits(const Ctx &c, const Graph &g)
 {
     const Options &o = c.opt;
-    return g.n <= BS_MAX_N && (g.max_deg <= 16 || g.m + 16ll * g.n <= BS_COST) && o.bfs_direction != 2 &&
-           o.bfs_frontier == 0 && o.advance_mapping == 1 && !o.step_graphs;
+    const bool fits = g.max_deg <= 8 || (g.max_deg <= 16 && g.n + g.m / 8 <= BS_TURNS) ||
+                      g.m + 16ll * g.n <= BS_COST;
+    return g.n <= BS_MAX_N && fits && o.bfs_direction != 2 && o.bfs_frontier == 0 && o.advance_mapping == 1 &&
+           !o.step_graphs;
 }
 
 static void run_bfs_small(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s)

@@ -438,6 +438,23 @@ def test_small_graph_bfs(ctx, name):
     g.free()
 
 
+@pytest.mark.parametrize("n, side, one_group", [(32768, 4, True), (32769, 4, False), (19661, 6, True),
+                                                (19662, 6, False), (16384, 8, True), (16385, 8, False)])
+def test_small_graph_bfs_line_by_row_length(ctx, n, side, one_group):
+    """One work-group as long as the entries it walks alone are few; the one-launch levels report no edges."""
+    import paper_1501_05387_amd as gfr
+    row, col = _ring(n, side)
+    g = ctx.graph_load_csr(row, col)
+    for src in (0, n - 1):
+        assert np.array_equal(_host(ctx.bfs(g, src)), oracle.bfs(row, col, src))
+        if one_group:
+            assert ctx.stat("edges_inspected") == col.size and ctx.stat("launches") == 1
+        else:
+            with pytest.raises(gfr.GfrError):
+                ctx.stat("edges_inspected")
+    g.free()
+
+
 # what the queue levels and iterations report, and so every path that is taken in their place
 BFS_STATS = ["levels", "push_levels", "pull_levels", "edges_inspected", "push_entries", "push_edges", "push_new",
              "pull_unvisited", "pull_inspected", "pull_new", "launches", "solves", "kernel_ms"]

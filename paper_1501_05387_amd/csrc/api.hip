@@ -611,8 +611,8 @@ static void with_pred(Ctx &c, Graph &g, int32_t *pred_out, hipStream_t s, Run ru
     c.arena.reserve((dev ? 0 : al256(4ull * g.n)) + pred_scratch_bytes(g));   // the solve's scratch is no longer needed
     if (!dev) pd = c.arena.take<int32_t>(g.n);
     run(pd);
-    c.waited = false;
     if (!dev) deliver(c, pred_out, pd, 4ull * g.n, s);
+    c.waited = !dev;   // (deliver waits)
 }
 
 extern "C" {

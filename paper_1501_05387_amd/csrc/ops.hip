@@ -382,12 +382,12 @@ int64_t run_filter(Ctx &c, Graph &g, const int32_t *items, int64_t count, const 
         GFR_HIP(hipMemcpyAsync(excl_dev, exclude, (size_t)n, hipMemcpyHostToDevice, s));
         exclude = excl_dev;
     }
+    // (a copy from pageable memory waits for what is queued before it, so it comes first)
+    const int32_t *X = count > 0 ? device_list(items, count, staging, s) : nullptr;
     Fills().add(mark, 0u, (n + 3) / 4).add(bad, 0u, 1).run(s);
-    if (count > 0) {
-        const int32_t *X = device_list(items, count, staging, s);
+    if (count > 0)
         hipLaunchKernelGGL(mark_items, list_grid(c, count), dim3(GFR_BLOCK), 0, s, X, count, n, exclude, mark,
                            bad);
-    }
     const ListEmit emit{out};
     run_tiles(MarkVal{mark, bad}, n, totals, grand, Gate{ANY, (unsigned long long)out_cap}, &emit, s);
     const int64_t kept = (int64_t)grand_back(c, grand, s, "filter").tot.b;

@@ -202,6 +202,7 @@ void run_two_hop(Ctx &c, Graph &g, const int32_t *seeds, int32_t k, uint64_t *co
     }
     GFR_LAUNCH_CHECK();
     qb.check(c, s, "two_hop");
+    c.waited = true;
     c.stats.v["pull_levels"] = pull ? 1.0 : 0.0;
     c.stats.v["edges_inspected"] = (double)mf1 + (pull ? (double)g.m : (double)mf2);
     c.stats.v["middle_vertices"] = (double)c.pinned[3];
@@ -371,6 +372,7 @@ void run_bipartite_rank(Ctx &c, Graph &g, int32_t nl, int32_t iters, bool walk, 
     qb.check(c, s, walk ? "salsa" : "hits");
     deliver(c, hub, hub_dev, 8ull * nl, s);
     deliver(c, auth, auth_dev, 8ull * (n - nl), s);
+    c.waited = true;
     c.stats.v["iterations"] = iters;
 }
 

@@ -123,8 +123,9 @@ const char *gfr_last_error(const gfr_ctx *ctx);
  *                     16 bits first; 3 try 8 bits first.  A batch whose distances outgrow its rows
  *                     is solved again with rows twice as wide; results do not change
  *   "batch.blocks_per_cu"  batched SSSP relaxation grid: work-groups per CU (default 64, at
- *                     most 64, and never more than one per 1024 edges of the graph), 0 = as
- *                     many as are resident at once
+ *                     most 64, and never more than one per 1024 edges of the graph; on graphs of
+ *                     less than 2^22 entries one per 256 edges and at most 16), 0 = as many as
+ *                     are resident at once
  *   "batch.pair"      batched SSSP with 32-bit rows: 1 relaxes two edges per distance-row
  *                     load (each half-wave one edge), 0 (default) one edge per load
  *   "batch.pending"   batched SSSP: 1 (default) a queued vertex also relaxes the queries improved

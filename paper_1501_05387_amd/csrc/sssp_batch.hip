@@ -1299,10 +1299,13 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
     // sizes the per-work-group partials.
     const int bpc = c.opt.batch_blocks_per_cu;
     const int gcap = (int)std::min<int64_t>(64ll * c.num_cu, std::max<int64_t>(c.num_cu, g.m / chunk + 1));
-    // (small chunks: eight groups per CU.  A mesh runs hundreds of thin launches,
-    // whose idle groups cost it 16.9 ms per 24-query batch on the 1000^2 lattice
-    // with a group per chunk, 13.4 ms so.)
-    const int gfine = 8 * c.num_cu;
+    // (small chunks: at most sixteen groups per CU, eight with rows of 32 words.
+    // A mesh runs hundreds of thin launches, whose idle groups cost it 16.9 ms per
+    // 24-query batch on the 1000^2 lattice with a group per chunk, 13.4 ms with
+    // eight per CU.  48 and 64 queries there, one bucket: 27.5 and 30.8 ms with
+    // eight, 25.1 and 27.8 with sixteen; R-MAT of 100,003 vertices 1,167 and 1,198 us,
+    // 1,060 and 1,115; 24 queries 735 and 754.)
+    const int gfine = 16 * c.num_cu, ghalf = 8 * c.num_cu;
     auto grid_of = [&](const void *relax, const void *pull) {
         const int cap = fine ? std::min(gcap, gfine) : gcap;
         return std::min(cap, std::max(resident_grid(c, relax, bpc), resident_grid(c, pull, bpc)));
@@ -1402,7 +1405,7 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
             compact();   // queue of the sources
             GFR_LAUNCH_CHECK();
             auto launch = [&]() {
-                const int Gb = Gw[bits == 8 ? 0 : bits == 16 ? 1 : 2];
+                const int Gf = Gw[bits == 8 ? 0 : bits == 16 ? 1 : 2], Gb = half && fine ? std::min(Gf, ghalf) : Gf;
                 c.ktimer.run("bsssp_relax", s, [&]() {
                     if (half && fine)
                         hipLaunchKernelGGL(bsssp_relax_half<256>, dim3(Gb), dim3(GFR_BLOCK), 0, s, a);

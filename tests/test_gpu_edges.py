@@ -156,6 +156,30 @@ def _random_regular(n, deg, seed):
     return graphgen.from_edges(n, u, v)
 
 
+@pytest.mark.parametrize("name", list(MESHES))
+def test_mark_byte_levels_of_small_graphs(ctx, name):
+    """The one-launch levels themselves, also where one work-group would walk the whole graph."""
+    import paper_1501_05387_amd as gfr
+    make, src = MESHES[name]
+    row, col = make()
+    g = ctx.graph_load_csr(row, col)
+    want = oracle.bfs(row, col, src)
+    ctx.set_option("bfs.frontier", 2)
+    try:
+        for _ in range(2):
+            out = ctx.bfs(g, src)
+            assert np.array_equal(_host(out), want)
+            assert ctx.stat("levels") == want.max() + 1
+            with pytest.raises(gfr.GfrError):   # (one work-group reports them)
+                ctx.stat("edges_inspected")
+        assert np.array_equal(_host(ctx.bfs_noalloc(g, src, out)), want)
+        with pytest.raises(gfr.GfrError):
+            ctx.stat("edges_inspected")
+    finally:
+        ctx.set_option("bfs.frontier", 0)
+        g.free()
+
+
 def _ring(n, side):
     """Every vertex joined to `side` neighbours on either side."""
     v = np.arange(n)

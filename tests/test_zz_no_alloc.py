@@ -58,6 +58,35 @@ def test_noalloc_matches_bfs_twice_second_smaller(ctx, kind):
         assert np.array_equal(got, oracle.bfs(row, col, src)), (kind, call)
 
 
+# calls in a row whose traversals use the scratch: queue levels, mark-byte levels, and one after the other
+STALE = {
+    "queue": [("rmat", 16, 1), ("rmat", 14, 1), ("rmat", 11, 1), ("grid", 40, 1)],
+    "marks": [("grid", 400, 2), ("grid", 200, 2), ("grid", 40, 2), ("rmat", 9, 2)],
+    "mixed": [("grid", 400, 2), ("rmat", 14, 1), ("grid", 300, 0), ("rmat", 15, 0), ("grid", 50, 2)],
+}
+
+
+@pytest.mark.parametrize("name", list(STALE))
+def test_noalloc_over_another_calls_scratch(ctx, name):
+    """Each call finds what the one before left in the fixed scratch (small graphs by themselves would not touch it)."""
+    import torch
+    for call, (kind, size, frontier) in enumerate(STALE[name]):
+        row, col = getattr(graphgen, kind)(size)
+        src = int(graphgen.sample_sources(row, col, 1, seed=21 + call)[0])
+        _say("bfs_noalloc", name, "call", call, kind, size, "frontier", frontier, "source", src)
+        g = ctx.graph_load_csr(row, col)
+        ctx.set_option("bfs.frontier", frontier)
+        try:
+            for source in (src, int(np.argmax(np.diff(row)))):
+                out = torch.full((row.size - 1,), 7, dtype=torch.int32, device="cuda:0")
+                got = ctx.bfs_noalloc(g, source, out).cpu().numpy()
+                assert np.array_equal(got, oracle.bfs(row, col, source)), (kind, size, frontier)
+                assert ctx.stat("launches") > 1   # (one work-group takes one)
+        finally:
+            ctx.set_option("bfs.frontier", 0)
+            g.free()
+
+
 def test_noalloc_rejects_host_output_and_bad_source(ctx):
     import paper_1501_05387_amd as gfr
     import torch

@@ -51,8 +51,8 @@ def kernel_source_digest(files=None) -> str:
 # Everything the batched relaxation kernel is compiled from: its source file,
 # the headers it includes and the build flags.  A counter figure taken for
 # that kernel stays valid while these are unchanged.
-RELAX_SOURCES = ["csrc/sssp_batch.hip", "csrc/compact.h", "csrc/device.h", "csrc/engine.h",
-                 "../include/gfr.h", "build.py"]
+RELAX_SOURCES = ["csrc/sssp_batch.hip", "csrc/compact.h", "csrc/device.h", "csrc/engine.h", "csrc/entries.h",
+                 "csrc/batches.h", "csrc/error.h", "csrc/nearness.h", "csrc/spare.h", "../include/gfr.h", "build.py"]
 
 
 def relax_source_digest() -> str:

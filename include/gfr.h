@@ -192,9 +192,12 @@ gfr_status gfr_validate_csr(int32_t n, int64_t m, const int32_t *row_offsets,
  * must be undirected, i.e. stored symmetrically, as every graph the paper
  * evaluates is (Sec. 6).  The arrays are host memory and are copied; the
  * caller may free them on return.  `weights` may be NULL (SSSP then fails).
- * Rejected with GFR_E_INVALID: n <= 0, m < 0, m >= 2^31, R[0] != 0,
+ * Rejected with GFR_E_INVALID: n <= 0, m < 0, m >= 2^31 - 1, R[0] != 0,
  * R[n] != m, decreasing offsets, column ids outside [0,n); with GFR_VALIDATE
  * also the symmetric/simple checks of gfr_validate_csr.
+ * Scale-free graphs of 2^23 entries or more also get 4 bytes per vertex that the
+ * pull levels of a BFS read first (0.9 ms for 128 M entries; left out if memory
+ * is short).
  * On success *out receives a handle owned by the context.
  */
 gfr_status gfr_graph_load_csr(gfr_ctx *ctx, int32_t n, int64_t m, const int32_t *row_offsets,
@@ -215,7 +218,12 @@ gfr_status gfr_graph_info(gfr_ctx *ctx, gfr_graph g, int32_t *n, int64_t *m,
  * depth_out[source] = 0, unreached vertices -1.  n int32 elements.
  * Level-synchronous advance + filter with a per-level push/pull choice; on
  * mesh-class graphs the frontier stays as mark bytes, one launch per level
- * (option "bfs.frontier").  The depths are the same either way.
+ * (option "bfs.frontier").  Graphs of at most 32,768 vertices and few entries
+ * (m + 16 n <= 196,608, or rows of at most 8, or of 16 while n + m / 8 <= 49,152)
+ * are pushed by one work-group in one launch while bfs.frontier, bfs.direction,
+ * advance.mapping and graph.steps are at their defaults or the direction is 1;
+ * bfs.alpha, bfs.beta, bfs.dedup and advance.chunk mean nothing there.  The
+ * depths are the same either way.
  * pred_out (n int32, may be NULL): a BFS tree read off the depths --
  * pred[source] = source, unreached -1, otherwise the first neighbour in v's
  * row one level up (the smallest such id when rows are sorted).
@@ -273,8 +281,11 @@ gfr_status gfr_bc(gfr_ctx *ctx, gfr_graph g, const int32_t *sources, int32_t k, 
 /*
  * Connected components (Sec. 5.4): label_out[v] = smallest vertex id of v's
  * component (n int32 elements); *num_components_out (host pointer, may be
- * NULL) = number of components.  Hooking over an edge frontier that is
- * filtered each round, then pointer jumping.
+ * NULL) = number of components.  Every vertex hooks along its first two
+ * neighbours, then the vertices outside the largest component (told from a
+ * sample of the labels) along all of theirs, with pointer jumping after each
+ * step.  Vertices of that component rely on their neighbours' entries for them,
+ * so an entry without its reverse may be missed.
  */
 gfr_status gfr_cc(gfr_ctx *ctx, gfr_graph g, int32_t *label_out, int32_t *num_components_out,
                   gfr_stream stream);

@@ -17,6 +17,10 @@
 // lists skips every vertex that carries it: an edge between such a vertex and
 // another component is hooked from the other side (graphs are stored
 // symmetrically).  The sample only decides what is skipped, never the result.
+// Hooking few neighbours first and leaving out the sampled component is the
+// neighbour sampling of Sutton, Ben-Nun and Barak (Afforest, IPDPS 2018); climbs
+// that write back the ancestors they reach are known from Jaiganesh and
+// Burtscher (ECL-CC, HPDC 2018).
 //
 // Two sweeps over all edges, hooking with atomicMin, took 3.0 ms each on the
 // 3001^2 lattice (35 M entries) and the call 6.6 ms.  This

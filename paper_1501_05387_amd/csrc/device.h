@@ -33,7 +33,6 @@ __device__ __forceinline__ uint64_t shfl_u64(uint64_t x, int src)
     return ((uint64_t)hi << 32) | lo;
 }
 
-// inclusive prefix sum across the wave
 // x of another lane by DPP (no trip through LDS); 0 where there is none.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t x)
@@ -41,7 +40,7 @@ __device__ __forceinline__ uint32_t dpp_u32(uint32_t x)
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
 }
 
-// Inclusive scan over the wave, by DPP: the steps are a chain, and one through
+// Inclusive prefix sum over the wave, by DPP: the steps are a chain, and one through
 // LDS (a shuffle) takes several times as long.  With shuffles in the scans the
 // gather sweeps of four BC sources on R-MAT with 1 M vertices took 1,666 us,
 // 1,597 so.

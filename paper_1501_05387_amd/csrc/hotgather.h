@@ -70,7 +70,8 @@ __global__ __launch_bounds__(HG_BLOCK) void gather_hot(HotGraph g, const T *tabl
     // the loads would have to wait for them where it joins)
     auto columns = [&](Chunk &x, uint32_t at) __attribute__((always_inline)) {
         at = min(at, g.nch - 1u);
-        // read once, so not kept in L2 (without the hint 322 us against 314 a sweep)
+        // read once, so not kept in L2 (without the hint 322 us against 314, averaged over all launches of a call,
+        // those after its end among them)
         x.col = __builtin_nontemporal_load((const vec4 *)(g.C + (size_t)at * HG_CH + k));
         x.word = g.starts[at * (HG_CH / 32) + k / 32];
         x.base = g.entry[at];

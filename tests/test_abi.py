@@ -169,6 +169,16 @@ def test_bench_traffic_digest_covers_existing_sources():
     assert bench.relax_source_digest() != bench.kernel_source_digest()
 
 
+def test_bench_traffic_digest_covers_the_headers_of_its_headers():
+    import bench
+    pkg = os.path.join(ROOT, "paper_1501_05387_amd")
+    covered = {os.path.basename(f) for f in bench.RELAX_SOURCES}
+    for f in bench.RELAX_SOURCES:
+        if f.endswith((".h", ".hip")):
+            for h in re.findall(r'#include "([^"]+)"', open(os.path.join(pkg, f)).read()):
+                assert os.path.basename(h) in covered, (f, h)
+
+
 def test_bench_sssp_floor_bytes_counts_each_reached_pair_once():
     """The batched relaxation's algorithmic bytes (the SSSP work model at
     r = 1) equal, summed per query and per reached vertex, 16 B for its

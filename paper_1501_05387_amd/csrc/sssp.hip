@@ -747,7 +747,7 @@ __global__ __launch_bounds__(BLOCK) void sssp_mark_level(SmArgs a, int32_t L, in
                     uint32_t wt[8], d[8];
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
-                        const uint32_t ek = entry_or_last(e, k, e1);
+                        const int32_t ek = entry_or_last(e, k, e1);
                         u[k] = a.C[ek];
                         wt[k] = a.W[ek];
                     }

@@ -20,8 +20,9 @@ constexpr bool walk(uint32_t begin, uint32_t end, uint32_t step)
     for (uint32_t e = begin; e < end; e += step) {
         if (++turns > 1000) return false;
         for (uint32_t k = 0; k < step; ++k) {
-            const uint32_t i = entry_or_last(e, k, end);
-            if (i < begin || i >= end) return false;
+            const int32_t at = entry_or_last(e, k, end);
+            const uint32_t i = (uint32_t)at;
+            if (at < 0 || i < begin || i >= end) return false;
             if (e + k < end && i != next++) return false;
         }
     }

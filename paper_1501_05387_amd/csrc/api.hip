@@ -75,6 +75,26 @@ static void *noalloc_scratch(int device)
     return ptr;
 }
 
+// Each device's context whose compactions start in order (Ctx::in_order): the
+// first one that finds none, until it is destroyed.
+static std::mutex order_mu;
+static std::map<int, const Ctx *> order_of;
+
+static void claim_order(Ctx &c)
+{
+    std::lock_guard<std::mutex> lk(order_mu);
+    c.in_order = order_of.emplace(c.device, &c).second;
+}
+
+static bool release_order(Ctx &c)   // false: it was not this context
+{
+    std::lock_guard<std::mutex> lk(order_mu);
+    if (!c.in_order) return false;
+    order_of.erase(c.device);
+    c.in_order = false;
+    return true;
+}
+
 // true if p is device memory of `device`
 static bool is_device_ptr_on(const void *p, int device)
 {
@@ -343,7 +363,11 @@ static gfr_status guard(gfr_ctx *ctx, F f)
     try {
         c.err.clear();
         GFR_HIP(hipSetDevice(c.device));
-        with_room([&]() { f(c); }, [&]() { return give_back_spares(c); });
+        const auto in_turn = [&]() {
+            call_again_if([&]() { f(c); },
+                          [&](const Error &e) { return e.crowded && release_order(c); });   // another process's
+        };
+        with_room(in_turn, [&]() { return give_back_spares(c); });
         return GFR_OK;
     } catch (const Error &e) {
         c.err = e.msg;
@@ -651,6 +675,7 @@ gfr_status gfr_ctx_create(int32_t device, const char *tuning_json, gfr_ctx **out
         GFR_HIP(hipStreamCreateWithFlags(&cc.stream, hipStreamDefault));
         cc.noalloc_scratch = noalloc_scratch(device);
         alloc_pinned(cc);
+        claim_order(cc);
         GFR_HIP(hipEventCreate(&cc.ev0));
         GFR_HIP(hipEventCreate(&cc.ev1));
         cc.zero_word.alloc(256);
@@ -675,6 +700,7 @@ gfr_status gfr_ctx_destroy(gfr_ctx *ctx)
     Ctx *c = (Ctx *)ctx;
     (void)hipSetDevice(c->device);
     serve_shutdown(*c);
+    release_order(*c);
     c->graphs.clear();
     c->step_graphs.clear();
     c->arena.mem.release();

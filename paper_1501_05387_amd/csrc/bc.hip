@@ -51,7 +51,7 @@ struct BcCtl {
     uint32_t done;           // first word: read back by the host
     uint32_t levels;         // levels found
     uint32_t pull;           // the next discovery pulls
-    uint32_t parity, err;    // of the compaction
+    uint32_t parity, err, ticket;    // of the compaction
     uint32_t force;          // 0 auto, 1 push, 2 pull
     uint32_t push_levels, pull_levels;
     double mu, prev_nf;      // edges of unvisited vertices; size of the level before
@@ -340,7 +340,8 @@ void run_bc(Ctx &c, Graph &g, const int32_t *sources, int32_t k, float *bc, hipS
             if (L > n) return;   // (there are at most n levels)
             hipLaunchKernelGGL(bc_discover<GATHER_CH>, grid, block, 0, s, a, n, q, lv, ctl, fb, L, mark);
             hipLaunchKernelGGL(compact_kernel<BcMarks>, dim3(cg.blocks), block, 0, s, a.R, n, nwords, cg.wpt,
-                               BcMarks{mark, a.vis, fb, lv, ctl, L, n}, q, GATHER_CH, status, &ctl->parity, &ctl->err);
+                               BcMarks{mark, a.vis, fb, lv, ctl, L, n}, q, GATHER_CH, status, &ctl->parity, &ctl->err,
+                               c.in_order ? nullptr : &ctl->ticket);
             const BcLevel *x = lv + L + 1;
             const QueueAt at{&x->start};
             hipLaunchKernelGGL((gather_chunks<GATHER_CH, SigmaOp, SigmaFin>), grid, block, 0, s, q, &x->nf, &x->mf,
@@ -352,7 +353,7 @@ void run_bc(Ctx &c, Graph &g, const int32_t *sources, int32_t k, float *bc, hipS
         const int32_t hint = g.bc_levels_hint.load(std::memory_order_relaxed);
         run_until_done(c, &ctl->done, 1u, hint + hint / 32, (int64_t)n + 8, s, launch, sizeof(BcCtl));
         memcpy(&h, c.pinned, sizeof h);
-        if (h.err) fail(GFR_E_DEVICE, "bc: frontier compaction look-back timed out");
+        if (h.err) fail_crowded("bc");
         g.bc_levels_hint.store((int32_t)h.levels, std::memory_order_relaxed);
         used = h.levels + 1;
         levels_total += (double)h.levels;

@@ -57,6 +57,7 @@ struct BfsCtl {
     float alpha, beta;
     uint32_t parity;    // status-buffer parity of the compaction
     uint32_t err;       // compaction look-back gave up (never expected)
+    uint32_t ticket;    // of the compaction
     uint32_t push_levels, pull_levels;
     // traffic model counters (summed over levels)
     unsigned long long push_entries, push_edges, push_new;
@@ -462,6 +463,7 @@ struct BfsFirst {
             ctl->beta = beta;
             ctl->parity = 0;
             ctl->err = 0;
+            ctl->ticket = 0;
             ctl->push_levels = ctl->pull_levels = 0;
             ctl->push_entries = ctl->push_edges = ctl->push_new = 0ull;
             ctl->pull_unvisited = ctl->pull_inspected = ctl->pull_new = 0ull;
@@ -1003,7 +1005,8 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena
         });
         c.ktimer.run("bfs_compact", s, [&]() {
             hipLaunchKernelGGL(compact_kernel<BfsMarks>, dim3(cg.blocks), dim3(GFR_BLOCK), 0, s, a.R, n, nwords,
-                               cg.wpt, marks, a.q, chunk, status, &a.ctl->parity, &a.ctl->err);
+                               cg.wpt, marks, a.q, chunk, status, &a.ctl->parity, &a.ctl->err,
+                               c.in_order ? nullptr : &a.ctl->ticket);
         });
     };
     // (no captured steps over fixed scratch: instantiating a graph may allocate)
@@ -1014,7 +1017,7 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena
                                             ar.fixed ? nullptr : &key);
     BfsCtl h;
     memcpy(&h, c.pinned, sizeof(BfsCtl));
-    if (h.err) fail(GFR_E_DEVICE, "bfs: frontier compaction look-back timed out");
+    if (h.err) fail_crowded("bfs");
     c.stats.v["levels"] += h.level;
     c.stats.v["push_levels"] += h.push_levels;
     c.stats.v["pull_levels"] += h.pull_levels;

@@ -13,10 +13,11 @@
 // thread the row offsets stay in LDS); a block scan and a decoupled look-back
 // across work-groups give every thread its global slot and edge offset; pass 2
 // stages the group's entries in LDS and writes (vertex, edge offset, row start)
-// contiguously, plus the chunk index used by the load-balanced advance.  No counter is shared by all work-groups (on
-// MI355X same-address atomics serialise at ~11 ns each): the only
-// cross-group traffic is one 64-bit status word per work-group, and the last
-// work-group, which learns the grand totals, runs the caller's control.
+// contiguously, plus the chunk index used by the load-balanced advance.  Cross-group
+// traffic is one 64-bit status word per work-group and, where other streams may
+// compact at the same time, one ticket (scan_place): on MI355X same-address
+// atomics serialise at ~11 ns each.  The last work-group, which learns the grand
+// totals, runs the caller's control.
 //
 // Status words (one per work-group, two parity buffers): flag in bits 62-63
 // (1 = aggregate of this group, 2 = inclusive prefix), entry count in bits
@@ -112,11 +113,10 @@ __device__ __forceinline__ unsigned long long block_excl_scan_u64(unsigned long 
 // Work-group exclusive prefix by decoupled look-back (wave 0; the other waves
 // receive it through LDS).  Every wait is bounded, so the kernel always ends;
 // if a bound is ever exhausted *err is set and the results are flagged bad.
-__device__ __forceinline__ unsigned long long lookback_prefix(unsigned long long *status, unsigned long long agg,
-                                                              uint32_t *err)
+__device__ __forceinline__ unsigned long long lookback_prefix(int b, unsigned long long *status,
+                                                              unsigned long long agg, uint32_t *err)
 {
     __shared__ unsigned long long s_prefix;
-    const int b = blockIdx.x;
     if (threadIdx.x < 64) {
         const int lane = lane_id();
         if (b == 0) {
@@ -295,6 +295,32 @@ __device__ __forceinline__ void chunk_starts(const uint32_t *o, uint32_t cnt, ui
     }
 }
 
+// This work-group's place in the scan.  A group waits for those before it, so
+// they have to be running or over.  Alone on the device the groups of one launch
+// are, in the order of their ids.  Beside another stream's compaction they need
+// not be: every XCD starts its own share of a grid, one grid fills the chip (59
+// KB of LDS, two groups per CU), and where one XCD is full of the groups of one
+// grid and another of the other's, each waits for a group that cannot start: a
+// query in service then failed after the 2.2 s that the bound of the wait takes.
+// With a ticket (0 before the launch and after it) the place is the number of the
+// group's start: whoever has a smaller one has started, and waits for nobody with
+// a larger one.  The ticket costs 1 us a launch (BFS of R-MAT with 4 M vertices
+// 279 us, 270 without; four sources of BC on 1 M 2,366 and 2,352), so the one
+// context whose calls cannot meet another compaction goes without (Ctx::in_order).
+__device__ __forceinline__ uint32_t scan_place(uint32_t *ticket)
+{
+    if (!ticket || gridDim.x == 1) return blockIdx.x;
+    __shared__ uint32_t s_place;
+    if (threadIdx.x == 0) {
+        const uint32_t t = atomicAdd(ticket, 1u);
+        if (t == gridDim.x - 1)   // the last to start
+            __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_place = t;
+    }
+    __syncthreads();
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)s_place);
+}
+
 // Compaction kernel.  M: functor with
 //     bool skip() const                  whole launch is a no-op (uniform)
 //     uint32_t mask(uint32_t w)          marks of vertices 32w..32w+31 (may consume / update state)
@@ -305,13 +331,14 @@ template <class M>
 __global__ __launch_bounds__(GFR_BLOCK) void compact_kernel(const int32_t *R, int32_t n, uint32_t nwords,
                                                             uint32_t wpt, M mk, FrontierQ q, uint32_t chunk,
                                                             unsigned long long *status2, const uint32_t *parity,
-                                                            uint32_t *err)
+                                                            uint32_t *err, uint32_t *ticket)
 {
     if (mk.skip()) return;
     q = placed(mk, q, 0);
     const uint32_t p = *parity;
     unsigned long long *status = status2 + (size_t)p * gridDim.x;
-    const uint32_t w0 = (blockIdx.x * GFR_BLOCK + threadIdx.x) * wpt;
+    const uint32_t place = scan_place(ticket);
+    const uint32_t w0 = (place * GFR_BLOCK + threadIdx.x) * wpt;
     uint32_t words[COMPACT_MAX_WPT];
     uint32_t cnt = 0, edges = 0;
 #pragma unroll
@@ -340,7 +367,7 @@ __global__ __launch_bounds__(GFR_BLOCK) void compact_kernel(const int32_t *R, in
     unsigned long long btot;
     const unsigned long long mine = ((unsigned long long)cnt << 31) | edges;
     const unsigned long long excl = block_excl_scan_u64(mine, &btot);
-    const unsigned long long base = lookback_prefix(status, btot, err);
+    const unsigned long long base = lookback_prefix((int)place, status, btot, err);
     const uint32_t bcnt = (uint32_t)(btot >> 31);
     const uint32_t slot0 = (uint32_t)(base >> 31);
     uint32_t eoff = (uint32_t)(base & 0x7FFFFFFFull);   // edge offset of the next staged entry
@@ -444,8 +471,8 @@ __global__ __launch_bounds__(GFR_BLOCK) void compact_kernel(const int32_t *R, in
         __syncthreads();
     }
     // clear this group's slot of the other parity for the next launch
-    if (threadIdx.x == 0) status2[(size_t)(p ^ 1u) * gridDim.x + blockIdx.x] = 0ull;
-    if (blockIdx.x == gridDim.x - 1) {   // whole group: control may reduce per-group partials
+    if (threadIdx.x == 0) status2[(size_t)(p ^ 1u) * gridDim.x + place] = 0ull;
+    if (place == gridDim.x - 1) {   // whole group: control may reduce per-group partials
         __atomic_thread_fence(__ATOMIC_ACQUIRE);   // see the side results of partial()
         const unsigned long long all = base + btot;
         mk.control((uint32_t)(all >> 31), (uint32_t)(all & 0x7FFFFFFFull));

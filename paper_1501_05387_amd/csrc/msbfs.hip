@@ -46,7 +46,7 @@ struct MsCtl {
     uint32_t nf, mf;
     uint32_t parity, err;
     float alpha;       // pull when frontier edges > m / alpha
-    uint32_t pad;
+    uint32_t ticket;   // of the compaction
     unsigned long long m;
     unsigned long long push_edges, pull_levels, push_levels;
     unsigned long long allq;     // sources (lanes) in use
@@ -399,6 +399,7 @@ __global__ void msbfs_init(MsArgs a, Sources64 src, float alpha)
         ctl->nf = ctl->mf = 0;
         ctl->parity = 0;
         ctl->err = 0;
+        ctl->ticket = 0;
         ctl->alpha = alpha;
         ctl->m = (unsigned long long)a.R[a.n];
         ctl->push_edges = ctl->pull_levels = ctl->push_levels = 0ull;
@@ -474,7 +475,8 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
             });
             c.ktimer.run("msbfs_compact", s, [&]() {
                 hipLaunchKernelGGL(compact_kernel<MsMarks>, dim3(cg.blocks), dim3(GFR_BLOCK), 0, s, a.R, n, nwords,
-                                   cg.wpt, MsMarks{a}, a.q, chunk, status, &a.ctl->parity, &a.ctl->err);
+                                   cg.wpt, MsMarks{a}, a.q, chunk, status, &a.ctl->parity, &a.ctl->err,
+                                   c.in_order ? nullptr : &a.ctl->ticket);
             });
         };
         StepKey key("msbfs");
@@ -488,7 +490,7 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
                        (int64_t)n + 8, s, launch, sizeof(MsCtl), &key, output);
         MsCtl h;
         memcpy(&h, c.pinned, sizeof(MsCtl));
-        if (h.err) fail(GFR_E_DEVICE, "bfs_batch: frontier compaction look-back timed out");
+        if (h.err) fail_crowded("bfs_batch");
         g.msbfs_levels_hint.store(h.level, std::memory_order_relaxed);
         levels += h.level;
         pull_levels += (double)h.pull_levels;
@@ -547,6 +549,7 @@ __global__ void ms_session_init(MsArgs a, float alpha)
     ctl->nf = ctl->mf = 0;
     ctl->parity = 0;
     ctl->err = 0;
+    ctl->ticket = 0;
     ctl->alpha = alpha;
     ctl->m = (unsigned long long)a.R[a.n];
     ctl->push_edges = ctl->pull_levels = ctl->push_levels = 0ull;
@@ -679,7 +682,7 @@ struct MsSession final : LaneSession {
         hipLaunchKernelGGL(msbfs_level<GATHER_CH>, dim3(G), dim3(GFR_BLOCK), 0, stream, a);
         hipLaunchKernelGGL(msbfs_finalize, dim3(G), dim3(GFR_BLOCK), 0, stream, a);
         hipLaunchKernelGGL(compact_kernel<MsMarks>, dim3(cg.blocks), dim3(GFR_BLOCK), 0, stream, a.R, a.n, nwords,
-                           cg.wpt, MsMarks{a}, a.q, 1024u, status, &a.ctl->parity, &a.ctl->err);
+                           cg.wpt, MsMarks{a}, a.q, 1024u, status, &a.ctl->parity, &a.ctl->err, &a.ctl->ticket);
         GFR_LAUNCH_CHECK();
         GFR_HIP(hipMemcpyAsync(pin, a.ctl, sizeof(MsCtl), hipMemcpyDeviceToHost, stream));
     }

@@ -391,6 +391,7 @@ struct PfCtl {
     uint32_t nf, mf;     // current queue: entries and edges
     uint32_t iso_active; // the zero-degree class is in the frontier
     uint32_t err;        // compaction look-back error
+    uint32_t ticket;     // of the compaction
     double n_iso;        // number of zero-degree vertices
     double x_iso;        // their common rank
     double D;            // rank held by zero-degree vertices
@@ -538,8 +539,9 @@ const uint8_t *run_pagerank_filtered(Ctx &c, Graph &g, double damping, double ve
     const int32_t *R = g.R.as<int32_t>(), *C = g.C.as<int32_t>();
     hipLaunchKernelGGL(pf_init, dim3(G), dim3(GFR_BLOCK), 0, s, R, n, x, contrib, keep);
     PfMarks mk{keep, part, (uint32_t)G, ctl, n, 1u};
+    uint32_t *ticket = c.in_order ? nullptr : &ctl->ticket;
     hipLaunchKernelGGL(compact_kernel<PfMarks>, dim3(cg.blocks), dim3(GFR_BLOCK), 0, s, R, n, nwords, cg.wpt, mk, q,
-                       (uint32_t)GATHER_CH, status, &ctl->parity, &ctl->err);
+                       (uint32_t)GATHER_CH, status, &ctl->parity, &ctl->err, ticket);
     GFR_LAUNCH_CHECK();
     mk.first = 0u;
 
@@ -552,7 +554,7 @@ const uint8_t *run_pagerank_filtered(Ctx &c, Graph &g, double damping, double ve
                            &ctl->mf, fin, gs, &ctl->done);
         hipLaunchKernelGGL(pf_finalize, dim3(G), dim3(GFR_BLOCK), 0, s, R, n, q, x, contrib, sum, keep, part, ctl);
         hipLaunchKernelGGL(compact_kernel<PfMarks>, dim3(cg.blocks), dim3(GFR_BLOCK), 0, s, R, n, nwords, cg.wpt, mk,
-                           q, (uint32_t)GATHER_CH, status, &ctl->parity, &ctl->err);
+                           q, (uint32_t)GATHER_CH, status, &ctl->parity, &ctl->err, ticket);
     };
     const int32_t first = max_iter < 8 ? max_iter : 8;
     run_until_done(c, &ctl->done, 1u, first, (int64_t)max_iter + 8, s, launch, sizeof h, nullptr, NoOutput(),
@@ -560,7 +562,7 @@ const uint8_t *run_pagerank_filtered(Ctx &c, Graph &g, double damping, double ve
     hipLaunchKernelGGL(pf_output, dim3(G), dim3(GFR_BLOCK), 0, s, R, n, x, keep, ctl, rank, active);
     GFR_LAUNCH_CHECK();
     memcpy(&h, c.pinned, sizeof h);
-    if (h.err) fail(GFR_E_DEVICE, "pagerank_filtered: frontier compaction look-back timed out");
+    if (h.err) fail_crowded("pagerank_filtered");
     *iters = (int32_t)h.iters;
     *l1 = h.l1;
     c.stats.v["iterations"] = h.iters;

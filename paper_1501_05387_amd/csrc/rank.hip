@@ -87,7 +87,8 @@ struct QueueBuilder {
     uint32_t nwords;
     CompactGeom cg;
     unsigned long long *status;
-    uint32_t *cw;   // [0] parity, [1] look-back error
+    uint32_t *cw;   // [0] parity, [1] look-back error, [2] ticket
+    bool in_order;
     static size_t bytes(int32_t n, int num_cu)
     {
         const uint32_t nw = (uint32_t)(((int64_t)n + 63) / 64) * 2u;
@@ -97,6 +98,7 @@ struct QueueBuilder {
     {
         nwords = (uint32_t)(((int64_t)n + 63) / 64) * 2u;
         cg = compact_geom(nwords, c.num_cu);
+        in_order = c.in_order;
         status = c.arena.take<unsigned long long>(2ull * cg.blocks);
         cw = c.arena.take<uint32_t>(64);
         Fills().add(status, 0u, 4ull * cg.blocks).add(cw, 0u, 64).run(s);
@@ -104,13 +106,13 @@ struct QueueBuilder {
     template <class M> void build(const Graph &g, M mk, FrontierQ q, hipStream_t s)
     {
         hipLaunchKernelGGL(compact_kernel<M>, dim3(cg.blocks), dim3(GFR_BLOCK), 0, s, g.R.as<int32_t>(), g.n, nwords,
-                           cg.wpt, mk, q, (uint32_t)GATHER_CH, status, cw, cw + 1);
+                           cg.wpt, mk, q, (uint32_t)GATHER_CH, status, cw, cw + 1, in_order ? nullptr : cw + 2);
         GFR_LAUNCH_CHECK();
     }
     void check(Ctx &c, hipStream_t s, const char *who)
     {
         read_back(c, cw + 1, 4, s);
-        if (c.pinned[0]) fail(GFR_E_DEVICE, std::string(who) + ": frontier compaction look-back timed out");
+        if (c.pinned[0]) fail_crowded(who);
     }
 };
 

@@ -46,7 +46,8 @@ struct SsspCtl {
     uint32_t dir;                // SS_PUSH / SS_PULL for the next relaxation
     float pull_alpha;            // pull when the near queue's edges exceed m / pull_alpha (0: never)
     unsigned long long m;
-    uint32_t pull_iters, pad;
+    uint32_t pull_iters;
+    uint32_t ticket;             // of the compaction
 };
 
 enum : uint32_t { SS_PUSH = 0, SS_PULL = 1 };
@@ -420,6 +421,7 @@ struct SsspFirst {
             ctl->unfit = 0;
             ctl->parity = 0;
             ctl->err = 0;
+            ctl->ticket = 0;
             ctl->splits = 0;
             ctl->near_entries = ctl->relaxed = ctl->improvements = ctl->far_entries = 0ull;
             ctl->dir = SS_PUSH;
@@ -1005,7 +1007,8 @@ void run_sssp(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStream_t s)
             });
         c.ktimer.run("sssp_compact", s, [&]() {
             hipLaunchKernelGGL(compact_kernel<SsspMarks>, dim3(cg.blocks), dim3(GFR_BLOCK), 0, s, a.R, n, nwords,
-                               cg.wpt, marks, a.q, chunk, status, &a.ctl->parity, &a.ctl->err);
+                               cg.wpt, marks, a.q, chunk, status, &a.ctl->parity, &a.ctl->err,
+                               c.in_order ? nullptr : &a.ctl->ticket);
         });
     };
     // every iteration relaxes or splits; the loop is bounded well below this cap
@@ -1016,7 +1019,7 @@ void run_sssp(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStream_t s)
                                             sizeof(SsspCtl), &key);
     SsspCtl h;
     memcpy(&h, c.pinned, sizeof(SsspCtl));
-    if (h.err) fail(GFR_E_DEVICE, "sssp: frontier compaction look-back timed out");
+    if (h.err) fail_crowded("sssp");
     if (h.unfit) sssp_check_unfit(c, g, dist, unfit_flag, s);
     c.stats.v["iterations"] += h.iter;
     c.stats.v["relaxations"] += (double)h.relaxed;

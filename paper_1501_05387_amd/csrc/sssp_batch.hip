@@ -74,7 +74,8 @@ struct BsCtl {
     uint32_t dir;                // BS_PUSH / BS_PULL for the next relaxation
     float pull_alpha;            // pull when the frontier's edges exceed m / pull_alpha (0: never)
     unsigned long long m;
-    uint32_t pull_iters, pad2;
+    uint32_t pull_iters;
+    uint32_t ticket;             // of the compaction
     unsigned long long lane_relaxed;   // (edge, query) relaxations: edges visited x queries active at the source
     uint32_t unfit;              // 32-bit rows: a relaxation's sum did not fit below 0xFFFFFFFF (checked after the batch)
     uint32_t pad3;
@@ -1219,6 +1220,7 @@ __global__ void bsssp_init(BsArgs a, Sources64 src, int32_t k, uint32_t delta, f
         ctl->pull_alpha = pull_alpha;
         ctl->m = (unsigned long long)a.R[a.n];
         ctl->pull_iters = 0;
+        ctl->ticket = 0;
     }
 }
 
@@ -1398,7 +1400,8 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
                         constexpr int W = decltype(B)::value;
                         hipLaunchKernelGGL(compact_kernel<BsMarks<W>>, dim3(cg.blocks), dim3(GFR_BLOCK), 0, s, a.R,
                                            n, nwords, cg.wpt, BsMarks<W>{a, (uint32_t)G, cg.blocks, cg.wpt == 1u}, a.q, chunk,
-                                           status, &a.ctl->parity, &a.ctl->err);
+                                           status, &a.ctl->parity, &a.ctl->err,
+                                           c.in_order ? nullptr : &a.ctl->ticket);
                     });
                 });
             };
@@ -1446,7 +1449,7 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
             run_until_done(c, &a.ctl->mode, BS_DONE, g.bsssp_iter_hint.load(std::memory_order_relaxed) + 1,
                            64ll * n + 1024, s, launch, sizeof(BsCtl), &key, output);
             memcpy(&h, c.pinned, sizeof(BsCtl));
-            if (h.err) fail(GFR_E_DEVICE, "sssp_batch: frontier compaction look-back timed out");
+            if (h.err) fail_crowded("sssp_batch");
             g.bsssp_iter_hint.store((int32_t)h.iter, std::memory_order_relaxed);
             if (bits < 32 && h.overflow) {
                 // a distance outgrew the narrow rows: this batch again, twice as wide
@@ -1550,6 +1553,7 @@ __global__ void bs_session_init(BsArgs a, float pull_alpha)
     ctl->pull_alpha = pull_alpha;
     ctl->m = (unsigned long long)a.R[a.n];
     ctl->pull_iters = 0;
+    ctl->ticket = 0;
 }
 
 namespace {
@@ -1681,7 +1685,7 @@ struct BsSession final : LaneSession {
         if (pull) hipLaunchKernelGGL((bsssp_pull<1024, 32>), dim3(G), dim3(GFR_BLOCK), 0, stream, a);
         hipLaunchKernelGGL(compact_kernel<BsMarks<32>>, dim3(cg.blocks), dim3(GFR_BLOCK), 0, stream, a.R, a.n,
                            nwords, cg.wpt, BsMarks<32>{a, (uint32_t)G, cg.blocks, cg.wpt == 1u}, a.q, 1024u, status,
-                           &a.ctl->parity, &a.ctl->err);
+                           &a.ctl->parity, &a.ctl->err, &a.ctl->ticket);
         GFR_LAUNCH_CHECK();
         GFR_HIP(hipMemcpyAsync(pin, a.ctl, sizeof(BsCtl), hipMemcpyDeviceToHost, stream));
     }

@@ -730,3 +730,70 @@ def test_regular_graph_bfs_around_the_mark_byte_line(ctx, degree):
         assert np.array_equal(_host(d), want)
         assert np.array_equal(_host(ctx.bfs_noalloc(g, src, d)), want)
     g.free()
+
+
+def _sparse(n, m, seed):
+    rng = np.random.default_rng(seed)
+    return graphgen.from_edges(n, rng.integers(0, n, m), rng.integers(0, n, m))
+
+
+@pytest.mark.parametrize("n", [8192, 8193, 300007, 4194304, 4194369])
+def test_compactions_placed_by_their_start(ctx, n):
+    """A second context's work-groups take their places as they start; the results are those of the first."""
+    import paper_1501_05387_amd as gfr
+    row, col = _sparse(n, 2 * n, n)   # one work-group, two, 37, 512 and two words a thread
+    w = graphgen.weights(row, col, 64)
+    srcs = graphgen.sample_sources(row, col, 3)
+    with gfr.Context(0, tuning_json=gfr.tuned_json()) as other:
+        got = []
+        for c in (ctx, other):
+            g = c.graph_load_csr(row, col, w)
+            c.set_option("bfs.frontier", 1)
+            c.set_option("sssp.frontier", 1)
+            try:
+                out = [_host(c.bfs(g, int(srcs[0]))), _host(c.sssp(g, int(srcs[1]))).view(np.uint32)]
+                assert np.array_equal(out[0], oracle.bfs(row, col, int(srcs[0])))
+                assert np.array_equal(out[1], oracle.sssp(row, col, w, int(srcs[1])))
+                out += [_host(c.bfs_batch(g, srcs)), _host(c.sssp_batch(g, srcs)), _host(c.bc(g, srcs[:2])),
+                        _host(c.two_hop(g, srcs)), _host(c.pagerank_filtered(g, 0.85, 1e-4 / n, 30)[0])]
+            finally:
+                c.set_option("bfs.frontier", 0)
+                c.set_option("sssp.frontier", 0)
+                g.free()
+            got.append(out)
+        for a, b in zip(*got):
+            assert np.array_equal(a, b)
+
+
+def test_compactions_of_contexts_side_by_side(ctx):
+    """Grids that each fill the chip wait inside themselves only: no context's look-back runs out."""
+    import threading
+    import torch
+    import paper_1501_05387_amd as gfr
+    row, col = _sparse(4194304, 4194304, 11)
+    src = int(graphgen.sample_sources(row, col, 1)[0])
+    want = torch.from_numpy(oracle.bfs(row, col, src)).cuda()
+    wrong = []
+
+    def calls(c, k):
+        g = c.graph_load_csr(row, col)
+        c.set_option("bfs.frontier", 1)
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for i in range(30):
+                    out = c.bfs(g, src) if i % 3 else c.bfs_batch(g, [src])
+                    if not torch.equal(out.view(-1), want):
+                        wrong.append((k, i))
+        except Exception as e:   # a look-back that ran out
+            wrong.append((k, str(e)))
+        finally:
+            c.set_option("bfs.frontier", 0)
+            g.free()
+
+    with gfr.Context(0) as second, gfr.Context(0) as third:
+        threads = [threading.Thread(target=calls, args=(c, k)) for k, c in enumerate((ctx, second, third))]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    assert not wrong

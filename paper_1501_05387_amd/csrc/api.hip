@@ -3,6 +3,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <map>
 #include <mutex>
@@ -75,25 +76,30 @@ static void *noalloc_scratch(int device)
     return ptr;
 }
 
-// Each device's context whose compactions start in order (Ctx::in_order): the
-// first one that finds none, until it is destroyed.
-static std::mutex order_mu;
-static std::map<int, const Ctx *> order_of;
+// The context of each device whose call's compactions start in order (Ctx::in_order).
+constexpr int ORDERED_DEVICES = 64;   // on devices past these every compaction takes tickets
+static std::atomic<const Ctx *> order_of[ORDERED_DEVICES];
 
-static void claim_order(Ctx &c)
-{
-    std::lock_guard<std::mutex> lk(order_mu);
-    c.in_order = order_of.emplace(c.device, &c).second;
-}
-
-static bool release_order(Ctx &c)   // false: it was not this context
-{
-    std::lock_guard<std::mutex> lk(order_mu);
-    if (!c.in_order) return false;
-    order_of.erase(c.device);
-    c.in_order = false;
-    return true;
-}
+// For the time of a call: this context's compactions start in order if no other
+// context's do.  A call returns when its work is over; one that fails may leave
+// some behind, and a wait that runs out for that only makes a call run twice.
+struct InOrder {
+    Ctx &c;
+    std::atomic<const Ctx *> *slot = nullptr;
+    explicit InOrder(Ctx &cc) : c(cc)
+    {
+        const Ctx *none = nullptr;
+        if (c.in_order || c.crowded || c.device < 0 || c.device >= ORDERED_DEVICES) return;
+        if (order_of[c.device].compare_exchange_strong(none, &c)) slot = &order_of[c.device];
+        c.in_order = slot != nullptr;
+    }
+    ~InOrder()
+    {
+        if (!slot) return;
+        c.in_order = false;
+        slot->store(nullptr);
+    }
+};
 
 // true if p is device memory of `device`
 static bool is_device_ptr_on(const void *p, int device)
@@ -363,9 +369,15 @@ static gfr_status guard(gfr_ctx *ctx, F f)
     try {
         c.err.clear();
         GFR_HIP(hipSetDevice(c.device));
+        InOrder turn(c);
         const auto in_turn = [&]() {
             call_again_if([&]() { f(c); },
-                          [&](const Error &e) { return e.crowded && release_order(c); });   // another process's
+                          [&](const Error &e) {
+                              if (!e.crowded || !c.in_order) return false;
+                              c.in_order = false;   // (until the call's end, and then for good)
+                              c.crowded = true;
+                              return true;
+                          });
         };
         with_room(in_turn, [&]() { return give_back_spares(c); });
         return GFR_OK;
@@ -675,7 +687,6 @@ gfr_status gfr_ctx_create(int32_t device, const char *tuning_json, gfr_ctx **out
         GFR_HIP(hipStreamCreateWithFlags(&cc.stream, hipStreamDefault));
         cc.noalloc_scratch = noalloc_scratch(device);
         alloc_pinned(cc);
-        claim_order(cc);
         GFR_HIP(hipEventCreate(&cc.ev0));
         GFR_HIP(hipEventCreate(&cc.ev1));
         cc.zero_word.alloc(256);
@@ -700,7 +711,6 @@ gfr_status gfr_ctx_destroy(gfr_ctx *ctx)
     Ctx *c = (Ctx *)ctx;
     (void)hipSetDevice(c->device);
     serve_shutdown(*c);
-    release_order(*c);
     c->graphs.clear();
     c->step_graphs.clear();
     c->arena.mem.release();

@@ -1011,7 +1011,7 @@ void run_bfs(Ctx &c, Graph &g, int32_t src, int32_t *depth, hipStream_t s, Arena
     };
     // (no captured steps over fixed scratch: instantiating a graph may allocate)
     StepKey key("bfs");
-    key.add(a).add(G).add(cg).add(chunk).add(status);
+    key.add(a).add(G).add(cg).add(chunk).add(status).add(c.in_order);
     const int32_t launched = run_until_done(c, &a.ctl->dir, DIR_DONE, g.levels_hint() + 1,
                                             (int64_t)n + 4, s, launch, sizeof(BfsCtl),
                                             ar.fixed ? nullptr : &key);

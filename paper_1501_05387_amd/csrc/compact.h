@@ -305,8 +305,9 @@ __device__ __forceinline__ void chunk_starts(const uint32_t *o, uint32_t cnt, ui
 // With a ticket (0 before the launch and after it) the place is the number of the
 // group's start: whoever has a smaller one has started, and waits for nobody with
 // a larger one.  The ticket costs 1 us a launch (BFS of R-MAT with 4 M vertices
-// 279 us, 270 without; four sources of BC on 1 M 2,366 and 2,352), so the one
-// context whose calls cannot meet another compaction goes without (Ctx::in_order).
+// 279 us, 270 without; four sources of BC on 1 M 2,366 and 2,352), so one
+// call at a time goes without (Ctx::in_order): beside groups that take tickets its
+// own find room sooner or later.
 __device__ __forceinline__ uint32_t scan_place(uint32_t *ticket)
 {
     if (!ticket || gridDim.x == 1) return blockIdx.x;

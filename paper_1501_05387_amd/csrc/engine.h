@@ -359,12 +359,12 @@ struct Ctx {
     DevMem zero_word;             // a device word that always holds 0
     uint32_t *pinned = nullptr;   // small pinned host buffer for control readbacks (alloc_pinned)
     uint32_t arrivals = 0;        // number of the newest read-back (see await_arrival)
-    // No other compaction of this process runs beside this context's (scan_place):
-    // its calls are made one at a time, and it is the only context on its device
-    // that says so.  Serving sessions and threads never do.  Where another
-    // process's compactions make a wait run out all the same, the call is made
-    // again with places by start, as are all after it.
+    // No other compaction of this process that starts in order runs beside those of
+    // the running call (scan_place): the calls of a context are made one at a time,
+    // and one context on a device says so at a time.  Serving sessions and threads
+    // never do.
     bool in_order = false;
+    bool crowded = false;         // a wait ran out all the same (another process): never in order again
     bool waited = false;          // set by a solver whose last queued work the host has waited for
     Options opt;                  // in effect; per-class values are applied by OptScope
     Tuning tuning;

@@ -480,7 +480,7 @@ void run_bfs_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, int32_t 
             });
         };
         StepKey key("msbfs");
-        key.add(a).add(G).add(cg).add(chunk).add(status);
+        key.add(a).add(G).add(cg).add(chunk).add(status).add(c.in_order);
         const auto output = [&]() {
             c.ktimer.run("msbfs_output", s, [&]() {
                 hipLaunchKernelGGL(msbfs_output, dim3(grid_blocks(c, 8)), dim3(GFR_BLOCK), 0, s, a);

@@ -1014,7 +1014,7 @@ void run_sssp(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStream_t s)
     // every iteration relaxes or splits; the loop is bounded well below this cap
     const int64_t cap = 64ll * n + 1024;
     StepKey key("sssp");
-    key.add(a).add(G).add(cg).add(chunk).add(status).add(pull);
+    key.add(a).add(G).add(cg).add(chunk).add(status).add(c.in_order).add(pull);
     const int32_t launched = run_until_done(c, &a.ctl->mode, SS_DONE, g.iter_hint() + 1, cap, s, launch,
                                             sizeof(SsspCtl), &key);
     SsspCtl h;

@@ -1436,7 +1436,7 @@ void run_sssp_batch(Ctx &c, Graph &g, const int32_t *sources, int32_t k, uint32_
                 compact();
             };
             StepKey key("bsssp");
-            key.add(a).add(G).add(Gw).add(cg).add(chunk).add(status).add(bits).add(pair).add(pull_alpha);
+            key.add(a).add(G).add(Gw).add(cg).add(chunk).add(status).add(c.in_order).add(bits).add(pair).add(pull_alpha);
             const auto output = [&]() {
                 if (bits != 32) return;   // a fallback may follow (a failed batch of 32-bit rows fails the call)
                 if (half)

@@ -739,30 +739,50 @@ def _sparse(n, m, seed):
 
 @pytest.mark.parametrize("n", [8192, 8193, 300007, 4194304, 4194369])
 def test_compactions_placed_by_their_start(ctx, n):
-    """A second context's work-groups take their places as they start; the results are those of the first."""
+    """Beside another context's call the work-groups take their places as they start; the results stay."""
+    import threading
     import paper_1501_05387_amd as gfr
     row, col = _sparse(n, 2 * n, n)   # one work-group, two, 37, 512 and two words a thread
     w = graphgen.weights(row, col, 64)
     srcs = graphgen.sample_sources(row, col, 3)
-    with gfr.Context(0, tuning_json=gfr.tuned_json()) as other:
-        got = []
-        for c in (ctx, other):
-            g = c.graph_load_csr(row, col, w)
-            c.set_option("bfs.frontier", 1)
-            c.set_option("sssp.frontier", 1)
-            try:
-                out = [_host(c.bfs(g, int(srcs[0]))), _host(c.sssp(g, int(srcs[1]))).view(np.uint32)]
-                assert np.array_equal(out[0], oracle.bfs(row, col, int(srcs[0])))
-                assert np.array_equal(out[1], oracle.sssp(row, col, w, int(srcs[1])))
-                out += [_host(c.bfs_batch(g, srcs)), _host(c.sssp_batch(g, srcs)), _host(c.bc(g, srcs[:2])),
-                        _host(c.two_hop(g, srcs)), _host(c.pagerank_filtered(g, 0.85, 1e-4 / n, 30)[0])]
-            finally:
-                c.set_option("bfs.frontier", 0)
-                c.set_option("sssp.frontier", 0)
-                g.free()
-            got.append(out)
-        for a, b in zip(*got):
-            assert np.array_equal(a, b)
+    prow, pcol = graphgen.from_edges(20000, np.arange(19999), np.arange(1, 20000))
+    stop, ran = threading.Event(), []
+
+    def beside(c):   # calls of 20,000 levels, one after the other
+        g = c.graph_load_csr(prow, pcol)
+        c.set_option("bfs.frontier", 1)
+        while not stop.is_set():
+            ran.append(int(c.bfs(g, 0).max()))
+
+    g = ctx.graph_load_csr(row, col, w)
+    ctx.set_option("bfs.frontier", 1)
+    ctx.set_option("sssp.frontier", 1)
+    try:
+        with gfr.Context(0) as other:
+            got = []
+            for crowd in (False, True):
+                t = threading.Thread(target=beside, args=(other,)) if crowd else None
+                if t:
+                    t.start()
+                    while not ran:
+                        stop.wait(0.01)
+                out = [_host(ctx.bfs(g, int(srcs[0]))), _host(ctx.sssp(g, int(srcs[1]))).view(np.uint32),
+                       _host(ctx.bfs_batch(g, srcs)), _host(ctx.sssp_batch(g, srcs)), _host(ctx.bc(g, srcs[:2])),
+                       _host(ctx.two_hop(g, srcs)), _host(ctx.pagerank_filtered(g, 0.85, 1e-4 / n, 30)[0])]
+                if t:
+                    stop.set()
+                    t.join()
+                got.append(out)
+            assert set(ran) == {19999}
+    finally:
+        stop.set()
+        ctx.set_option("bfs.frontier", 0)
+        ctx.set_option("sssp.frontier", 0)
+        g.free()
+    assert np.array_equal(got[0][0], oracle.bfs(row, col, int(srcs[0])))
+    assert np.array_equal(got[0][1], oracle.sssp(row, col, w, int(srcs[1])))
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
 
 
 def test_compactions_of_contexts_side_by_side(ctx):

@@ -76,30 +76,32 @@ static void *noalloc_scratch(int device)
     return ptr;
 }
 
-// The context of each device whose call's compactions start in order (Ctx::in_order).
+// the context of each device whose compactions start in order
 constexpr int ORDERED_DEVICES = 64;   // on devices past these every compaction takes tickets
 static std::atomic<const Ctx *> order_of[ORDERED_DEVICES];
 
-// For the time of a call: this context's compactions start in order if no other
-// context's do.  A call returns when its work is over; one that fails may leave
-// some behind, and a wait that runs out for that only makes a call run twice.
-struct InOrder {
-    Ctx &c;
-    std::atomic<const Ctx *> *slot = nullptr;
-    explicit InOrder(Ctx &cc) : c(cc)
-    {
-        const Ctx *none = nullptr;
-        if (c.in_order || c.crowded || c.device < 0 || c.device >= ORDERED_DEVICES) return;
-        if (order_of[c.device].compare_exchange_strong(none, &c)) slot = &order_of[c.device];
-        c.in_order = slot != nullptr;
-    }
-    ~InOrder()
-    {
-        if (!slot) return;
-        c.in_order = false;
-        slot->store(nullptr);
-    }
-};
+InOrder::InOrder(Ctx &cc) : c(cc)
+{
+    const Ctx *none = nullptr;
+    if (c.in_order || c.crowded || c.device < 0 || c.device >= ORDERED_DEVICES) return;
+    if (order_of[c.device].compare_exchange_strong(none, &c)) slot = &order_of[c.device];
+    c.in_order = slot != nullptr;
+}
+
+InOrder::~InOrder()
+{
+    if (!slot) return;
+    c.in_order = false;
+    slot->store(nullptr);
+}
+
+bool InOrder::again(const Error &e)
+{
+    if (!e.crowded || !c.in_order) return false;
+    c.in_order = false;
+    c.crowded = true;
+    return true;
+}
 
 // true if p is device memory of `device`
 static bool is_device_ptr_on(const void *p, int device)
@@ -371,13 +373,7 @@ static gfr_status guard(gfr_ctx *ctx, F f)
         GFR_HIP(hipSetDevice(c.device));
         InOrder turn(c);
         const auto in_turn = [&]() {
-            call_again_if([&]() { f(c); },
-                          [&](const Error &e) {
-                              if (!e.crowded || !c.in_order) return false;
-                              c.in_order = false;   // (until the call's end, and then for good)
-                              c.crowded = true;
-                              return true;
-                          });
+            call_again_if([&]() { f(c); }, [&](const Error &e) { return turn.again(e); });
         };
         with_room(in_turn, [&]() { return give_back_spares(c); });
         return GFR_OK;

@@ -359,10 +359,7 @@ struct Ctx {
     DevMem zero_word;             // a device word that always holds 0
     uint32_t *pinned = nullptr;   // small pinned host buffer for control readbacks (alloc_pinned)
     uint32_t arrivals = 0;        // number of the newest read-back (see await_arrival)
-    // No other compaction of this process that starts in order runs beside those of
-    // the running call (scan_place): the calls of a context are made one at a time,
-    // and one context on a device says so at a time.  Serving sessions and threads
-    // never do.
+    // The running call's compactions start in order (InOrder).
     bool in_order = false;
     bool crowded = false;         // a wait ran out all the same (another process): never in order again
     bool waited = false;          // set by a solver whose last queued work the host has waited for
@@ -601,6 +598,21 @@ __device__ __forceinline__ void arrive(uint32_t *pinned, uint32_t k)
 {
     __hip_atomic_store(pinned + ARRIVAL_WORD, k, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
+
+// Held for the time of a call, or of a query that a serving thread solves alone:
+// its compactions start in order (scan_place) if no others on the device do.
+// Sessions' never do.  The work is over when it is given back; a call that failed
+// may leave some behind, and a wait that runs out for that, or beside another
+// process, only makes a call run twice.
+struct InOrder {
+    Ctx &c;
+    std::atomic<const Ctx *> *slot = nullptr;
+    explicit InOrder(Ctx &c);
+    ~InOrder();
+    InOrder(const InOrder &) = delete;
+    InOrder &operator=(const InOrder &) = delete;
+    bool again(const Error &e);   // true: make the call again, with places by start from now on
+};
 
 // Spin on a device word until the speculative level loop reports completion.
 // Launches `launch()` batches and reads `bytes` at flag_dev (the control block,

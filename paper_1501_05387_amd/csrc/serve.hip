@@ -277,8 +277,13 @@ static void run_one(Server *sv, SingleCtx &sc, gfr_ticket t)
         const size_t row = 4ull * g->n;
         if (sc.stage.bytes < row) sc.stage.alloc(row);
         hipStream_t s = sc.c.stream;
-        if (q.kind == GFR_Q_BFS) run_bfs(sc.c, *g, q.source, sc.stage.as<int32_t>(), s);
-        else run_sssp(sc.c, *g, q.source, sc.stage.as<uint32_t>(), s);
+        InOrder turn(sc.c);
+        call_again_if(
+            [&]() {
+                if (q.kind == GFR_Q_BFS) run_bfs(sc.c, *g, q.source, sc.stage.as<int32_t>(), s);
+                else run_sssp(sc.c, *g, q.source, sc.stage.as<uint32_t>(), s);
+            },
+            [&](const Error &e) { return turn.again(e); });
         if (q.out_on_device) GFR_HIP(hipMemcpyAsync(q.out, sc.stage.p, row, hipMemcpyDeviceToDevice, s));
         else copy_to_host(sc.bounce, q.out, sc.stage.p, row, s);
         GFR_HIP(hipStreamSynchronize(s));

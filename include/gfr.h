@@ -303,7 +303,8 @@ gfr_status gfr_cc(gfr_ctx *ctx, gfr_graph g, int32_t *label_out, int32_t *num_co
  * memory).  The second call on the graph makes it, or the first one where that
  * already pays (max_iter >= 8, l1_tol <= 1e-3 and 10 * 2^20 entries, or l1_tol <= 1e-2
  * and 2^25 entries).  Without room for it the CSR is used, and it is given back
- * when another call on the context runs out of device memory.
+ * when another call on the context runs out of device memory (queries in service do not
+ * ask for it).
  */
 gfr_status gfr_pagerank(gfr_ctx *ctx, gfr_graph g, float damping, double l1_tol,
                         int32_t max_iter, float *rank_out, int32_t *iters_out,

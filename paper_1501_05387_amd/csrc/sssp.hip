@@ -944,11 +944,12 @@ void run_sssp(Ctx &c, Graph &g, int32_t src, uint32_t *dist, hipStream_t s)
     const uint32_t delta = c.opt.sssp_delta > 0 ? (uint32_t)c.opt.sssp_delta : sssp_auto_delta(g, c.opt.sssp_delta_factor);
     // mark-byte iterations on mesh-like graphs of at most six edges per vertex,
     // whose near sets are thin and whose rows one thread takes in one turn:
-    // 1.4 ms against 3.0 on the 1000^2 lattice, 6.6 against 10.0 on the 4096^2
-    // one; random regular graphs of 1 M vertices with 4, 6, 8 and 12 edges
-    // each, packaged bucket width: 0.94 / 0.96, 1.26 / 1.30, 1.46 / 1.24 and
-    // 2.48 / 1.73 ms (a hub's row is worse: R-MAT, 1 M vertices, 75 against
-    // 1.0).  A pull sweep needs the queue.
+    // 1.5 ms against 3.0 on the 1000^2 lattice, 6.7 against 9.4 on the 4096^2
+    // one; random regular graphs with 4, 6, 8 and 12 edges each, packaged bucket
+    // width: 100,000 vertices 330 / 475, 359 / 442, 475 / 505 and 661 / 556 us, 1 M
+    // vertices 612 / 853, 800 / 1,019, 994 / 1,214 and 1,304 / 1,342 (a hub's row is
+    // worse: R-MAT, 1 M vertices, 75 ms against 1.0).  The line was drawn where marks
+    // were ahead with larger spans.  A pull sweep needs the queue.
     const int fr = c.opt.sssp_frontier;
     if (fr == 2 || (fr == 0 && g.cls == GRAPH_MESH && g.m <= 6ll * n && !(c.opt.sssp_pull_alpha > 0))) {
         run_sssp_marks(c, g, src, dist, s, delta);
